@@ -269,8 +269,7 @@ mpm_status enqueue_p2g(mpm_ctx *ctx, const mpm_particles *p, double dt, hipStrea
 }
 
 mpm_status enqueue_update(mpm_ctx *ctx, double dt, hipStream_t s) {
-    float g[3] = {(float)ctx->cfg.gravity[0], (float)ctx->cfg.gravity[1], (float)ctx->cfg.gravity[2]};
-    launch_grid_update(ctx->d, (float)dt, g, ctx->grid_pool, ctx->grid_table, s);
+    launch_grid_update(ctx->d, (float)dt, ctx->grid_pool, ctx->grid_table, s);
     return last_error();
 }
 
@@ -280,14 +279,17 @@ mpm_status enqueue_update(mpm_ctx *ctx, double dt, hipStream_t s) {
 // MLS path only, and not in deterministic mode.
 bool can_carry(const mpm_ctx *ctx) { return !ctx->d.det && !ctx->d.quadratic && ctx->d.transfer == MPM_TRANSFER_MLS; }
 
-mpm_status enqueue_g2p(mpm_ctx *ctx, mpm_particles *p, double dt, hipStream_t s, bool carry = false) {
+// inner (inside mpm_step, for every step but the last): no grid update was launched and
+// nobody reads this step's grid, so the G2P forms the updated velocities as it gathers
+// them, and the carried form is written where it exists.
+mpm_status enqueue_g2p(mpm_ctx *ctx, mpm_particles *p, double dt, hipStream_t s, bool inner = false) {
     if (ctx->p2g_done != p->state[p->current]) return MPM_E_INVALID;
     if (!p->state[p->current ^ 1]) return MPM_E_INVALID;
     if ((p->id[0] == nullptr) != (p->id[1] == nullptr)) return MPM_E_INVALID;
     if ((p->mat[0] == nullptr) != (p->mat[1] == nullptr)) return MPM_E_INVALID;
     const PartArgs pa = part_args(p, true);
-    carry = carry && can_carry(ctx);
-    launch_g2p(ctx->d, pa, (float)dt, ctx->grid_pool, ctx->grid_table, s, carry, ctx->g2p_carried);
+    const bool carry = inner && can_carry(ctx);
+    launch_g2p(ctx->d, pa, (float)dt, ctx->grid_pool, ctx->grid_table, s, carry, ctx->g2p_carried, inner);
     ctx->g2p_carried = false;
     ctx->carried = carry ? pa.out : nullptr;
     p->current ^= 1;
@@ -306,6 +308,7 @@ void fill_devctx(DevCtx &d, const mpm_config &cfg, const mpm_material *mats, int
     d.transfer = cfg.transfer;
     for (int i = 0; i < n_mat; ++i) d.mats[i] = dev_material(mats[i]);
     d.n_mat = n_mat;
+    for (int a = 0; a < 3; ++a) d.gravity[a] = (float)cfg.gravity[a];
     d.max_blocks = (int)cfg.max_blocks;
     d.nbv = (long long)d.geo.NB[0] * d.geo.NB[1] * d.geo.NB[2];
     d.tau_stride = (long long)cfg.max_particles;
@@ -440,7 +443,6 @@ mpm_status group_step(mpm_ctx *ctx, mpm_particles *p, double dt, JobStep &out) {
     out.d = ctx->d;
     out.pa = pa;
     out.dt = (float)dt;
-    for (int a = 0; a < 3; ++a) out.g[a] = (float)ctx->cfg.gravity[a];
     out.table = t;
     out.first = ready ? 0 : 1;
     p->current ^= 1;
@@ -538,10 +540,11 @@ mpm_status step_sequence(mpm_ctx *ctx, mpm_particles *p, double dt, int32_t nste
     if (!(ctx->cfg.flags & MPM_FLAG_FUSED_G2P2G)) {
         for (int k = 0; k < nsteps; ++k) {
             hipEvent_t *ev = event_slot(ctx, s);
+            const bool inner = k + 1 < nsteps;   // the last step leaves its updated grid for mpm_grid_read
             mpm_status st = enqueue_p2g(ctx, p, dt, s, ev, true);
-            if (st == MPM_OK) st = enqueue_update(ctx, dt, s);
+            if (st == MPM_OK && !inner) st = enqueue_update(ctx, dt, s);
             if (st == MPM_OK && ev) (void)hipEventRecord(ev[3], s);
-            if (st == MPM_OK) st = enqueue_g2p(ctx, p, dt, s, k + 1 < nsteps);
+            if (st == MPM_OK) st = enqueue_g2p(ctx, p, dt, s, inner);
             if (st == MPM_OK && ev) {
                 (void)hipEventRecord(ev[4], s);
                 ctx->ev_used += 1;

@@ -68,6 +68,7 @@ struct DevCtx {
     int transfer;          // 0 MLS, 1 APIC with exact kernel gradients, 2 PIC
     DevMaterial mats[kMaxMaterials];
     int n_mat;
+    float gravity[3];
     int max_blocks;
     long long nbv;         // number of virtual blocks
     uint32_t *key;         // per particle: block * 64 + cell of the current buffer
@@ -152,14 +153,13 @@ struct PartArgs {
 
 // One job's share of a step run for many jobs at once (one launch per phase, row y
 // of every grid working on job y): the job's device context and particles, its time
-// step and gravity, the page table and pool its sort builds and its P2G, update and
+// step, the page table and pool its sort builds and its P2G, update and
 // G2P use, and whether its keys, stamps and stress still have to be formed (first
 // step).
 struct JobStep {
     DevCtx d;
     PartArgs pa;           // in: this step's state, out: the other buffer
     float dt;
-    float g[3];
     int table;
     int first;
 };
@@ -818,13 +818,16 @@ void launch_stress(const DevCtx &d, const PartArgs &pa, hipStream_t s);
 // the P2G may keep where that G2P changed nothing (see DevCtx::bchg)
 void launch_p2g(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt, hipStream_t s, bool carried = false,
                 bool reuse = false);
-void launch_grid_update(const DevCtx &d, float dt, const float gravity[3], int gp, int gt, hipStream_t s);
+void launch_grid_update(const DevCtx &d, float dt, int gp, int gt, hipStream_t s);
 void launch_det_gather(const DevCtx &d, int gp, int gt, hipStream_t s);
 // carry: write the carried state (Q = (m B - dt V0 tau) D^-1 / dx in the B planes and no
 // stress, the packed remainder) for a P2G with `carried` that follows in the same step
-// sequence; carried: the input is such a state
+// sequence; carried: the input is such a state; fold: the grid holds the P2G's momenta
+// and the kernel forms the updated velocities itself as it gathers them (no grid update
+// was launched and no caller reads the grid before the next step's P2G; always so with
+// carry)
 void launch_g2p(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt, hipStream_t s, bool carry = false,
-                bool carried = false);
+                bool carried = false, bool fold = false);
 void launch_grid_export(const DevCtx &d, float *m, float *vec, int gp, int gt, int g0, int ng, hipStream_t s);
 void launch_block_order(const DevCtx &d, hipStream_t s);
 void launch_g2p2g(const DevCtx &d, const PartArgs &pa, float dt, int gp_in, int gt_in, int gp_out, int gt_out,

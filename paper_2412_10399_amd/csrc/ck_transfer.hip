@@ -64,6 +64,58 @@ __device__ __forceinline__ void wave_stamp(const DevCtx &d, int vb, int E) {
     }
 }
 
+// Addresses of a block's 341 tile nodes, which do not depend on the block: per entry the
+// tile node (bits 0-8: 5 x 5 x 5 of G-, then 6 x 6 x 6 of G+, x fastest), the neighbour
+// block holding it (bits 9-13, the index into nbr), its place in that pool block (bits
+// 14-22: grid and node) and in the padded P2G tile (bits 23-30).  The entries run block by
+// block, the block's own 64 nodes of either grid first: consecutive lanes then hold
+// consecutive nodes of one pool block, so a wave's load or atomic touches few cache lines
+// (the flush's atomics cost by the line), and no lane divides a tile index into
+// coordinates.  Against tile order with divided indices: k_g2p_cc 215.6 -> 213.7 us,
+// the first step's k_p2g 290 -> 281 us on the sand column.
+// Nodes past the last one of the lattice need no test: they lie in an allocated block or
+// in none (nbr -1), no particle contributes to them, and their mass is zero.
+struct TileTable {
+    uint32_t e[kTileNodes];
+};
+constexpr int kTY = 6, kTZ = 40;   // strides of the padded P2G tile, see below
+constexpr TileTable make_tile_table() {
+    TileTable t{};
+    int n = 0;
+    for (int pass = 0; pass < 2; ++pass)   // own nodes, then the neighbours'
+        for (int gi = 0; gi < 2; ++gi) {
+            const int g = 1 - gi;
+            for (int nb = 0; nb < 27; ++nb) {
+                if ((nb == 13) != (pass == 0)) continue;
+                for (int l = 0; l < 64; ++l) {
+                    // tile coordinates: the tile starts g nodes below the block
+                    const int x = 4 * (nb % 3 - 1) + (l & 3) + g, y = 4 * (nb / 3 % 3 - 1) + ((l >> 2) & 3) + g,
+                              z = 4 * (nb / 9 - 1) + (l >> 4) + g;
+                    const int w = 5 + g;
+                    if (x < 0 || y < 0 || z < 0 || x >= w || y >= w || z >= w) continue;
+                    const int ni = g * kTileMinus + x + w * (y + w * z);
+                    t.e[n++] = (uint32_t)ni | (uint32_t)nb << 9 | (uint32_t)(g * 256 + l) << 14 |
+                               (uint32_t)(x + kTY * y + kTZ * z) << 23;
+                }
+            }
+        }
+    return t;
+}
+__device__ const TileTable kTile = make_tile_table();
+
+struct TileNode {
+    int ni, nb, at, t, g;   // tile node, neighbour, offset in its pool block (channel 0), padded tile index, grid
+};
+__device__ __forceinline__ TileNode tile_entry(uint32_t e) {
+    TileNode q;
+    q.ni = (int)(e & 511u);
+    q.nb = (int)((e >> 9) & 31u);
+    q.at = (int)((e >> 14) & 511u);
+    q.t = (int)(e >> 23);
+    q.g = q.at >> 8;
+    return q;
+}
+
 // Map tile node `ni` (0..340) of block (bx,by,bz) to its grid (0 = G-, 1 = G+) and
 // global node coordinates.
 __device__ __forceinline__ void tile_node(int ni, int bx, int by, int bz, int &g, int &ix, int &iy, int &iz) {
@@ -293,7 +345,6 @@ static_assert((double)kMaxBlockParticles * 1099511627776.0 <= 2251799813685248.0
 // the 64 lanes of one atomic whose particles lie in distinct cells spread evenly over
 // the LDS banks; among the strides with that property these give the smallest tile
 // (189 and 236 words per channel for the 125 and 216 nodes).
-constexpr int kTY = 6, kTZ = 40;
 constexpr int kTileMStride = 4 * kTZ + 5 * kTY;   // words per channel, G- ([0,4]^3)
 constexpr int kTilePStride = 5 * kTZ + 6 * kTY;   // words per channel, G+ ([0,5]^3)
 constexpr double kMagic = 6755399441055744.0;                  // 1.5 * 2^52
@@ -781,6 +832,35 @@ __device__ __forceinline__ bool kept_block_order(const DevCtx &d, int r, int s, 
     return true;
 }
 
+// The four channels of tile node q, converted back from the fixed-point sums.
+__device__ __forceinline__ void tile_values(const TileNode &q, const unsigned long long *tile_m,
+                                            const unsigned long long *tile_p, double inv, float (&val)[4]) {
+    const unsigned long long *tb = q.g == 0 ? tile_m : tile_p;
+    const int cs = q.g == 0 ? kTileMStride : kTilePStride;
+#pragma unroll
+    for (int ch = 0; ch < 4; ++ch) val[ch] = (float)((double)(long long)tb[ch * cs + q.t] * inv);
+}
+
+// Adds every nonzero tile node to the pool, one float atomic per channel.
+__device__ __forceinline__ void flush_tile(const DevCtx &d, float *pool, const int *nbr, const unsigned long long *tile_m,
+                                           const unsigned long long *tile_p, double inv) {
+    for (int k = threadIdx.x; k < kTileNodes; k += kP2GThreads) {
+        const TileNode q = tile_entry(kTile.e[k]);
+        float val[4];
+        tile_values(q, tile_m, tile_p, inv, val);
+        if (val[0] == 0.0f && val[1] == 0.0f && val[2] == 0.0f && val[3] == 0.0f) continue;
+        const int ph = nbr[q.nb];
+        if (ph < 0) {
+            set_status(d.counters, ST_CAPACITY);
+            continue;
+        }
+        float *a = pool + (size_t)ph * kBlockFloats + q.at;
+#pragma unroll
+        for (int ch = 0; ch < 4; ++ch)
+            if (val[ch] != 0.0f) atomicAdd(a + ch * 64, val[ch]);
+    }
+}
+
 // Reduces a per-thread contribution bound over the workgroup (bmax in LDS, reset by
 // the caller before the preceding barrier) and returns the fixed-point scale.
 __device__ __forceinline__ double block_scale(float bnd, unsigned int *bmax) {
@@ -869,26 +949,7 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
                     scatter_pool(d, pool_of(d, gp), nbr, bx, by, bz, st);
             }
             lds_barrier();
-            for (int ni = tid; ni < kTileNodes; ni += kP2GThreads) {
-                int g, ix, iy, iz;
-                tile_node(ni, bx, by, bz, g, ix, iy, iz);
-                const int lx = ix - 4 * bx + g, ly = iy - 4 * by + g, lz = iz - 4 * bz + g;   // tile-local
-                const unsigned long long *tb = g == 0 ? tile_m : tile_p;
-                const int cs = g == 0 ? kTileMStride : kTilePStride;
-                const int t = lx + ly * kTY + lz * kTZ;
-                float val[4];
-#pragma unroll
-                for (int ch = 0; ch < 4; ++ch) val[ch] = (float)((double)(long long)tb[ch * cs + t] * inv_unit);
-                if (val[0] == 0.0f && val[1] == 0.0f && val[2] == 0.0f && val[3] == 0.0f) continue;
-                const long long a = pool_index(d, nbr, bx, by, bz, g, ix, iy, iz, 0);
-                if (a < 0) {
-                    set_status(d.counters, ST_CAPACITY);
-                    continue;
-                }
-#pragma unroll
-                for (int ch = 0; ch < 4; ++ch)
-                    if (val[ch] != 0.0f) atomicAdd(&pool_of(d, gp)[a + ch * 64], val[ch]);
-            }
+            flush_tile(d, pool_of(d, gp), nbr, tile_m, tile_p, inv_unit);
             lds_barrier();
             continue;
         }
@@ -916,36 +977,19 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
                     scatter_particle<kTY, kTZ, kTileMStride, kTilePStride>(st[k], st[k].c[0] - 4 * bx, st[k].c[1] - 4 * by,
                                                                            st[k].c[2] - 4 * bz, tile_m, tile_p, S);
             lds_barrier();
-            // ---- flush every nonzero tile node to the pool
+            // deterministic mode: the block's tile (the same thread owns a node in every
+            // pass, so later passes add to what it wrote before)
             const double inv = 1.0 / S;
-            for (int ni = tid; ni < kTileNodes; ni += kP2GThreads) {
-                int g, ix, iy, iz;
-                tile_node(ni, bx, by, bz, g, ix, iy, iz);
-                const int lx = ix - 4 * bx + g, ly = iy - 4 * by + g, lz = iz - 4 * bz + g;   // tile-local
-                const unsigned long long *tb = g == 0 ? tile_m : tile_p;
-                const int cs = g == 0 ? kTileMStride : kTilePStride;
-                const int t = lx + ly * kTY + lz * kTZ;
+            float *sg = d.stage + (size_t)r * kStageFloats;
+            for (int k = tid; k < kTileNodes; k += kP2GThreads) {
+                const TileNode q = tile_entry(kTile.e[k]);
                 float val[4];
+                tile_values(q, tile_m, tile_p, inv, val);
 #pragma unroll
-                for (int ch = 0; ch < 4; ++ch) val[ch] = (float)((double)(long long)tb[ch * cs + t] * inv);
-                if (d.det) {
-                    // deterministic mode: the block's tile (the same thread owns node ni in
-                    // every pass, so later passes add to what it wrote before)
-                    float *sg = d.stage + (size_t)r * kStageFloats + ni;
-#pragma unroll
-                    for (int ch = 0; ch < 4; ++ch)
-                        sg[ch * kTileNodes] = c0 == 0 ? val[ch] : sg[ch * kTileNodes] + val[ch];
-                    continue;
+                for (int ch = 0; ch < 4; ++ch) {
+                    float *w = sg + ch * kTileNodes + q.ni;
+                    *w = c0 == 0 ? val[ch] : *w + val[ch];
                 }
-                if (val[0] == 0.0f && val[1] == 0.0f && val[2] == 0.0f && val[3] == 0.0f) continue;
-                const long long a = pool_index(d, nbr, bx, by, bz, g, ix, iy, iz, 0);
-                if (a < 0) {
-                    set_status(d.counters, ST_CAPACITY);
-                    continue;
-                }
-#pragma unroll
-                for (int ch = 0; ch < 4; ++ch)
-                    if (val[ch] != 0.0f) atomicAdd(&pool_of(d, gp)[a + ch * 64], val[ch]);
             }
             lds_barrier();
         }
@@ -1046,10 +1090,23 @@ __global__ void __launch_bounds__(128) k_det_gather_multi(const JobStep *__restr
 // ---------------------------------------------------------------- grid update
 // Section 4.3 grid update on each grid: m v~ = m v + dt f (the stress impulse is
 // already in the momentum), plus gravity; v~ = 0 where m = 0 and on wall nodes.
+__device__ __forceinline__ void node_velocity(const DevCtx &d, float dt, int g, int ix, int iy, int iz, float m,
+                                              float p0, float p1, float p2, float (&v)[3]) {
+    const bool inside = ix >= d.geo.stick_lo[g] && iy >= d.geo.stick_lo[g] && iz >= d.geo.stick_lo[g] &&
+                        ix <= d.geo.stick_hi[g][0] && iy <= d.geo.stick_hi[g][1] && iz <= d.geo.stick_hi[g][2];
+    v[0] = v[1] = v[2] = 0.0f;
+    if (m > 0.0f && inside) {
+        const float im = fast_rcp(m);
+        v[0] = p0 * im + dt * d.gravity[0];
+        v[1] = p1 * im + dt * d.gravity[1];
+        v[2] = p2 * im + dt * d.gravity[2];
+    }
+}
+
 constexpr int kGridPer = 4;   // grid blocks per workgroup and pass of the update
 constexpr int kGridWGs = 3072;
 
-__device__ __forceinline__ void b_grid_update(const DevCtx &d, float dt, float g0, float g1, float g2, int gp, int gt) {
+__device__ __forceinline__ void b_grid_update(const DevCtx &d, float dt, int gp, int gt) {
     const int ng = (int)d.counters[ngb_slot(gt)];
     const int t = threadIdx.x;
     const int g = t >> 6, l = t & 63;
@@ -1077,31 +1134,17 @@ __device__ __forceinline__ void b_grid_update(const DevCtx &d, float dt, float g
             if (b >= ng) break;
             int bx, by, bz;
             block_coords(d.geo, vb[k], bx, by, bz);
-            const int ix = 4 * bx + lx, iy = 4 * by + ly, iz = 4 * bz + lz;
-            const bool inside = ix >= d.geo.stick_lo[g] && iy >= d.geo.stick_lo[g] && iz >= d.geo.stick_lo[g] &&
-                                ix <= d.geo.stick_hi[g][0] && iy <= d.geo.stick_hi[g][1] && iz <= d.geo.stick_hi[g][2];
-            float v0 = 0.0f, v1 = 0.0f, v2 = 0.0f;
-            if (m[k] > 0.0f && inside) {
-                const float im = fast_rcp(m[k]);
-                v0 = p0[k] * im + dt * g0;
-                v1 = p1[k] * im + dt * g1;
-                v2 = p2[k] * im + dt * g2;
-            }
+            float v[3];
+            node_velocity(d, dt, g, 4 * bx + lx, 4 * by + ly, 4 * bz + lz, m[k], p0[k], p1[k], p2[k], v);
             float *blk = pool_of(d, gp) + (size_t)b * kBlockFloats + g * 256;
-            blk[64 + l] = v0;
-            blk[128 + l] = v1;
-            blk[192 + l] = v2;
+            blk[64 + l] = v[0];
+            blk[128 + l] = v[1];
+            blk[192 + l] = v[2];
         }
     }
 }
 
-__global__ void __launch_bounds__(128) k_grid_update(DevCtx d, float dt, float g0, float g1, float g2, int gp, int gt) { b_grid_update(d, dt, g0, g1, g2, gp, gt); }
-
-// one launch for many jobs: workgroup row y runs job y
-__global__ void __launch_bounds__(128) k_grid_update_multi(const JobStep *__restrict__ jobs) {
-    const JobStep &J = jobs[blockIdx.y];
-    b_grid_update(J.d, J.dt, J.g[0], J.g[1], J.g[2], J.table, J.table);
-}
+__global__ void __launch_bounds__(128) k_grid_update(DevCtx d, float dt, int gp, int gt) { b_grid_update(d, dt, gp, gt); }
 
 // ---------------------------------------------------------------- G2P
 // v_p = 1/2 sum_k sum_i w v~_i,   B_p = 1/2 sum_k sum_i w v~_i (x_i - x_p)^T,
@@ -1363,6 +1406,17 @@ __device__ __forceinline__ int g2p_finish(const DevCtx &d, const PartArgs &pa, f
 // column; the quadratic and gradient G2P gain 9 %).
 constexpr int kG2PThreads = 128;
 
+// Workgroups per particle block, as a shift: 1, 2 or 4 of them, each taking every 2nd or
+// 4th pass of the block's particles and gathering the tile for itself.  A block of 512
+// particles is four passes one after the other, each bound by its chain of dependent
+// instructions; while the blocks leave workgroup slots of the GPU empty (256 CUs of six
+// 128-thread workgroups), the passes run side by side.  The lines: four workgroups up to
+// one round of the slots, two up to 10 workgroups per CU.  Measured (us per mpm_step step
+// at 124 / 343 / 576 / 897 / 1728 blocks of moving sand): one workgroup 66 / 74 / 77 / 86 /
+// 125, two - / - / 68.4 / 84.2 / 132, four 54 / 61 / 69.8 / - / -; G2P alone at 125 blocks
+// 23.4 -> 13.9 us.
+__device__ __forceinline__ int g2p_split(int np) { return np <= 256 * 6 / 4 ? 2 : np <= 256 * 10 / 2 ? 1 : 0; }
+
 // One pass of the G2P particle loop over particles j0 + thread of a block: `cur` holds
 // the particle's inputs (loaded a pass before); `nxt` loads those of the next pass from
 // the index pnext (loaded a pass before), and pnext the index after that.  Lanes past
@@ -1370,13 +1424,13 @@ constexpr int kG2PThreads = 128;
 // use of a particle's inputs wait for that particle's loads alone.
 template <bool kCarry, bool kCarried>
 __device__ __forceinline__ void g2p_pass(const DevCtx &d, const PartArgs &pa, float dt, const float *vt, int bx,
-                                         int by, int bz, int s, int cnt, uint32_t last, int j0, int E, G2PIn &cur,
-                                         G2PIn &nxt, uint32_t &pnext) {
+                                         int by, int bz, int s, int cnt, uint32_t last, int j0, int step, int E,
+                                         G2PIn &cur, G2PIn &nxt, uint32_t &pnext) {
     const int j = j0 + (int)threadIdx.x;
     const bool act = j < cnt;
     if (kCarried) unpack_remainder(d.geo, cur.rp, cur.xr);
     const uint32_t pn = pnext;   // the index first, then the next particle's inputs
-    pnext = ld_at(d.perm, min((uint32_t)(s + j + 2 * kG2PThreads), last));
+    pnext = ld_at(d.perm, min((uint32_t)(s + j + 2 * step), last));
     g2p_load_index(pa, pn, nxt, kCarried);
     const uint32_t out = (uint32_t)(s + j);
     CellCoord cc;
@@ -1409,6 +1463,62 @@ __device__ __forceinline__ void g2p_pass(const DevCtx &d, const PartArgs &pa, fl
     wave_stamp(d, sig, E + 1);
 }
 
+// Gathers the velocity tile of block (bx,by,bz) (kTileNodes nodes, three channels) by
+// the workgroup's threads; nodes outside active blocks are at rest.  The loads of all of
+// a thread's nodes are issued before any is used: one memory round trip for the tile.
+// kFold: the pool still holds the P2G's momenta, and the grid update is applied to each
+// node as it is gathered.  A node is gathered by 2.7 blocks on average in the interior of
+// a body, but that costs less than the update's own pass over the grid and its launch:
+// sand column, update 11 us + G2P 213.7 us -> G2P 221.5 us; 1,000 particles, a step
+// 47.2 -> 45.1 us; 262,144 particles in deterministic mode, 109 -> 104 us.
+template <bool kFold>
+__device__ __forceinline__ void gather_tile(const DevCtx &d, float dt, int gp, const int *nbr, int bx, int by, int bz,
+                                            float *vt) {
+    constexpr int kPer = (kTileNodes + kG2PThreads - 1) / kG2PThreads;
+    const float *pool = pool_of(d, gp);
+    float m[kPer], p[kPer][3];
+    TileNode q[kPer];
+    int ph[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        q[k] = tile_entry(kTile.e[min((int)threadIdx.x + k * kG2PThreads, kTileNodes - 1)]);
+        ph[k] = nbr[q[k].nb];
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const float *a = pool + (size_t)max(ph[k], 0) * kBlockFloats + q[k].at;
+        if (kFold) m[k] = a[0];
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) p[k][ch] = a[(1 + ch) * 64];
+    }
+    // (uniform) no node of the tile lies on a wall
+    const bool inner = kFold && 4 * min(bx, min(by, bz)) - 1 >= max(d.geo.stick_lo[0], d.geo.stick_lo[1]) &&
+                       4 * bx + 4 <= min(d.geo.stick_hi[0][0], d.geo.stick_hi[1][0]) &&
+                       4 * by + 4 <= min(d.geo.stick_hi[0][1], d.geo.stick_hi[1][1]) &&
+                       4 * bz + 4 <= min(d.geo.stick_hi[0][2], d.geo.stick_hi[1][2]);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        float v[3];
+        if (kFold) {
+            const float mk = ph[k] >= 0 ? m[k] : 0.0f;
+            if (inner) {
+                const float im = fast_rcp(mk);
+#pragma unroll
+                for (int ch = 0; ch < 3; ++ch) v[ch] = mk > 0.0f ? p[k][ch] * im + dt * d.gravity[ch] : 0.0f;
+            } else {
+                const int nb = q[k].nb, l = q[k].at & 63;
+                node_velocity(d, dt, q[k].g, 4 * (bx + nb % 3 - 1) + (l & 3), 4 * (by + nb / 3 % 3 - 1) + ((l >> 2) & 3),
+                              4 * (bz + nb / 9 - 1) + (l >> 4), mk, p[k][0], p[k][1], p[k][2], v);
+            }
+        } else {
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) v[ch] = ph[k] >= 0 ? p[k][ch] : 0.0f;
+        }
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) vt[ch * kTileNodes + q[k].ni] = v[ch];
+    }
+}
+
 // kCarry: the output is the carried state for the next P2G of the same step sequence
 // (Q in the B planes, the packed remainder); kCarried: so is the input.  The particle
 // loop runs two passes per trip, each reading the inputs the other loaded: the two
@@ -1416,69 +1526,69 @@ __device__ __forceinline__ void g2p_pass(const DevCtx &d, const PartArgs &pa, fl
 // of every pass would wait for every store of the pass.  kKept: the step's P2G was
 // b_p2g, which kept every block's neighbourhood (one load, not a page lookup that
 // waits for the block's id).
-template <bool kCarry = false, bool kCarried = false, bool kKept = false>
+template <bool kCarry = false, bool kCarried = false, bool kKept = false, bool kFold = false>
 __device__ __forceinline__ void b_g2p(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt) {
     __shared__ float vt[3 * kTileNodes];
     __shared__ int nbr[27];
     const int np = (int)d.counters[C_NPB];
     const int E = (int)d.counters[C_EPOCH];
     const int tid = threadIdx.x;
-    for (int base = 0; base < np; base += gridDim.x) {
-        const int r = round_block(base, np);
-        if (r < 0) continue;
+    const int sh = g2p_split(np), step = kG2PThreads << sh;
+    for (int base = 0; base < np << sh; base += gridDim.x) {
+        const int u = round_block(base, np << sh);
+        if (u < 0) continue;
+        const int r = u >> sh, first = (u & ((1 << sh) - 1)) * kG2PThreads;
         const int vb = d.plist[r];
         int bx, by, bz;
         block_coords(d.geo, vb, bx, by, bz);
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
-        if (cnt <= 0 || cnt > kMaxBlockParticles) continue;
+        if (cnt <= first || cnt > kMaxBlockParticles) continue;
         // the first particle's inputs load while the tile is gathered, and the index of
         // the one after
         const uint32_t last = (uint32_t)(s + cnt - 1);
         G2PIn qa, qb;
-        g2p_load_index(pa, ld_at(d.perm, min((uint32_t)(s + tid), last)), qa, kCarried);
-        uint32_t pnext = ld_at(d.perm, min((uint32_t)(s + tid + kG2PThreads), last));
+        g2p_load_index(pa, ld_at(d.perm, min((uint32_t)(s + first + tid), last)), qa, kCarried);
+        uint32_t pnext = ld_at(d.perm, min((uint32_t)(s + first + tid + step), last));
         if (kKept) {
             if (tid < 27) nbr[tid] = d.nbrs[27 * (size_t)r + tid];
         } else {
             load_neighbours(d, gt, bx, by, bz, nbr);
         }
         lds_barrier();
-        for (int ni = tid; ni < kTileNodes; ni += kG2PThreads) {
-            int g, ix, iy, iz;
-            tile_node(ni, bx, by, bz, g, ix, iy, iz);
-            const long long a = pool_index(d, nbr, bx, by, bz, g, ix, iy, iz, 1);
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) vt[ch * kTileNodes + ni] = a >= 0 ? pool_of(d, gp)[a + ch * 64] : 0.0f;
-        }
+        gather_tile<kFold>(d, dt, gp, nbr, bx, by, bz, vt);
         lds_barrier();
-        for (int j0 = 0; j0 < cnt; j0 += 2 * kG2PThreads) {   // the same trip count for every lane
-            g2p_pass<kCarry, kCarried>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0, E, qa, qb, pnext);
-            if (j0 + kG2PThreads < cnt)
-                g2p_pass<kCarry, kCarried>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0 + kG2PThreads, E, qb, qa, pnext);
+        for (int j0 = first; j0 < cnt; j0 += 2 * step) {   // the same trip count for every lane
+            g2p_pass<kCarry, kCarried>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0, step, E, qa, qb, pnext);
+            if (j0 + step < cnt)
+                g2p_pass<kCarry, kCarried>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0 + step, step, E, qb, qa, pnext);
         }
         lds_barrier();
     }
 }
 
-__global__ void __launch_bounds__(kG2PThreads) k_g2p(DevCtx d, PartArgs pa, float dt, int gp, int gt) { b_g2p(d, pa, dt, gp, gt); }
-// The forms inside an mpm_step sequence, whose P2G (k_p2g or k_p2g_carried) kept every
-// block's neighbourhood.
-__global__ void __launch_bounds__(kG2PThreads) k_g2p_carry(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
-    b_g2p<true, false, true>(d, pa, dt, gp, gt);
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p(DevCtx d, PartArgs pa, float dt, int gp, int gt) { b_g2p(d, pa, dt, gp, gt); }
+// The forms inside an mpm_step sequence, whose P2G (b_p2g) kept every block's
+// neighbourhood; every one but the last step's folds the grid update into its gather.
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_fold(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_g2p<false, false, true, true>(d, pa, dt, gp, gt);
 }
-__global__ void __launch_bounds__(kG2PThreads) k_g2p_cc(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
-    b_g2p<true, true, true>(d, pa, dt, gp, gt);
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_carry(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_g2p<true, false, true, true>(d, pa, dt, gp, gt);
 }
-__global__ void __launch_bounds__(kG2PThreads) k_g2p_cf(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_cc(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_g2p<true, true, true, true>(d, pa, dt, gp, gt);
+}
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_cf(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
     b_g2p<false, true, true>(d, pa, dt, gp, gt);
 }
 
 // one launch for many jobs: workgroup row y runs job y (every job's P2G of the round,
-// plain or deterministic, was b_p2g, which kept the neighbourhoods)
-__global__ void __launch_bounds__(kG2PThreads) k_g2p_multi(const JobStep *__restrict__ jobs) {
+// plain or deterministic, was b_p2g, which kept the neighbourhoods; nobody reads the
+// grid of a served job, so its update is folded into the gather)
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_multi(const JobStep *__restrict__ jobs) {
     const JobStep &J = jobs[blockIdx.y];
-    b_g2p<false, false, true>(J.d, J.pa, J.dt, J.table, J.table);
+    b_g2p<false, false, true, true>(J.d, J.pa, J.dt, J.table, J.table);
 }
 
 // ---------------------------------------------------------------- exact-gradient transfers
@@ -1664,27 +1774,7 @@ __global__ void __launch_bounds__(kP2GThreads) k_p2g_grad(DevCtx d, PartArgs pa,
                 if (st[k].on)
                     grad_scatter(st[k], st[k].c[0] - 4 * bx, st[k].c[1] - 4 * by, st[k].c[2] - 4 * bz, tile_m, tile_p, S);
             lds_barrier();
-            const double inv = 1.0 / S;
-            for (int ni = tid; ni < kTileNodes; ni += kP2GThreads) {
-                int g, ix, iy, iz;
-                tile_node(ni, bx, by, bz, g, ix, iy, iz);
-                const int lx = ix - 4 * bx + g, ly = iy - 4 * by + g, lz = iz - 4 * bz + g;
-                const unsigned long long *tb = g == 0 ? tile_m : tile_p;
-                const int cs = g == 0 ? kTileMStride : kTilePStride;
-                const int t = lx + ly * kTY + lz * kTZ;
-                float val[4];
-#pragma unroll
-                for (int ch = 0; ch < 4; ++ch) val[ch] = (float)((double)(long long)tb[ch * cs + t] * inv);
-                if (val[0] == 0.0f && val[1] == 0.0f && val[2] == 0.0f && val[3] == 0.0f) continue;
-                const long long a = pool_index(d, nbr, bx, by, bz, g, ix, iy, iz, 0);
-                if (a < 0) {
-                    set_status(d.counters, ST_CAPACITY);
-                    continue;
-                }
-#pragma unroll
-                for (int ch = 0; ch < 4; ++ch)
-                    if (val[ch] != 0.0f) atomicAdd(&pool_of(d, gp)[a + ch * 64], val[ch]);
-            }
+            flush_tile(d, pool_of(d, gp), nbr, tile_m, tile_p, 1.0 / S);
             lds_barrier();
         }
     }
@@ -1693,7 +1783,8 @@ __global__ void __launch_bounds__(kP2GThreads) k_p2g_grad(DevCtx d, PartArgs pa,
 // G2P with the exact velocity gradient: v = 1/2 sum w v~, B = 1/2 sum w v~ d^T (APIC;
 // zero for PIC), C = 1/2 sum v~ grad w^T, all relative to the velocity of one stencil
 // node (the weights of a grid sum to one, their gradients to zero).
-__global__ void __launch_bounds__(kG2PThreads) k_g2p_grad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+__global__ void __launch_bounds__(kG2PThreads) k_g2p_grad(DevCtx d, PartArgs pa, float dt, int gp, int gt,
+                                                          int fold) {
     __shared__ float vt[3 * kTileNodes];
     __shared__ int nbr[27];
     const bool pic = d.transfer == 2;
@@ -1713,13 +1804,8 @@ __global__ void __launch_bounds__(kG2PThreads) k_g2p_grad(DevCtx d, PartArgs pa,
         if (tid < cnt) g2p_load(d, pa, (uint32_t)(s + tid), nxt);
         load_neighbours(d, gt, bx, by, bz, nbr);
         lds_barrier();
-        for (int ni = tid; ni < kTileNodes; ni += kG2PThreads) {
-            int g, ix, iy, iz;
-            tile_node(ni, bx, by, bz, g, ix, iy, iz);
-            const long long a = pool_index(d, nbr, bx, by, bz, g, ix, iy, iz, 1);
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) vt[ch * kTileNodes + ni] = a >= 0 ? pool_of(d, gp)[a + ch * 64] : 0.0f;
-        }
+        if (fold) gather_tile<true>(d, dt, gp, nbr, bx, by, bz, vt);
+        else gather_tile<false>(d, dt, gp, nbr, bx, by, bz, vt);
         lds_barrier();
         for (int j0 = 0; j0 < cnt; j0 += kG2PThreads) {
             const int j = j0 + tid;
@@ -1989,7 +2075,8 @@ __global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_quad(DevCtx d, PartArgs 
     }
 }
 
-__global__ void __launch_bounds__(kG2PThreads) k_g2p_quad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+__global__ void __launch_bounds__(kG2PThreads) k_g2p_quad(DevCtx d, PartArgs pa, float dt, int gp, int gt,
+                                                          int fold) {
     __shared__ float vt[3 * kQNodes];
     __shared__ int nbr[27];
     const int np = (int)d.counters[C_NPB];
@@ -2010,9 +2097,12 @@ __global__ void __launch_bounds__(kG2PThreads) k_g2p_quad(DevCtx d, PartArgs pa,
         lds_barrier();
         for (int ni = tid; ni < kQNodes; ni += kG2PThreads) {
             const int ix = 4 * bx - 1 + ni % 7, iy = 4 * by - 1 + (ni / 7) % 7, iz = 4 * bz - 1 + ni / 49;
-            const long long a = pool_index(d, nbr, bx, by, bz, 0, ix, iy, iz, 1);
+            const long long a = pool_index(d, nbr, bx, by, bz, 0, ix, iy, iz, 0);
+            const float *q = pool_of(d, gp) + (a >= 0 ? a : 0);
+            float v[3] = {q[64], q[128], q[192]};
+            if (fold) node_velocity(d, dt, 0, ix, iy, iz, a >= 0 ? q[0] : 0.0f, v[0], v[1], v[2], v);
 #pragma unroll
-            for (int ch = 0; ch < 3; ++ch) vt[ch * kQNodes + ni] = a >= 0 ? pool_of(d, gp)[a + ch * 64] : 0.0f;
+            for (int ch = 0; ch < 3; ++ch) vt[ch * kQNodes + ni] = a >= 0 ? v[ch] : 0.0f;
         }
         lds_barrier();
         for (int j0 = 0; j0 < cnt; j0 += kG2PThreads) {
@@ -2310,23 +2400,26 @@ void launch_det_gather(const DevCtx &d, int gp, int gt, hipStream_t s) {
     hipLaunchKernelGGL(k_det_gather, dim3(d.max_blocks < kGridWGs ? d.max_blocks : kGridWGs), dim3(128), 0, s, d, gp, gt);
 }
 
-void launch_grid_update(const DevCtx &d, float dt, const float gravity[3], int gp, int gt, hipStream_t s) {
+void launch_grid_update(const DevCtx &d, float dt, int gp, int gt, hipStream_t s) {
     hipLaunchKernelGGL(k_grid_update, dim3(d.max_blocks < kGridWGs ? d.max_blocks : kGridWGs), dim3(128), 0, s, d, dt,
-                       gravity[0], gravity[1], gravity[2], gp, gt);
+                       gp, gt);
 }
 
 void launch_g2p(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt, hipStream_t s, bool carry,
-                bool carried) {
+                bool carried, bool fold) {
+    const int fo = fold ? 1 : 0;
     if (d.quadratic)
-        hipLaunchKernelGGL(k_g2p_quad, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt);
+        hipLaunchKernelGGL(k_g2p_quad, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt, fo);
     else if (d.transfer != 0)
-        hipLaunchKernelGGL(k_g2p_grad, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt);
+        hipLaunchKernelGGL(k_g2p_grad, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt, fo);
     else if (carry && carried)
         hipLaunchKernelGGL(k_g2p_cc, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt);
     else if (carry)
         hipLaunchKernelGGL(k_g2p_carry, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt);
     else if (carried)
         hipLaunchKernelGGL(k_g2p_cf, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt);
+    else if (fold)
+        hipLaunchKernelGGL(k_g2p_fold, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt);
     else
         hipLaunchKernelGGL(k_g2p, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt);
 }
@@ -2373,7 +2466,6 @@ void launch_step_run(const JobStep *dev, const JobStep *host, int njobs, hipStre
     if (any_plain) hipLaunchKernelGGL(k_p2g_multi, dim3(pgrid, njobs), dim3(kP2GThreads), 0, s, dev);
     if (any_det) hipLaunchKernelGGL(k_p2g_det_multi, dim3(pgrid, njobs), dim3(kP2GThreads), 0, s, dev);
     if (any_det) hipLaunchKernelGGL(k_det_gather_multi, dim3(ugrid, njobs), dim3(128), 0, s, dev);
-    hipLaunchKernelGGL(k_grid_update_multi, dim3(ugrid, njobs), dim3(128), 0, s, dev);
     hipLaunchKernelGGL(k_g2p_multi, dim3(pgrid, njobs), dim3(kG2PThreads), 0, s, dev);
 }
 
