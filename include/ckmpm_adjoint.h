@@ -16,9 +16,9 @@
  *
  * Particles keep their order (no sort).  mpm_ad_create allocates the grids once;
  * the calls allocate nothing.  When max_blocks covers every block of 4x4x4 nodes
- * of the (n+1)^3 node lattice, both staggered grids are dense (about 112 B per
+ * of the (n+1)^3 node lattice, both staggered grids are dense (about 96 B per
  * node).  Otherwise they are block-sparse: a pool of max_blocks blocks per grid
- * (about 7 KiB per block, plus 10 B per block of the whole lattice for the page
+ * (about 6 KiB per block, plus 10 B per block of the whole lattice for the page
  * tables); each call marks the blocks that its particles' stencils reach on each
  * grid, gives them pool slots and sweeps those slots only.  A call whose particles
  * reach more than max_blocks blocks on a grid reports MPM_E_CAPACITY (its results

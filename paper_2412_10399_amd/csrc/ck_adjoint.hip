@@ -40,27 +40,41 @@ struct mpm_ad_ctx {
     long long nbv = 0;        // nb[0] nb[1] nb[2]
     long long nodes = 0;      // nodes of one grid: (n+1)^3 when direct, else (cap + 1) * 64
                               // (pool slots, the last a spill slot)
-    float *grid = nullptr;    // 14 planes of 2 * nodes floats, see below
+    float4 *grid = nullptr;   // 3 arrays of 2 * nodes float4, see below
     int *page = nullptr;      // [grid][nbv]: pool slot of a block in this call, -1 if untouched
-    int *blist = nullptr;     // [grid][cap]: block of a slot
     bool direct = false;      // max_blocks covers the lattice: dense grids, no marking
     unsigned char *flag = nullptr;   // [grid][nbv]: touched by a particle's stencil
-    unsigned int *cnt = nullptr;     // [2]: slots taken per grid
+    unsigned int *ctl = nullptr;     // control words, see AdCtl
     unsigned int *status = nullptr;
 };
 
 namespace {
 
 // Grids.  When max_blocks covers every 4x4x4-node block of the lattice (`direct`),
-// the grids are dense, node (ix, iy, iz) at (iz ny + iy) nx + ix, and the sweeps run
-// over all nodes.  Otherwise they are block-sparse: each call marks the blocks that
-// its particles' stencils touch (k_ad_mark) and gives them pool slots (k_ad_alloc);
-// the node lives at page[g][block] * 64 + ((iz & 3) * 4 + (iy & 3)) * 4 + (ix & 3),
-// and the sweeps run over the taken slots only.  Past the pool's capacity a block
-// gets the spill slot `cap` (never swept, its values meaningless) and the call
+// the grids are dense, node (ix, iy, iz) at (iz ny + iy) nx + ix.  Otherwise they are
+// block-sparse: each call marks the blocks that its particles' stencils touch
+// (k_ad_mark) and gives them pool slots (k_ad_alloc); the node lives at
+// page[g][block] * 64 + ((iz & 3) * 4 + (iy & 3)) * 4 + (ix & 3).  Past the pool's
+// capacity a block gets the spill slot `cap` (its values meaningless) and the call
 // reports ST_CAPACITY.
-// Planes of the pool buffer (each 2 * nodes floats: G- then G+):
-enum GridPlane { GM = 0, GP = 1, GV = 4, GVB = 7, GMB = 10, GPB = 11, kGridPlanes = 14 };
+//
+// Arrays of 2 * nodes float4 (G- then G+), a node's values in one 16-byte load:
+//   X0, X1  (m, p0, p1, p2): the calls take turns.  P2G sums into one while other
+//           workgroups of its launch clear the one that the call before left behind;
+//   VB      dL/dv~ (three used): the scatter target of the reverse step, cleared in the
+//           same way after a reverse call.
+// There is no pass over the grid: G2P and its adjoint form the node velocities
+// v~ = p/m + dt g as they gather (m, p), and the P2G adjoint forms the node cotangents
+// from (m, p) and dL/dv~.  Which X a call uses is read from the control words, not
+// decided on the host, so that a captured sequence of calls can be replayed.
+enum AdCtl {
+    A_CUR = 0,     // X the next call uses; the call's second kernel writes it (nobody reads it there)
+    A_USE = 1,     // X of this call for the kernels after P2G, which writes it
+    A_VB = 2,      // VB holds an earlier call's sums; written by the call's second kernel
+    A_CNT = 4,     // [2]: slots taken per grid in this call (block-sparse)
+    A_PREV = 6,    // [2]: slots taken in the call before
+    kCtlWords = 8
+};
 
 struct AdArgs {
     Geometry geo;
@@ -69,23 +83,27 @@ struct AdArgs {
     int nx, ny;   // lattice nodes per axis (direct)
     int nbx, nby, cap;
     long long nbv, nodes;
-    float *grid;
-    int *page, *blist;
+    float4 *grid;
+    int *page;
     int direct;
     unsigned char *flag;
-    unsigned int *cnt;
+    unsigned int *ctl;
     unsigned int *status;
     int n;
+    int pgrid;    // workgroups that take particles, a multiple of 8 (those of P2G past them clear)
     long long stride;
     float dt;
 };
 
-__device__ __forceinline__ float *plane(const AdArgs &a, int k) { return a.grid + (long long)k * 2 * a.nodes; }
+__device__ __forceinline__ float4 *ad_x(const AdArgs &a, unsigned int which) {
+    return a.grid + ((which & 1u) ? 2 * a.nodes : 0);
+}
+__device__ __forceinline__ float4 *ad_vb(const AdArgs &a) { return a.grid + 4 * a.nodes; }
 
 // Sets status bits in the context's one status word (read by mpm_ad_sync).
 __device__ __forceinline__ void ad_status(const AdArgs &a, unsigned int bits) { atomicOr(a.status, bits); }
 
-// Index of node (ix, iy, iz) of grid g in the grid planes: dense, or in the pool
+// Index of node (ix, iy, iz) of grid g in the node arrays: dense, or in the pool
 // (kSparse; the node's block was marked by this call).
 template <bool kSparse>
 __device__ __forceinline__ long long ad_index(const AdArgs &a, int g, int ix, int iy, int iz) {
@@ -95,23 +113,40 @@ __device__ __forceinline__ long long ad_index(const AdArgs &a, int g, int ix, in
     return g * a.nodes + (long long)slot * 64 + (((iz & 3) * 4 + (iy & 3)) * 4 + (ix & 3));
 }
 
-// Node coordinates of local node l of pool slot `slot` of grid g (block-sparse).
-__device__ __forceinline__ void ad_coords(const AdArgs &a, int g, int slot, int l, int &ix, int &iy, int &iz) {
-    const int b = a.blist[(long long)g * a.cap + slot];
-    const int bxy = a.nbx * a.nby;
-    iz = 4 * (b / bxy) + (l >> 4);
-    iy = 4 * ((b % bxy) / a.nbx) + ((l >> 2) & 3);
-    ix = 4 * (b % a.nbx) + (l & 3);
+__device__ __forceinline__ bool node_free(const AdArgs &a, int g, int ix, int iy, int iz) {
+    return ix >= a.geo.stick_lo[g] && iy >= a.geo.stick_lo[g] && iz >= a.geo.stick_lo[g] &&
+           ix <= a.geo.stick_hi[g][0] && iy <= a.geo.stick_hi[g][1] && iz <= a.geo.stick_hi[g][2];
 }
 
 // ------------------------------------------------------------ particle stencil
+// Two neighbouring lanes share a particle: the even lane takes its stencil on G-, the odd
+// one on G+.  A workload of 65,536 particles is one wave per SIMD with a thread per
+// particle, bound by each wave's own chain of instructions; the pair halves the chain and
+// the registers (the reverse kernels held two grids' stencils in 256 and spilled).  Sums
+// over both grids are formed by one exchange within the pair (pair_sum).
 struct AdStencil {
-    int base[2][3];     // node base + o (o = 0, 1) on grid g, axis a
-    float w[2][3][2];   // per-axis weights
-    float dw[2][3][2];  // their derivatives with respect to X_a (cell units)
-    float s[2][3], c[2][3], xi[2][3];
-    float Dinv[9];      // D^-1 in world units
+    int base[3];        // nodes base + o (o = 0, 1) per axis
+    float w[3][2];      // per-axis weights
+    float dw[3];        // derivative of w[.][0] with respect to X_a (cell units); w[.][1] has its negative
+    float s[3], xi[3];
+    float Dinv[9];      // D^-1 in world units (of the particle)
 };
+
+__device__ __forceinline__ int pair_grid() { return (int)threadIdx.x & 1; }
+
+// Which 128 particles the workgroup takes.  Workgroups are dealt to the 8 XCDs round-robin
+// by index; each XCD gets a contiguous eighth of the particles, so that the nodes which
+// neighbouring rows of cells share meet in one L2 (119,223 particles, block-sparse: P2G
+// 27.4 -> 26.1 us, G2P adjoint 34.4 -> 33.4 us).
+__device__ __forceinline__ int ad_block(const AdArgs &a) {
+    return ((int)blockIdx.x & 7) * (a.pgrid >> 3) + ((int)blockIdx.x >> 3);
+}
+
+// v of this lane plus v of the pair's other lane (the same value on both).
+__device__ __forceinline__ float pair_sum(float v) {
+    const int o = __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true);   // quad_perm 1,0,3,2
+    return v + __int_as_float(o);
+}
 
 // X = (x + r - origin) / dx (the position is x + r, FP32 rounding and remainder,
 // summed in FP64); false when the particle is outside the valid domain.
@@ -124,56 +159,43 @@ __device__ __forceinline__ bool ad_position(const AdArgs &a, const float x[3], c
     return true;
 }
 
-// False (and nothing filled in) when the particle is outside the valid domain.
+// The lane's grid of the particle's stencil; false (and nothing filled in) when the
+// particle is outside the valid domain.  Both lanes of a pair call it together.
 __device__ __forceinline__ bool ad_stencil(const AdArgs &a, const float x[3], const float r[3], AdStencil &st) {
     constexpr float kInv2Pi = 0.15915494309189535f;
     float X[3];
     if (!ad_position(a, x, r, X)) return false;
+    const float k = pair_grid() ? 0.25f : -0.25f;
 #pragma unroll
-    for (int g = 0; g < 2; ++g) {
-        const float k = g == 0 ? -0.25f : 0.25f;
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            const float Xk = X[ax] - k;
-            const float b = floorf(Xk);
-            const float xi = Xk - b;
-            st.base[g][ax] = (int)b;
-            const float s = __builtin_amdgcn_sinf(xi) * kInv2Pi;   // argument in revolutions
-            const float c = __builtin_amdgcn_cosf(xi);
-            st.xi[g][ax] = xi;
-            st.s[g][ax] = s;
-            st.c[g][ax] = c;
-            st.w[g][ax][0] = 1.0f - xi + s;
-            st.w[g][ax][1] = xi - s;
-            st.dw[g][ax][0] = c - 1.0f;
-            st.dw[g][ax][1] = 1.0f - c;
-        }
+    for (int ax = 0; ax < 3; ++ax) {
+        const float Xk = X[ax] - k;
+        const float b = floorf(Xk);
+        const float xi = Xk - b;
+        st.base[ax] = (int)b;
+        const float s = __builtin_amdgcn_sinf(xi) * kInv2Pi;   // argument in revolutions
+        st.xi[ax] = xi;
+        st.s[ax] = s;
+        st.w[ax][0] = 1.0f - xi + s;
+        st.w[ax][1] = xi - s;
+        st.dw[ax] = __builtin_amdgcn_cosf(xi) - 1.0f;
     }
     // D / dx^2: diagonal 1/2 sum_k (xi (1 - xi) - s (1 - 2 xi)), off-diagonal
     // 1/2 sum_k s_a s_b (the first moments are -s on each grid)
-    float Dh[9];
+    float Dh[6];   // 00 11 22 01 02 12
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            float v = 0.0f;
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                if (i == j) {
-                    const float xi = st.xi[g][i];
-                    v += 0.5f * (xi * (1.0f - xi) - st.s[g][i] * (1.0f - 2.0f * xi));
-                } else {
-                    v += 0.5f * st.s[g][i] * st.s[g][j];
-                }
-            }
-            Dh[3 * i + j] = v;
-        }
+    for (int i = 0; i < 3; ++i) {
+        const float xi = st.xi[i];
+        Dh[i] = pair_sum(0.5f * (xi * (1.0f - xi) - st.s[i] * (1.0f - 2.0f * xi)));
+    }
+    Dh[3] = pair_sum(0.5f * st.s[0] * st.s[1]);
+    Dh[4] = pair_sum(0.5f * st.s[0] * st.s[2]);
+    Dh[5] = pair_sum(0.5f * st.s[1] * st.s[2]);
     // inverse by cofactors (D is symmetric positive definite, condition number < 2)
-    const float c00 = Dh[4] * Dh[8] - Dh[5] * Dh[7], c01 = Dh[5] * Dh[6] - Dh[3] * Dh[8],
-                c02 = Dh[3] * Dh[7] - Dh[4] * Dh[6];
-    const float c11 = Dh[0] * Dh[8] - Dh[2] * Dh[6], c12 = Dh[2] * Dh[3] - Dh[0] * Dh[5];
-    const float c22 = Dh[0] * Dh[4] - Dh[1] * Dh[3];
-    const float det = Dh[0] * c00 + Dh[1] * c01 + Dh[2] * c02;
+    const float c00 = Dh[1] * Dh[2] - Dh[5] * Dh[5], c01 = Dh[5] * Dh[4] - Dh[3] * Dh[2],
+                c02 = Dh[3] * Dh[5] - Dh[1] * Dh[4];
+    const float c11 = Dh[0] * Dh[2] - Dh[4] * Dh[4], c12 = Dh[4] * Dh[3] - Dh[0] * Dh[5];
+    const float c22 = Dh[0] * Dh[1] - Dh[3] * Dh[3];
+    const float det = Dh[0] * c00 + Dh[3] * c01 + Dh[4] * c02;
     const float sc = a.geo.inv_dx_f * a.geo.inv_dx_f / det;
     st.Dinv[0] = c00 * sc; st.Dinv[1] = c01 * sc; st.Dinv[2] = c02 * sc;
     st.Dinv[3] = c01 * sc; st.Dinv[4] = c11 * sc; st.Dinv[5] = c12 * sc;
@@ -181,18 +203,17 @@ __device__ __forceinline__ bool ad_stencil(const AdArgs &a, const float x[3], co
     return true;
 }
 
-// Node o (bits x, y, z) of grid g: weight, d = x_i - x_p (world) and the gradient
-// of the weight with respect to x_p (world).
-__device__ __forceinline__ void ad_weights(const AdArgs &a, const AdStencil &st, int g, int o, float &w, float d[3],
+// Node o (bits x, y, z; per lane): weight, d = x_i - x_p (world) and the gradient of the
+// weight with respect to x_p (world).
+__device__ __forceinline__ void ad_weights(const AdArgs &a, const AdStencil &st, int o, float &w, float d[3],
                                            float gw[3]) {
-    const int ox = o & 1, oy = (o >> 1) & 1, oz = o >> 2;
-    const int off[3] = {ox, oy, oz};
     float wa[3], dwa[3];
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-        wa[ax] = st.w[g][ax][off[ax]];
-        dwa[ax] = st.dw[g][ax][off[ax]] * a.geo.inv_dx_f;
-        d[ax] = ((float)off[ax] - st.xi[g][ax]) * a.geo.dx;
+        const bool up = (o >> ax) & 1;
+        wa[ax] = up ? st.w[ax][1] : st.w[ax][0];
+        dwa[ax] = (up ? -st.dw[ax] : st.dw[ax]) * a.geo.inv_dx_f;
+        d[ax] = ((up ? 1.0f : 0.0f) - st.xi[ax]) * a.geo.dx;
     }
     w = wa[0] * wa[1] * wa[2];
     gw[0] = dwa[0] * wa[1] * wa[2];
@@ -200,29 +221,58 @@ __device__ __forceinline__ void ad_weights(const AdArgs &a, const AdStencil &st,
     gw[2] = wa[0] * wa[1] * dwa[2];
 }
 
-// The same and the node's pool index.
-template <bool kSparse>
-__device__ __forceinline__ long long ad_node(const AdArgs &a, const AdStencil &st, int g, int o, float &w, float d[3],
-                                             float gw[3]) {
-    ad_weights(a, st, g, o, w, d, gw);
-    return ad_index<kSparse>(a, g, st.base[g][0] + (o & 1), st.base[g][1] + ((o >> 1) & 1), st.base[g][2] + (o >> 2));
+// The eight nodes of a stencil are taken from node (particle & 7) on: particles are mostly
+// stored cell by cell, eight to a cell, and eight lanes of one cell at the same node
+// offset would add to one LDS word eight deep.
+__device__ __forceinline__ int ad_turn(int i) { return (i + ((int)threadIdx.x >> 1)) & 7; }
+
+// Whether no node of the lane's stencil lies on a wall (then no node is tested).
+__device__ __forceinline__ bool ad_all_free(const AdArgs &a, const AdStencil &st) {
+    const int g = pair_grid();
+    return node_free(a, g, st.base[0], st.base[1], st.base[2]) &&
+           node_free(a, g, st.base[0] + 1, st.base[1] + 1, st.base[2] + 1);
 }
 
-// Adds to xb the adjoint of D(x_p) for Db = dL/dD (world units):
+// Indices of the eight nodes (node ad_turn(i) in id[i]), and their values in node array
+// x, all loads in flight together.
+template <bool kSparse>
+__device__ __forceinline__ void ad_ids(const AdArgs &a, const AdStencil &st, long long (&id)[8]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int o = ad_turn(i);
+        id[i] = ad_index<kSparse>(a, pair_grid(), st.base[0] + (o & 1), st.base[1] + ((o >> 1) & 1), st.base[2] + (o >> 2));
+    }
+}
+__device__ __forceinline__ void ad_gather(const float4 *x, const long long (&id)[8], float4 (&q)[8]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) q[i] = x[id[i]];
+}
+
+// Grid update of one node: v~ = p/m + dt g where m > 0 and the node is free, else 0.
+// Returns 1/m there and 0 elsewhere.
+__device__ __forceinline__ float ad_node_velocity(const AdArgs &a, const AdStencil &st, bool all_free, int o,
+                                                  const float4 &q, float v[3]) {
+    bool live = q.x > 0.0f;
+    if (live && !all_free)
+        live = node_free(a, pair_grid(), st.base[0] + (o & 1), st.base[1] + ((o >> 1) & 1), st.base[2] + (o >> 2));
+    const float im = live ? 1.0f / q.x : 0.0f;
+    v[0] = live ? q.y * im + a.dt * a.g[0] : 0.0f;
+    v[1] = live ? q.z * im + a.dt * a.g[1] : 0.0f;
+    v[2] = live ? q.w * im + a.dt * a.g[2] : 0.0f;
+    return im;
+}
+
+// Adds to xb the lane's grid's part of the adjoint of D(x_p) for Db = dL/dD (world units):
 //   dD/dx_a = dx dD^/dX_a,  dD^_aa/dX_a = 1/2 sum_k ((1 - 2 xi)(1 - c) + 2 s),
 //   dD^_ab/dX_a = 1/2 sum_k c_a s_b  (b != a);  other entries do not depend on X_a.
 __device__ __forceinline__ void ad_moment_vjp(const AdArgs &a, const AdStencil &st, const float Db[9], float xb[3]) {
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-        float acc = 0.0f;
+        const float c1 = -st.dw[ax];   // 1 - c
+        float acc = Db[4 * ax] * 0.5f * ((1.0f - 2.0f * st.xi[ax]) * c1 + 2.0f * st.s[ax]);
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            const float xi = st.xi[g][ax], c = st.c[g][ax], s = st.s[g][ax];
-            acc += Db[4 * ax] * 0.5f * ((1.0f - 2.0f * xi) * (1.0f - c) + 2.0f * s);
-#pragma unroll
-            for (int b = 0; b < 3; ++b)
-                if (b != ax) acc += (Db[3 * ax + b] + Db[3 * b + ax]) * 0.5f * c * st.s[g][b];
-        }
+        for (int b = 0; b < 3; ++b)
+            if (b != ax) acc += (Db[3 * ax + b] + Db[3 * b + ax]) * 0.5f * (1.0f - c1) * st.s[b];
         xb[ax] += a.geo.dx * acc;
     }
 }
@@ -371,24 +421,144 @@ __device__ __forceinline__ void ad_tau_vjp(const float H[9], const Polar &P, flo
         }
 }
 
+// Coefficients of (1 + x)^(-1/2) - 1 by degree.
+__device__ __constant__ const float kInvSqrt[7] = {0.0f,            -0.5f,           0.375f,         -0.3125f,
+                                                   35.0f / 128.0f, -63.0f / 256.0f, 231.0f / 1024.0f};
+
+// tau and the adjoint of tau for strains that need no eigen-decomposition (the waves for
+// which kirchhoff takes its series): with E = F F^T - I, R = (I + E)^(-1/2) F, so that
+// R - I = H + G + G H, G = (I + E)^(-1/2) - I, and F - R = -(G + G H) without
+// cancellation.  With F = R S the rotation's derivative is R^T dR = [w]x with
+// (tr(S) I - S) w = axial(R^T dF - dF^T R); for Rb = -2 mu tb F that gives
+// Fb += R [z]x, (tr(S) I - S) z = axial(Y - Y^T), Y = R^T Rb -- the same map as U Z V^T
+// above, without U, V and s.
+__device__ __forceinline__ void ad_small_stress(const Sym3 &E, float r2, float jm1, float mu, float lam, float tau[9]) {
+    const Sym3 D = power_series(E, kSqrtDiff, wave_terms(r2, kLogThr2, 4, 2));
+    const float iso = lam * jm1 * (1.0f + jm1), k = 2.0f * mu;
+    tau[0] = k * D.xx + iso; tau[4] = k * D.yy + iso; tau[8] = k * D.zz + iso;
+    tau[1] = tau[3] = k * D.xy;
+    tau[2] = tau[6] = k * D.xz;
+    tau[5] = tau[7] = k * D.yz;
+}
+
+// tau of the fixed corotated model, all nine entries; the wave takes the series or the
+// eigen-decomposition as kirchhoff does.
+__device__ __forceinline__ void ad_stress(const float H[9], float mu, float lam, float tau[9]) {
+    const Sym3 E = left_cauchy_green_minus_I(H);
+    const float jm1 = det_minus_one(H), r2 = frob2(E);
+    if (wave_needs_eig(r2, jm1)) {
+        Polar P;
+        ad_polar(H, P);
+        ad_tau(H, P, mu, lam, tau);
+    } else {
+        ad_small_stress(E, r2, jm1, mu, lam, tau);
+    }
+}
+
+__device__ __forceinline__ void mat_mul(const float A[9], const float B[9], float C[9]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) C[3 * i + j] = A[3 * i] * B[j] + A[3 * i + 1] * B[3 + j] + A[3 * i + 2] * B[6 + j];
+}
+// A^T B
+__device__ __forceinline__ void mat_tmul(const float A[9], const float B[9], float C[9]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) C[3 * i + j] = A[i] * B[j] + A[3 + i] * B[3 + j] + A[6 + i] * B[6 + j];
+}
+
+__device__ __forceinline__ void ad_small_stress_vjp(const float H[9], const Sym3 &E, float r2, float jm1, float mu,
+                                                    float lam, const float tb[9], float Fb[9]) {
+    const Sym3 G = power_series(E, kInvSqrt, wave_terms(r2, kLogThr2, 4, 2));
+    const float g[9] = {G.xx, G.xy, G.xz, G.xy, G.yy, G.yz, G.xz, G.yz, G.zz};
+    float F[9], GF[9], R[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) F[i] = H[i] + ((i % 4 == 0) ? 1.0f : 0.0f);
+    mat_mul(g, H, GF);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        GF[i] += g[i];           // R - F
+        R[i] = F[i] + GF[i];
+    }
+    float tF[9], tD[9];
+    mat_mul(tb, F, tF);
+    mat_tmul(tb, GF, tD);        // tb^T (R - F)
+    float Y[9], S[9];
+    mat_tmul(R, tF, Y);          // Y = -2 mu R^T tb F, the factor below
+    mat_tmul(R, F, S);
+    const float y0 = Y[7] - Y[5], y1 = Y[2] - Y[6], y2 = Y[3] - Y[1];
+    // (tr(S) I - S) z = y: symmetric, eigenvalues s_i + s_j close to two here
+    const float m00 = S[4] + S[8], m11 = S[0] + S[8], m22 = S[0] + S[4];
+    const float m01 = -0.5f * (S[1] + S[3]), m02 = -0.5f * (S[2] + S[6]), m12 = -0.5f * (S[5] + S[7]);
+    const float c00 = m11 * m22 - m12 * m12, c01 = m02 * m12 - m01 * m22, c02 = m01 * m12 - m02 * m11;
+    const float c11 = m00 * m22 - m02 * m02, c12 = m01 * m02 - m00 * m12, c22 = m00 * m11 - m01 * m01;
+    const float k = -2.0f * mu / (m00 * c00 + m01 * c01 + m02 * c02);
+    const float z0 = k * (c00 * y0 + c01 * y1 + c02 * y2), z1 = k * (c01 * y0 + c11 * y1 + c12 * y2),
+                z2 = k * (c02 * y0 + c12 * y1 + c22 * y2);
+    const float jc = lam * (1.0f + 2.0f * jm1) * (tb[0] + tb[4] + tb[8]);
+    float cof[9];
+    cof[0] = F[4] * F[8] - F[5] * F[7];
+    cof[1] = F[5] * F[6] - F[3] * F[8];
+    cof[2] = F[3] * F[7] - F[4] * F[6];
+    cof[3] = F[2] * F[7] - F[1] * F[8];
+    cof[4] = F[0] * F[8] - F[2] * F[6];
+    cof[5] = F[1] * F[6] - F[0] * F[7];
+    cof[6] = F[1] * F[5] - F[2] * F[4];
+    cof[7] = F[2] * F[3] - F[0] * F[5];
+    cof[8] = F[0] * F[4] - F[1] * F[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        // row i of R [z]x
+        const float r0 = R[3 * i], r1 = R[3 * i + 1], r2v = R[3 * i + 2];
+        const float q[3] = {r1 * z2 - r2v * z1, r2v * z0 - r0 * z2, r0 * z1 - r1 * z0};
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            Fb[3 * i + j] += 2.0f * mu * (tF[3 * i + j] - tD[3 * i + j]) + q[j] + jc * cof[3 * i + j];
+    }
+}
+
+// tau, and Fb += dL/dF for tb = dL/dtau.
+__device__ __forceinline__ void ad_stress_vjp(const float H[9], float mu, float lam, const float tb[9], float tau[9],
+                                              float Fb[9]) {
+    const Sym3 E = left_cauchy_green_minus_I(H);
+    const float jm1 = det_minus_one(H), r2 = frob2(E);
+    if (wave_needs_eig(r2, jm1)) {
+        Polar P;
+        ad_polar(H, P);
+        ad_tau(H, P, mu, lam, tau);
+        ad_tau_vjp(H, P, mu, lam, tb, Fb);
+    } else {
+        ad_small_stress(E, r2, jm1, mu, lam, tau);
+        ad_small_stress_vjp(H, E, r2, jm1, mu, lam, tb, Fb);
+    }
+}
+
 __device__ __forceinline__ void load_planes(const float *base, long long stride, int p, int first, int count, float *out) {
     for (int i = 0; i < count; ++i) out[i] = base[(first + i) * stride + p];
 }
 
 // ------------------------------------------------------------ workgroup node tiles
 // The two scattering kernels accumulate into a 64-bit fixed-point LDS tile over the
-// node box of their workgroup's 256 particles (both grids), then add every nonzero
-// node to the grid with one float atomic per channel.  Particles keep their
-// creation order, cell by cell, so consecutive particles sit in neighbouring cells
-// and the box is small (a row of about 34 x 3 x 3 nodes for the box workload); a
-// workgroup whose box does not fit adds its contributions to the grid directly.
-// Integer sums are exact; the unit is 2^-39 of the largest contribution bound of
-// the workgroup, so a node's sum of at most 256 contributions stays below 2^48.
+// node boxes of their workgroup's 128 particles (both grids), then add every nonzero
+// node to the grid with one float atomic per channel.  Particles keep their creation
+// order, cell by cell, so consecutive particles sit in neighbouring cells and the box is
+// small (a row of about 18 x 3 x 3 nodes for the box workload).  Where a workgroup's
+// particles run over the end of a layer or a row of the body, one box over all of them
+// can be too large; they are then split in two where consecutive particles first jump by
+// more than three cells in y, or else in x (a body of 27 x 24 cells: one workgroup in
+// twenty ran over the end of a layer; its direct additions made P2G of 119,223 particles
+// 68 us instead of 29.5).  A workgroup whose boxes do not fit either way adds its contributions to the
+// grid directly.  Integer sums are exact; the unit is 2^-39 of the largest contribution
+// bound of the workgroup, so a node's sum of at most 128 contributions stays below 2^47.
 constexpr int kAdTileWords = 5120;   // 40 KiB
+constexpr int kAdParticles = 128;    // particles of a 256-thread workgroup
+constexpr int kAdTileInts = 16;      // LDS ints of the tile's set-up
 
 struct AdTile {
-    unsigned long long *w;   // [channel][grid][T]
-    int lo[3], L[3], T;
+    unsigned long long *w;        // [channel][grid][T]
+    int lo[2][3], L[2][3], off1, T;   // the boxes; the second one's first node, nodes of both
     bool on;
     double S;
 };
@@ -400,86 +570,151 @@ __device__ __forceinline__ unsigned long long ad_fixed(float v, double S) {
     return (unsigned long long)(__double_as_longlong(fma((double)v, S, kMagic)) - 0x4338000000000000LL);
 }
 
-// Called by every thread of the workgroup: node box of the valid particles'
-// stencils on both grids, scale from the largest bound `bnd`, tile of `nch`
-// channels cleared when it fits.  sh: 7 ints of LDS.
-__device__ void ad_tile_begin(bool valid, const AdStencil &st, float bnd, int nch, unsigned long long *words, int *sh,
-                              AdTile &t) {
-    const int tid = threadIdx.x;
-    if (tid < 3) sh[tid] = INT_MAX;
-    else if (tid < 6) sh[tid] = INT_MIN;
-    else if (tid == 6) sh[6] = 0;
-    __syncthreads();
-    if (valid) {
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            atomicMin(&sh[ax], min(st.base[0][ax], st.base[1][ax]));
-            atomicMax(&sh[3 + ax], max(st.base[0][ax], st.base[1][ax]) + 1);
-        }
-    }
-    float b = valid ? bnd : 0.0f;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) b = fmaxf(b, __shfl_xor(b, off));
-    if ((tid & 63) == 0) atomicMax(reinterpret_cast<unsigned int *>(&sh[6]), __float_as_uint(b));
-    __syncthreads();
-    t.w = words;
-    long long T = 1;
-    bool on = sh[0] <= sh[3];
+// Minimum of v over the wave's lanes, added to *at by its last lane (lane exchanges within
+// the vector registers: rows of 16 by shifts, then row to row).
+__device__ __forceinline__ void ad_wave_min(int v, int *at) {
+    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x111, 0xF, 0xF, false));   // row_shr 1, 2, 4, 8
+    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x112, 0xF, 0xF, false));
+    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xF, 0xF, false));
+    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x118, 0xF, 0xF, false));
+    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xA, 0xF, false));   // row_bcast 15, 31
+    v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xC, 0xF, false));
+    if ((threadIdx.x & 63) == 63) atomicMin(at, v);
+}
+
+// Node box of the lanes for which `in` holds, into box k of the tile (lo and, negated,
+// hi in sh[6 k ..]); every thread calls it between barriers.
+__device__ __forceinline__ void ad_box(bool in, const AdStencil &st, int *sh) {
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-        t.lo[ax] = sh[ax];
-        t.L[ax] = on ? sh[3 + ax] - sh[ax] + 1 : 0;
-        T *= t.L[ax];
+        ad_wave_min(in ? st.base[ax] : INT_MAX, &sh[ax]);
+        ad_wave_min(in ? -st.base[ax] - 1 : INT_MAX, &sh[3 + ax]);
     }
-    on = on && 2 * T * nch <= kAdTileWords;
-    t.on = on;
-    t.T = on ? (int)T : 0;
-    const float m = __uint_as_float((unsigned int)sh[6]);
+}
+
+// Box k from sh; returns its node count (0 when it is empty).
+__device__ __forceinline__ long long ad_box_read(const int *sh, int k, AdTile &t) {
+    long long T = 1;
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        t.lo[k][ax] = sh[ax];
+        t.L[k][ax] = sh[ax] == INT_MAX ? 0 : -sh[3 + ax] - sh[ax] + 1;
+        T *= t.L[k][ax];
+    }
+    return T;
+}
+
+// Called by every thread of the workgroup: node boxes of the valid particles' stencils on
+// both grids, scale from the largest bound `bnd`, tile of `nch` channels cleared when it
+// fits; sel: the thread's box.  sh: kAdTileInts ints of LDS.
+__device__ void ad_tile_begin(bool valid, const AdStencil &st, float bnd, int nch, unsigned long long *words, int *sh,
+                              AdTile &t, int &sel) {
+    const int tid = threadIdx.x;
+    sel = 0;
+    if (tid < kAdTileInts) sh[tid] = INT_MAX;
+    __syncthreads();
+    ad_box(valid, st, sh);
+    // the largest bound as the smallest negated bit pattern (bounds are not negative)
+    ad_wave_min(valid ? -__float_as_int(bnd) : 0, &sh[12]);
+    __syncthreads();
+    t.w = words;
+    long long T0 = ad_box_read(sh, 0, t), T1 = 0;
+    const bool any = sh[0] != INT_MAX;
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        t.lo[1][ax] = 0;
+        t.L[1][ax] = 0;
+    }
+    int *at = reinterpret_cast<int *>(words);   // the tile's words are not in use yet
+    for (int ax = 1; ax >= 0 && any && 2 * (T0 + T1) * nch > kAdTileWords; --ax) {
+        __syncthreads();   // the boxes have been read
+        at[tid] = valid ? st.base[ax] : INT_MIN;
+        if (tid < 12) sh[tid] = INT_MAX;
+        if (tid == 13) sh[13] = INT_MAX;
+        __syncthreads();
+        if (valid && tid >= 2 && at[tid - 2] != INT_MIN && abs(st.base[ax] - at[tid - 2]) > 3) atomicMin(&sh[13], tid & ~1);
+        __syncthreads();
+        sel = tid >= sh[13] ? 1 : 0;
+        ad_box(valid && !sel, st, sh);
+        ad_box(valid && sel, st, sh + 6);
+        __syncthreads();
+        T0 = ad_box_read(sh, 0, t);
+        T1 = ad_box_read(sh + 6, 1, t);
+    }
+    t.on = any && 2 * (T0 + T1) * nch <= kAdTileWords;
+    t.off1 = t.on ? (int)T0 : 0;
+    t.T = t.on ? (int)(T0 + T1) : 0;
+    const float m = __int_as_float(-sh[12]);
     t.S = m > 0.0f ? ldexp(1.0, 39 - ilogbf(m)) : 1.0;
-    if (on)
+    if (t.on)
         for (int q = tid; q < 2 * t.T * nch; q += blockDim.x) words[q] = 0ull;
     __syncthreads();
 }
 
-// Adds v to channel ch of node (ix, iy, iz) of grid g (pool index id): into the tile,
-// or straight into plane plane0 + ch of the grid when the tile is off.
-__device__ __forceinline__ void ad_tile_add(const AdArgs &a, const AdTile &t, int plane0, int ch, int g, int ix, int iy,
-                                            int iz, long long id, float v) {
-    if (t.on) {
-        const int r = ((iz - t.lo[2]) * t.L[1] + (iy - t.lo[1])) * t.L[0] + (ix - t.lo[0]);
-        atomicAdd(&t.w[(ch * 2 + g) * t.T + r], ad_fixed(v, t.S));
-    } else {
-        atomicAdd(&plane(a, plane0 + ch)[id], v);
-    }
+// Tile position of the lane's base node and the steps to the next node in y and z.
+__device__ __forceinline__ int ad_tile_base(const AdTile &t, const AdStencil &st, int sel, int &sy, int &sz) {
+    const int l0 = sel ? t.lo[1][0] : t.lo[0][0], l1 = sel ? t.lo[1][1] : t.lo[0][1], l2 = sel ? t.lo[1][2] : t.lo[0][2];
+    sy = sel ? t.L[1][0] : t.L[0][0];
+    sz = sy * (sel ? t.L[1][1] : t.L[0][1]);
+    return pair_grid() * t.T + (sel ? t.off1 : 0) + (st.base[2] - l2) * sz + (st.base[1] - l1) * sy + (st.base[0] - l0);
 }
 
-// Called by every thread after its adds: every nonzero tile node to the grid.
+// Called by every thread after its adds: every nonzero value of the tile to the node
+// array x.  Four consecutive lanes take a node's channels, so that a wave's atomics go to
+// consecutive addresses.
 template <bool kSparse>
-__device__ void ad_tile_flush(const AdArgs &a, const AdTile &t, int plane0, int nch) {
+__device__ void ad_tile_flush(const AdArgs &a, const AdTile &t, float4 *x, int nch) {
     __syncthreads();
     if (!t.on) return;
     const double inv = 1.0 / t.S;
-    const int LxLy = t.L[0] * t.L[1];
-    for (int q = threadIdx.x; q < 2 * t.T; q += blockDim.x) {
-        const int g = q >= t.T ? 1 : 0, r = q - g * t.T;
-        const int ix = t.lo[0] + r % t.L[0], iy = t.lo[1] + (r / t.L[0]) % t.L[1], iz = t.lo[2] + r / LxLy;
-        long long id = -1;   // looked up for a touched node only (its block is marked)
-        for (int ch = 0; ch < nch; ++ch) {
-            const long long v = (long long)t.w[(ch * 2 + g) * t.T + r];
-            if (v == 0) continue;
-            if (id < 0) id = ad_index<kSparse>(a, g, ix, iy, iz);
-            atomicAdd(&plane(a, plane0 + ch)[id], (float)((double)v * inv));
-        }
+    const int ch = threadIdx.x & 3;
+    for (int q = threadIdx.x >> 2; q < 2 * t.T; q += blockDim.x >> 2) {
+        const int g = q >= t.T ? 1 : 0, rt = q - g * t.T, k = rt >= t.off1 ? 1 : 0;
+        const long long v = ch < nch ? (long long)t.w[(ch * 2 + g) * t.T + rt] : 0ll;
+        if (v == 0) continue;
+        const int r = rt - (k ? t.off1 : 0), L0 = k ? t.L[1][0] : t.L[0][0], L1 = k ? t.L[1][1] : t.L[0][1];
+        // r / L0 and so on through FP32: exact for these sizes (r < 2^13)
+        const int row = (int)(((float)r + 0.5f) / (float)L0), iz = (int)(((float)row + 0.5f) / (float)L1);
+        const long long id = ad_index<kSparse>(a, g, (k ? t.lo[1][0] : t.lo[0][0]) + r - row * L0,
+                                               (k ? t.lo[1][1] : t.lo[0][1]) + row - iz * L1,
+                                               (k ? t.lo[1][2] : t.lo[0][2]) + iz);
+        atomicAdd(reinterpret_cast<float *>(x + id) + ch, (float)((double)v * inv));
     }
 }
 
 // ------------------------------------------------------------ kernels
+// Clears, for later calls, the X that the call before used (and VB when it holds a
+// reverse call's sums): the workgroups of the P2G launch past a.pgrid.
+template <bool kSparse>
+__device__ void ad_clear(const AdArgs &a, unsigned int use) {
+    float4 *x = ad_x(a, use ^ 1u), *vb = ad_vb(a);
+    const bool both = a.ctl[A_VB] != 0u;
+    const long long t0 = (long long)((int)blockIdx.x - a.pgrid) * 256 + threadIdx.x;
+    const long long step = (long long)((int)gridDim.x - a.pgrid) * 256;
+    const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        const long long n = kSparse ? 64ll * min(a.ctl[A_PREV + g], (unsigned int)a.cap) : a.nodes;
+        for (long long i = t0; i < n; i += step) {
+            x[g * a.nodes + i] = zero;
+            if (both) vb[g * a.nodes + i] = zero;
+        }
+    }
+}
+
 // P2G through the workgroup's node tile (direct float atomics when it does not fit).
 template <bool kSparse>
 __global__ void __launch_bounds__(256) k_ad_p2g(AdArgs a, const float *state, const float *logE) {
     __shared__ unsigned long long tw[kAdTileWords];
-    __shared__ int sh[8];
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ int sh[kAdTileInts];
+    const unsigned int use = a.ctl[A_CUR] & 1u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl[A_USE] = use;
+    if ((int)blockIdx.x >= a.pgrid) {   // the whole workgroup
+        ad_clear<kSparse>(a, use);
+        return;
+    }
+    float4 *x4 = ad_x(a, use);
+    const int p = ad_block(a) * kAdParticles + (threadIdx.x >> 1);
     float x[3], v[3], Q[9];
     AdStencil st;
     bool valid = false;
@@ -490,23 +725,18 @@ __global__ void __launch_bounds__(256) k_ad_p2g(AdArgs a, const float *state, co
         load_planes(state, a.stride, p, 6, 9, B);
         load_planes(state, a.stride, p, 15, 9, H);
         load_planes(state, a.stride, p, kPlaneR, 3, xr);
+        const float lE = logE[p];
         valid = ad_stencil(a, x, xr, st);
         if (!valid) {
             ad_status(a, ST_DOMAIN);
         } else {
-            const float E = expf(logE[p]);
-            Polar P;
-            ad_polar(H, P);
+            const float E = expf(lE);
             float tau[9];
-            ad_tau(H, P, a.nu_mu * E, a.nu_lambda * E, tau);
+            ad_stress(H, a.nu_mu * E, a.nu_lambda * E, tau);
             float A[9];
 #pragma unroll
             for (int i = 0; i < 9; ++i) A[i] = a.mass * B[i] - a.dt * a.vol0 * tau[i];
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-                    Q[3 * i + j] = A[3 * i] * st.Dinv[j] + A[3 * i + 1] * st.Dinv[3 + j] + A[3 * i + 2] * st.Dinv[6 + j];
+            mat_mul(A, st.Dinv, Q);
         }
     }
     // |w m| <= m and |w (m v + Q d)| <= |m v| + dx sum |Q| (w <= 1, |d_b| <= dx)
@@ -519,32 +749,45 @@ __global__ void __launch_bounds__(256) k_ad_p2g(AdArgs a, const float *state, co
                                  a.geo.dx * (fabsf(Q[3 * ax]) + fabsf(Q[3 * ax + 1]) + fabsf(Q[3 * ax + 2])));
     }
     AdTile t;
-    ad_tile_begin(valid, st, bnd, 4, tw, sh, t);
+    int sel;
+    ad_tile_begin(valid, st, bnd, 4, tw, sh, t, sel);
     if (valid) {
-        for (int g = 0; g < 2; ++g)
-            for (int o = 0; o < 8; ++o) {
-                float w, d[3], gw[3];
-                ad_weights(a, st, g, o, w, d, gw);
-                const int ix = st.base[g][0] + (o & 1), iy = st.base[g][1] + ((o >> 1) & 1), iz = st.base[g][2] + (o >> 2);
-                const long long id = t.on ? 0 : ad_index<kSparse>(a, g, ix, iy, iz);   // the tile's flush looks it up
-                ad_tile_add(a, t, GM, 0, g, ix, iy, iz, id, w * a.mass);
+        int sy = 0, sz = 0;
+        const int r0 = t.on ? ad_tile_base(t, st, sel, sy, sz) : 0;
 #pragma unroll
-                for (int ax = 0; ax < 3; ++ax)
-                    ad_tile_add(a, t, GM, 1 + ax, g, ix, iy, iz, id,
-                                w * (a.mass * v[ax] + Q[3 * ax] * d[0] + Q[3 * ax + 1] * d[1] + Q[3 * ax + 2] * d[2]));
+        for (int i = 0; i < 8; ++i) {
+            const int o = ad_turn(i), ox = o & 1, oy = (o >> 1) & 1, oz = o >> 2;
+            float w, d[3], gw[3];
+            ad_weights(a, st, o, w, d, gw);
+            float c[4];
+            c[0] = w * a.mass;
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax)
+                c[1 + ax] = w * (a.mass * v[ax] + Q[3 * ax] * d[0] + Q[3 * ax + 1] * d[1] + Q[3 * ax + 2] * d[2]);
+            if (t.on) {
+                unsigned long long *tp = t.w + r0 + ox + oy * sy + oz * sz;
+#pragma unroll
+                for (int ch = 0; ch < 4; ++ch) atomicAdd(tp + ch * 2 * t.T, ad_fixed(c[ch], t.S));
+            } else {
+                float *tp = reinterpret_cast<float *>(
+                    x4 + ad_index<kSparse>(a, pair_grid(), st.base[0] + ox, st.base[1] + oy, st.base[2] + oz));
+#pragma unroll
+                for (int ch = 0; ch < 4; ++ch) atomicAdd(tp + ch, c[ch]);
             }
+        }
     }
-    ad_tile_flush<kSparse>(a, t, GM, 4);
+    ad_tile_flush<kSparse>(a, t, x4, 4);
 }
 
 // Marks the blocks of the nodes a valid particle's stencil reaches on both grids
 // (nodes base and base + 1 per axis, base = floor(X - k/4) as in ad_stencil).
-// Also zeroes the slot counters that k_ad_alloc then counts up.
+// Also keeps the previous call's slot counts (for the clearing) and zeroes the counters
+// that k_ad_alloc then counts up.
 __global__ void __launch_bounds__(256) k_ad_mark(AdArgs a, const float *state) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p == 0) {
-        a.cnt[0] = 0u;
-        a.cnt[1] = 0u;
+    if (p < 2) {
+        a.ctl[A_PREV + p] = a.ctl[A_CNT + p];
+        a.ctl[A_CNT + p] = 0u;
     }
     if (p >= a.n) return;
     float x[3], xr[3], X[3];
@@ -570,7 +813,7 @@ __global__ void __launch_bounds__(256) k_ad_mark(AdArgs a, const float *state) {
 }
 
 // One thread per block of grid blockIdx.y: a marked block takes the grid's next pool
-// slot (one counter update per wave) and is recorded in blist; its flag is cleared.
+// slot (one counter update per wave); its flag is cleared.
 // Every block's page entry is rewritten (-1 for an untouched one).
 __global__ void __launch_bounds__(256) k_ad_alloc(AdArgs a) {
     const int g = blockIdx.y;
@@ -584,7 +827,7 @@ __global__ void __launch_bounds__(256) k_ad_alloc(AdArgs a) {
     }
     const int lane = threadIdx.x & 63, leader = __builtin_ctzll(m);
     unsigned int base = 0u;
-    if (lane == leader) base = atomicAdd(&a.cnt[g], (unsigned int)__popcll(m));
+    if (lane == leader) base = atomicAdd(&a.ctl[A_CNT + g], (unsigned int)__popcll(m));
     base = __shfl(base, leader);
     if (!in) return;
     int slot = -1;
@@ -592,7 +835,6 @@ __global__ void __launch_bounds__(256) k_ad_alloc(AdArgs a) {
         const unsigned int s = base + (unsigned int)__popcll(m & ((1ull << lane) - 1ull));
         if (s < (unsigned int)a.cap) {
             slot = (int)s;
-            a.blist[(long long)g * a.cap + s] = (int)b;
         } else {
             slot = a.cap;
             ad_status(a, ST_CAPACITY);
@@ -602,71 +844,16 @@ __global__ void __launch_bounds__(256) k_ad_alloc(AdArgs a) {
     a.page[g * a.nbv + b] = slot;
 }
 
-// Nodes the sweeps visit, both grids: [0, n0) on G-, then G+ (every node when
-// dense, else the nodes of the slots taken in this call).
-template <bool kSparse>
-__device__ __forceinline__ long long taken_nodes(const AdArgs &a, long long &n0) {
-    if (!kSparse) {
-        n0 = a.nodes;
-        return 2 * a.nodes;
-    }
-    const unsigned int cap = (unsigned int)a.cap;
-    const unsigned int c0 = min(a.cnt[0], cap), c1 = min(a.cnt[1], cap);
-    n0 = 64ll * c0;
-    return 64ll * (c0 + c1);
-}
-
-// Coordinates of node r of grid g in the order of taken_nodes (r < 2^32 when dense:
-// at most 2^26 blocks of 64 nodes).
-template <bool kSparse>
-__device__ __forceinline__ void taken_coords(const AdArgs &a, int g, long long r, int &ix, int &iy, int &iz) {
-    if (kSparse) {
-        ad_coords(a, g, (int)(r >> 6), (int)(r & 63), ix, iy, iz);
-    } else {
-        const unsigned int q = (unsigned int)r, nx = (unsigned int)a.nx, ny = (unsigned int)a.ny;
-        ix = (int)(q % nx);
-        iy = (int)((q / nx) % ny);
-        iz = (int)(q / (nx * ny));
-    }
-}
-
-__device__ __forceinline__ bool node_free(const AdArgs &a, int g, int ix, int iy, int iz) {
-    return ix >= a.geo.stick_lo[g] && iy >= a.geo.stick_lo[g] && iz >= a.geo.stick_lo[g] &&
-           ix <= a.geo.stick_hi[g][0] && iy <= a.geo.stick_hi[g][1] && iz <= a.geo.stick_hi[g][2];
-}
-
-// Grid update on the taken blocks.  With zero_mp (a forward call: m and p have no
-// later reader) m and p are zeroed after the read, ready for the next P2G.
-template <bool kSparse>
-__global__ void k_ad_grid(AdArgs a, int zero_mp) {
-    float *gm = plane(a, GM);
-    long long n0;
-    const long long total = taken_nodes<kSparse>(a, n0);
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-         i += (long long)gridDim.x * blockDim.x) {
-        const int g = i >= n0 ? 1 : 0;
-        const long long r = g ? i - n0 : i, id = g * a.nodes + r;
-        const float m = gm[id];
-        bool live = false;
-        if (m > 0.0f) {
-            int ix, iy, iz;
-            taken_coords<kSparse>(a, g, r, ix, iy, iz);
-            live = node_free(a, g, ix, iy, iz);
-        }
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            float *pp = plane(a, GP + ax) + id;
-            plane(a, GV + ax)[id] = live ? *pp / m + a.dt * a.g[ax] : 0.0f;
-            if (zero_mp) *pp = 0.0f;
-        }
-        if (zero_mp) gm[id] = 0.0f;
-    }
-}
-
 template <bool kSparse>
 __global__ void __launch_bounds__(256) k_ad_g2p(AdArgs a, const float *state, float *out) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = ad_block(a) * kAdParticles + (threadIdx.x >> 1), g = pair_grid();
+    const unsigned int use = a.ctl[A_USE];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.ctl[A_CUR] = use ^ 1u;
+        a.ctl[A_VB] = 0u;
+    }
     if (p >= a.n) return;
+    const float4 *x4 = ad_x(a, use);
     float x[3], xr[3], H[9];
     load_planes(state, a.stride, p, 0, 3, x);
     load_planes(state, a.stride, p, kPlaneR, 3, xr);
@@ -674,52 +861,66 @@ __global__ void __launch_bounds__(256) k_ad_g2p(AdArgs a, const float *state, fl
     AdStencil st;
     if (!ad_stencil(a, x, xr, st)) {
         ad_status(a, ST_DOMAIN);
-        for (int i = 0; i < MPM_STATE_PLANES; ++i) out[i * a.stride + p] = state[i * a.stride + p];
+        for (int i = g; i < MPM_STATE_PLANES; i += 2) out[i * a.stride + p] = state[i * a.stride + p];
         return;
     }
     float vp[3] = {0.0f, 0.0f, 0.0f}, Bn[9];
 #pragma unroll
     for (int i = 0; i < 9; ++i) Bn[i] = 0.0f;
-    for (int g = 0; g < 2; ++g)
-        for (int o = 0; o < 8; ++o) {
-            float w, d[3], gw[3];
-            const long long id = ad_node<kSparse>(a, st, g, o, w, d, gw);
+    {
+        const bool all_free = ad_all_free(a, st);
+        long long id[8];
+        float4 q[8];
+        ad_ids<kSparse>(a, st, id);
+        ad_gather(x4, id, q);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int o = ad_turn(i);
+            float w, d[3], gw[3], vi[3];
+            ad_weights(a, st, o, w, d, gw);
+            ad_node_velocity(a, st, all_free, o, q[i], vi);
 #pragma unroll
             for (int ax = 0; ax < 3; ++ax) {
-                const float vi = plane(a, GV + ax)[id];
-                vp[ax] += 0.5f * w * vi;
+                const float wv = 0.5f * w * vi[ax];
+                vp[ax] += wv;
 #pragma unroll
-                for (int b = 0; b < 3; ++b) Bn[3 * ax + b] += 0.5f * w * vi * d[b];
+                for (int b = 0; b < 3; ++b) Bn[3 * ax + b] += wv * d[b];
             }
         }
+    }
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) vp[ax] = pair_sum(vp[ax]);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) Bn[i] = pair_sum(Bn[i]);
     float C[9];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            C[3 * i + j] = Bn[3 * i] * st.Dinv[j] + Bn[3 * i + 1] * st.Dinv[3 + j] + Bn[3 * i + 2] * st.Dinv[6 + j];
+    mat_mul(Bn, st.Dinv, C);
+    // the new state's planes; the pair's lanes store half of them each
+    float q[28];
     // F' = (I + dt C) F  ->  H' = H + dt C (I + H)
-    float Hn[9];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j)
-            Hn[3 * i + j] = H[3 * i + j] + a.dt * (C[3 * i + j] + C[3 * i] * H[j] + C[3 * i + 1] * H[3 + j] + C[3 * i + 2] * H[6 + j]);
+            q[15 + 3 * i + j] = H[3 * i + j] + a.dt * (C[3 * i + j] + C[3 * i] * H[j] + C[3 * i + 1] * H[3 + j] + C[3 * i + 2] * H[6 + j]);
     float probe = 0.0f;
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-        float xn, xrn;
-        advance_position(x[ax], xr[ax], a.dt * vp[ax], xn, xrn);
-        out[ax * a.stride + p] = xn;
-        out[(kPlaneR + ax) * a.stride + p] = xrn;
-        out[(3 + ax) * a.stride + p] = vp[ax];
+        advance_position(x[ax], xr[ax], a.dt * vp[ax], q[ax], q[kPlaneR + ax]);
+        q[3 + ax] = vp[ax];
         probe += vp[ax] * 0.0f;
     }
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-        out[(6 + i) * a.stride + p] = Bn[i];
-        out[(15 + i) * a.stride + p] = Hn[i];
-        probe += Bn[i] * 0.0f + Hn[i] * 0.0f;
+        q[6 + i] = Bn[i];
+        probe += Bn[i] * 0.0f + q[15 + i] * 0.0f;
+    }
+    q[27] = 0.0f;
+    float *op = out + (long long)(g ? 14 : 0) * a.stride + p;
+#pragma unroll
+    for (int i = 0; i < 14; ++i) {
+        const float v = g ? q[14 + i] : q[i];
+        if (i < 13 || g == 0) *op = v;
+        op += a.stride;
     }
     if (!(probe == 0.0f)) ad_status(a, ST_NONFINITE);
 }
@@ -729,8 +930,15 @@ template <bool kSparse>
 __global__ void __launch_bounds__(256) k_ad_g2p_vjp(AdArgs a, const float *state, const float *cot_out,
                                                     float *cot_in) {
     __shared__ unsigned long long tw[kAdTileWords];
-    __shared__ int sh[8];
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ int sh[kAdTileInts];
+    const int p = ad_block(a) * kAdParticles + (threadIdx.x >> 1), lane_g = pair_grid();
+    const unsigned int use = a.ctl[A_USE];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.ctl[A_CUR] = use ^ 1u;
+        a.ctl[A_VB] = 1u;
+    }
+    const float4 *x4 = ad_x(a, use);
+    float4 *vb4 = ad_vb(a);
     float x[3], xr[3], H[9];
     float xbo[3], vbo[3], Bbo[9], Fbo[9];
     AdStencil st;
@@ -748,65 +956,37 @@ __global__ void __launch_bounds__(256) k_ad_g2p_vjp(AdArgs a, const float *state
             // the forward step left this particle unchanged; the position cotangent
             // is that of the x planes, written to the r planes as well
             ad_status(a, ST_DOMAIN);
-            for (int i = 0; i < MPM_STATE_PLANES; ++i) cot_in[i * a.stride + p] = cot_out[i * a.stride + p];
+            for (int i = 0; i < kPlaneR; ++i) cot_in[i * a.stride + p] = cot_out[i * a.stride + p];
             for (int i = 0; i < 3; ++i) cot_in[(kPlaneR + i) * a.stride + p] = xbo[i];
         }
     }
     // Every thread reaches the tile's set-up and flush (they hold workgroup barriers)
     // at the same two points, whatever its particle; invalid lanes add nothing.
-    float Bn[9], C[9], xb[3], vbt[3], Fb[9], Bbt[9], Dib[9];
+    float xb[3], vbt[3], Bbt[9], Cb[9];
     float bnd = 0.0f;
     if (valid) {
-        // forward quantities: B' and C = B' D^-1
+        // x' = x + dt v'  ->  xb = xb',  v'b = vb' + dt xb'
 #pragma unroll
-        for (int i = 0; i < 9; ++i) Bn[i] = 0.0f;
-        for (int g = 0; g < 2; ++g)
-            for (int o = 0; o < 8; ++o) {
-                float w, d[3], gw[3];
-                const long long id = ad_node<kSparse>(a, st, g, o, w, d, gw);
+        for (int ax = 0; ax < 3; ++ax) {
+            xb[ax] = lane_g ? 0.0f : xbo[ax];   // a lane's share; summed over the pair below
+            vbt[ax] = vbo[ax] + a.dt * xbo[ax];
+        }
+        // F' = (I + dt C) F  ->  Cb = dt Fb' F^T;  C = B' D^-1  ->  B'b += Cb D^-T
 #pragma unroll
-                for (int ax = 0; ax < 3; ++ax) {
-                    const float vi = plane(a, GV + ax)[id];
+        for (int i = 0; i < 3; ++i)
 #pragma unroll
-                    for (int b = 0; b < 3; ++b) Bn[3 * ax + b] += 0.5f * w * vi * d[b];
-                }
+            for (int j = 0; j < 3; ++j) {
+                float cb = 0.0f;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) cb += Fbo[3 * i + k] * (H[3 * j + k] + (j == k ? 1.0f : 0.0f));
+                Cb[3 * i + j] = a.dt * cb;
             }
 #pragma unroll
         for (int i = 0; i < 3; ++i)
 #pragma unroll
             for (int j = 0; j < 3; ++j)
-                C[3 * i + j] =
-                    Bn[3 * i] * st.Dinv[j] + Bn[3 * i + 1] * st.Dinv[3 + j] + Bn[3 * i + 2] * st.Dinv[6 + j];
-        // x' = x + dt v'  ->  xb = xb',  v'b = vb' + dt xb'
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            xb[ax] = xbo[ax];
-            vbt[ax] = vbo[ax] + a.dt * xbo[ax];
-        }
-        // F' = (I + dt C) F  ->  Cb = dt Fb' F^T,  Fb = (I + dt C)^T Fb'
-        float Cb[9];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                float cb = 0.0f, fb = Fbo[3 * i + j];
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    cb += Fbo[3 * i + k] * (H[3 * j + k] + (j == k ? 1.0f : 0.0f));
-                    fb += a.dt * C[3 * k + i] * Fbo[3 * k + j];
-                }
-                Cb[3 * i + j] = a.dt * cb;
-                Fb[3 * i + j] = fb;
-            }
-        // C = B' D^-1  ->  B'b += Cb D^-T,  (D^-1)b = B'^T Cb
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
                 Bbt[3 * i + j] = Bbo[3 * i + j] + Cb[3 * i] * st.Dinv[3 * j] + Cb[3 * i + 1] * st.Dinv[3 * j + 1] +
                                  Cb[3 * i + 2] * st.Dinv[3 * j + 2];
-                Dib[3 * i + j] = Bn[i] * Cb[j] + Bn[3 + i] * Cb[3 + j] + Bn[6 + i] * Cb[6 + j];
-            }
         // |1/2 w (v'b + B'b d)| <= 1/2 (|v'b| + dx sum |B'b|)
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax)
@@ -814,87 +994,89 @@ __global__ void __launch_bounds__(256) k_ad_g2p_vjp(AdArgs a, const float *state
                                                                   fabsf(Bbt[3 * ax + 2]))));
     }
     AdTile t;
-    ad_tile_begin(valid, st, bnd, 3, tw, sh, t);
+    int sel;
+    ad_tile_begin(valid, st, bnd, 3, tw, sh, t, sel);
     if (valid) {
+        // one pass over the nodes: the forward B' (for C and (D^-1)b), and
         // v' = 1/2 sum w v~,  B' = 1/2 sum w v~ d^T:
         //   v~b_i += 1/2 w (v'b + B'b d),  wb = 1/2 v~ . (v'b + B'b d),  db = 1/2 w B'b^T v~,
         //   and d = x_i - x_p moves against x_p
-        for (int g = 0; g < 2; ++g)
-            for (int o = 0; o < 8; ++o) {
-                float w, d[3], gw[3];
-                const long long id = ad_node<kSparse>(a, st, g, o, w, d, gw);
-                const int ix = st.base[g][0] + (o & 1), iy = st.base[g][1] + ((o >> 1) & 1),
-                          iz = st.base[g][2] + (o >> 2);
-                float vi[3], gv[3];
+        float Bn[9];
 #pragma unroll
-                for (int ax = 0; ax < 3; ++ax) {
-                    vi[ax] = plane(a, GV + ax)[id];
-                    gv[ax] = vbt[ax] + Bbt[3 * ax] * d[0] + Bbt[3 * ax + 1] * d[1] + Bbt[3 * ax + 2] * d[2];
-                }
-                float wb = 0.0f;
+        for (int i = 0; i < 9; ++i) Bn[i] = 0.0f;
+        const bool all_free = ad_all_free(a, st);
+        long long id[8];
+        float4 q[8];
+        ad_ids<kSparse>(a, st, id);
+        ad_gather(x4, id, q);
+        int sy = 0, sz = 0;
+        const int r0 = t.on ? ad_tile_base(t, st, sel, sy, sz) : 0;
 #pragma unroll
-                for (int ax = 0; ax < 3; ++ax) {
-                    ad_tile_add(a, t, GVB, ax, g, ix, iy, iz, id, 0.5f * w * gv[ax]);
-                    wb += 0.5f * vi[ax] * gv[ax];
-                }
+        for (int i = 0; i < 8; ++i) {
+            const int o = ad_turn(i), ox = o & 1, oy = (o >> 1) & 1, oz = o >> 2;
+            float w, d[3], gw[3], vi[3], gv[3];
+            ad_weights(a, st, o, w, d, gw);
+            ad_node_velocity(a, st, all_free, o, q[i], vi);
+            float wb = 0.0f;
 #pragma unroll
-                for (int b = 0; b < 3; ++b) {
-                    const float db = 0.5f * w * (Bbt[b] * vi[0] + Bbt[3 + b] * vi[1] + Bbt[6 + b] * vi[2]);
-                    xb[b] += wb * gw[b] - db;
-                }
+            for (int ax = 0; ax < 3; ++ax) {
+                gv[ax] = vbt[ax] + Bbt[3 * ax] * d[0] + Bbt[3 * ax + 1] * d[1] + Bbt[3 * ax + 2] * d[2];
+                wb += 0.5f * vi[ax] * gv[ax];
+#pragma unroll
+                for (int b = 0; b < 3; ++b) Bn[3 * ax + b] += 0.5f * w * vi[ax] * d[b];
             }
+            if (t.on) {
+                unsigned long long *tp = t.w + r0 + ox + oy * sy + oz * sz;
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax) atomicAdd(tp + ax * 2 * t.T, ad_fixed(0.5f * w * gv[ax], t.S));
+            } else {
+                float *tp = reinterpret_cast<float *>(vb4 + id[i]);
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax) atomicAdd(tp + ax, 0.5f * w * gv[ax]);
+            }
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const float db = 0.5f * w * (Bbt[b] * vi[0] + Bbt[3 + b] * vi[1] + Bbt[6 + b] * vi[2]);
+                xb[b] += wb * gw[b] - db;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 9; ++i) Bn[i] = pair_sum(Bn[i]);
+        // Fb = (I + dt C)^T Fb',  C = B' D^-1;  (D^-1)b = B'^T Cb
+        float C[9], Fb[9], Dib[9];
+        mat_mul(Bn, st.Dinv, C);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                float fb = Fbo[3 * i + j];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) fb += a.dt * C[3 * k + i] * Fbo[3 * k + j];
+                Fb[3 * i + j] = fb;
+            }
+        mat_tmul(Bn, Cb, Dib);
         float Db[9];
         ad_inverse_vjp(st.Dinv, Dib, Db);
         ad_moment_vjp(a, st, Db, xb);
 #pragma unroll
-        for (int ax = 0; ax < 3; ++ax) cot_in[ax * a.stride + p] = xb[ax];
-#pragma unroll
-        for (int i = 0; i < 9; ++i) cot_in[(15 + i) * a.stride + p] = Fb[i];
-    }
-    ad_tile_flush<kSparse>(a, t, GVB, 3);
-}
-
-// Grid update reversed: pb = v~b / m,  mb = -(v~b . p) / m^2 on live nodes.
-// As the last reader of m, p and v~b in a backward call, it also zeroes them for the
-// next call's scatters.
-template <bool kSparse>
-__global__ void k_ad_grid_vjp(AdArgs a) {
-    float *gm = plane(a, GM);
-    long long n0;
-    const long long total = taken_nodes<kSparse>(a, n0);
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-         i += (long long)gridDim.x * blockDim.x) {
-        const int g = i >= n0 ? 1 : 0;
-        const long long r = g ? i - n0 : i, id = g * a.nodes + r;
-        const float m = gm[id];
-        bool live = false;
-        if (m > 0.0f) {
-            int ix, iy, iz;
-            taken_coords<kSparse>(a, g, r, ix, iy, iz);
-            live = node_free(a, g, ix, iy, iz);
-        }
-        float dot = 0.0f;
-        const float im = live ? 1.0f / m : 0.0f;
-#pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
-            float *vbp = plane(a, GVB + ax) + id;
-            float *pp = plane(a, GP + ax) + id;
-            const float vb = *vbp;
-            plane(a, GPB + ax)[id] = vb * im;
-            dot += vb * *pp;
-            *vbp = 0.0f;
-            *pp = 0.0f;
+            xb[ax] = pair_sum(xb[ax]);
+            if (lane_g == 0) cot_in[ax * a.stride + p] = xb[ax];
         }
-        plane(a, GMB)[id] = live ? -dot * im * im : 0.0f;
-        gm[id] = 0.0f;
+        if (lane_g) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) cot_in[(15 + i) * a.stride + p] = Fb[i];
+        }
     }
+    ad_tile_flush<kSparse>(a, t, vb4, 3);
 }
 
-// P2G reversed (a gather): completes dL/dx and dL/dF, writes dL/dv, dL/dB, adds dL/dlogE.
+// P2G and grid update reversed (a gather): on live nodes pb = v~b / m and
+// mb = -(v~b . p) / m^2; completes dL/dx and dL/dF, writes dL/dv, dL/dB, adds dL/dlogE.
 template <bool kSparse>
 __global__ void __launch_bounds__(256) k_ad_p2g_vjp(AdArgs a, const float *state, const float *logE, float *cot_in,
                                                     float *logE_cot) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = ad_block(a) * kAdParticles + (threadIdx.x >> 1), g = pair_grid();
     if (p >= a.n) return;
     float x[3], xr[3], v[3], B[9], H[9];
     load_planes(state, a.stride, p, 0, 3, x);
@@ -906,32 +1088,36 @@ __global__ void __launch_bounds__(256) k_ad_p2g_vjp(AdArgs a, const float *state
     if (!ad_stencil(a, x, xr, st)) return;   // cotangent already passed through by the G2P adjoint
     const float E = expf(logE[p]);
     const float mu = a.nu_mu * E, lam = a.nu_lambda * E;
-    Polar P;
-    ad_polar(H, P);
-    float tau[9];
-    ad_tau(H, P, mu, lam, tau);
+    const float4 *x4 = ad_x(a, a.ctl[A_USE]), *vb4 = ad_vb(a);
     float A[9], Q[9];
+    ad_stress(H, mu, lam, A);
 #pragma unroll
-    for (int i = 0; i < 9; ++i) A[i] = a.mass * B[i] - a.dt * a.vol0 * tau[i];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            Q[3 * i + j] = A[3 * i] * st.Dinv[j] + A[3 * i + 1] * st.Dinv[3 + j] + A[3 * i + 2] * st.Dinv[6 + j];
-    float xb[3], vb[3] = {0.0f, 0.0f, 0.0f}, Qb[9];
-    load_planes(cot_in, a.stride, p, 0, 3, xb);
+    for (int i = 0; i < 9; ++i) A[i] = a.mass * B[i] - a.dt * a.vol0 * A[i];
+    mat_mul(A, st.Dinv, Q);
+    float xb[3] = {0.0f, 0.0f, 0.0f}, vb[3] = {0.0f, 0.0f, 0.0f}, Qb[9];   // the lane's share
 #pragma unroll
     for (int i = 0; i < 9; ++i) Qb[i] = 0.0f;
+    const bool all_free = ad_all_free(a, st);
     // m_i += w m,  p_i += w (m v + Q d):
     //   wb = m mb_i + pb_i . (m v + Q d),  vb += w m pb_i,  Qb += w pb_i d^T,  db = w Q^T pb_i
-    for (int g = 0; g < 2; ++g)
-        for (int o = 0; o < 8; ++o) {
-            float w, d[3], gw[3];
-            const long long id = ad_node<kSparse>(a, st, g, o, w, d, gw);
-            float pb[3];
+    long long id[8];
+    ad_ids<kSparse>(a, st, id);
 #pragma unroll
-            for (int ax = 0; ax < 3; ++ax) pb[ax] = plane(a, GPB + ax)[id];
-            float wb = a.mass * plane(a, GMB)[id];
+    for (int half = 0; half < 2; ++half) {
+        float4 q[4], r[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q[i] = x4[id[4 * half + i]];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = vb4[id[4 * half + i]];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int o = ad_turn(4 * half + i);
+            float w, d[3], gw[3], vi[3];
+            ad_weights(a, st, o, w, d, gw);
+            const float im = ad_node_velocity(a, st, all_free, o, q[i], vi);
+            const float pb[3] = {r[i].x * im, r[i].y * im, r[i].z * im};
+            const float mb = -(r[i].x * q[i].y + r[i].y * q[i].z + r[i].z * q[i].w) * im * im;
+            float wb = a.mass * mb;
 #pragma unroll
             for (int ax = 0; ax < 3; ++ax) {
                 const float pi = a.mass * v[ax] + Q[3 * ax] * d[0] + Q[3 * ax + 1] * d[1] + Q[3 * ax + 2] * d[2];
@@ -946,40 +1132,47 @@ __global__ void __launch_bounds__(256) k_ad_p2g_vjp(AdArgs a, const float *state
                 xb[b] += wb * gw[b] - db;
             }
         }
+    }
+#pragma unroll
+    for (int i = 0; i < 9; ++i) Qb[i] = pair_sum(Qb[i]);
     // Q = A D^-1  ->  Ab = Qb D^-T,  (D^-1)b = A^T Qb
-    float Ab[9], Dib[9];
+    float Ab[9], Dib[9], Db[9];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
+        for (int j = 0; j < 3; ++j)
             Ab[3 * i + j] = Qb[3 * i] * st.Dinv[3 * j] + Qb[3 * i + 1] * st.Dinv[3 * j + 1] + Qb[3 * i + 2] * st.Dinv[3 * j + 2];
-            Dib[3 * i + j] = A[i] * Qb[j] + A[3 + i] * Qb[3 + j] + A[6 + i] * Qb[6 + j];
-        }
-    float Db[9];
+    mat_tmul(A, Qb, Dib);
     ad_inverse_vjp(st.Dinv, Dib, Db);
     ad_moment_vjp(a, st, Db, xb);
-    // A = m B - dt V0 tau  ->  Bb = m Ab,  taub = -dt V0 Ab
-    float tb[9], Fb[9];
-    float lb = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-        tb[i] = -a.dt * a.vol0 * Ab[i];
-        lb += tb[i] * tau[i];   // tau is proportional to E = exp(logE)
-    }
-    load_planes(cot_in, a.stride, p, 15, 9, Fb);
-    ad_tau_vjp(H, P, mu, lam, tb, Fb);
+    // stored as soon as they are known; the pair's lanes store half of the planes each
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-        cot_in[ax * a.stride + p] = xb[ax];
-        cot_in[(kPlaneR + ax) * a.stride + p] = xb[ax];   // the position is x + r
-        cot_in[(3 + ax) * a.stride + p] = vb[ax];
+        const float xs = cot_in[ax * a.stride + p] + pair_sum(xb[ax]), vs = pair_sum(vb[ax]);
+        // the position is x + r: both take its cotangent
+        cot_in[(g ? kPlaneR + ax : ax) * a.stride + p] = xs;
+        if (g == 0) cot_in[(3 + ax) * a.stride + p] = vs;
     }
 #pragma unroll
-    for (int i = 0; i < 9; ++i) {
-        cot_in[(6 + i) * a.stride + p] = a.mass * Ab[i];
-        cot_in[(15 + i) * a.stride + p] = Fb[i];
+    for (int i = 0; i < 9; ++i)
+        if ((i < 5) == (g == 0)) cot_in[(6 + i) * a.stride + p] = a.mass * Ab[i];
+    // A = m B - dt V0 tau  ->  Bb = m Ab,  taub = -dt V0 Ab.  H is read again rather than
+    // held through the gather.
+    float tb[9], Fb[9], tau[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) tb[i] = -a.dt * a.vol0 * Ab[i];
+    load_planes(state, a.stride, p, 15, 9, H);
+    load_planes(cot_in, a.stride, p, 15, 9, Fb);
+    ad_stress_vjp(H, mu, lam, tb, tau, Fb);
+    if (g) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) cot_in[(15 + i) * a.stride + p] = Fb[i];
+    } else {
+        float lb = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) lb += tb[i] * tau[i];   // tau is proportional to E = exp(logE)
+        logE_cot[p] += lb;
     }
-    logE_cot[p] += lb;
 }
 
 AdArgs make_args(const mpm_ad_ctx *c, int64_t n, int64_t stride, double dt) {
@@ -999,60 +1192,39 @@ AdArgs make_args(const mpm_ad_ctx *c, int64_t n, int64_t stride, double dt) {
     a.ny = c->geo.n[1] + 1;
     a.grid = c->grid;
     a.page = c->page;
-    a.blist = c->blist;
     a.direct = c->direct ? 1 : 0;
     a.flag = c->flag;
-    a.cnt = c->cnt;
+    a.ctl = c->ctl;
     a.status = c->status;
     a.n = (int)n;
+    a.pgrid = (int)((n + 8 * kAdParticles - 1) / (8 * kAdParticles)) * 8;
     a.stride = stride;
     a.dt = (float)dt;
     return a;
 }
 
-int grid_blocks(long long work) {
-    const long long b = (work + 255) / 256;
-    return (int)(b < 8192 ? (b > 0 ? b : 1) : 8192);
+// Workgroups that clear a call's leftover arrays: eight nodes per thread, at most 1024.
+int clear_blocks(const AdArgs &a) {
+    const long long nodes = a.direct ? 2 * a.nodes : 2ll * a.cap * 64;
+    return (int)std::min<long long>(1024, (nodes + 2047) / 2048);
 }
 
-// Launch size of the sweeps (all nodes, or at most the pool's 2 * cap * 64).
-int sweep_blocks(const AdArgs &a) { return grid_blocks(a.direct ? 2 * a.nodes : 2ll * a.cap * 64); }
-
-// Blocks marked and given slots (unless direct), P2G into the (zero) m and p planes,
-// the grid update;
-// zero_mp for a forward call.
-void enqueue_forward_grid(const AdArgs &a, const float *state, const float *logE, int zero_mp, hipStream_t s) {
-    if (!a.direct) {
-        hipLaunchKernelGGL(k_ad_mark, dim3(a.n > 0 ? (a.n + 255) / 256 : 1), dim3(256), 0, s, a, state);
-        hipLaunchKernelGGL(k_ad_alloc, dim3((unsigned int)((a.nbv + 255) / 256), 2), dim3(256), 0, s, a);
-    }
-    const dim3 pg((a.n + 255) / 256), sg(sweep_blocks(a)), wg(256);
+// Blocks marked and given slots (unless direct), then P2G.  n > 0.
+void enqueue_p2g(const AdArgs &a, const float *state, const float *logE, hipStream_t s) {
+    const dim3 wg(256), grid(a.pgrid + clear_blocks(a));
     if (a.direct) {
-        if (a.n > 0) hipLaunchKernelGGL(k_ad_p2g<false>, pg, wg, 0, s, a, state, logE);
-        hipLaunchKernelGGL(k_ad_grid<false>, sg, wg, 0, s, a, zero_mp);
+        hipLaunchKernelGGL(k_ad_p2g<false>, grid, wg, 0, s, a, state, logE);
     } else {
-        if (a.n > 0) hipLaunchKernelGGL(k_ad_p2g<true>, pg, wg, 0, s, a, state, logE);
-        hipLaunchKernelGGL(k_ad_grid<true>, sg, wg, 0, s, a, zero_mp);
+        hipLaunchKernelGGL(k_ad_mark, dim3((a.n + 255) / 256), wg, 0, s, a, state);
+        hipLaunchKernelGGL(k_ad_alloc, dim3((unsigned int)((a.nbv + 255) / 256), 2), wg, 0, s, a);
+        hipLaunchKernelGGL(k_ad_p2g<true>, grid, wg, 0, s, a, state, logE);
     }
 }
 
 void free_buffers(mpm_ad_ctx *c) {
-    void *bufs[] = {c->grid, c->page, c->blist, c->flag, c->cnt, c->status};
+    void *bufs[] = {c->grid, c->page, c->flag, c->ctl, c->status};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
-}
-
-void launch_backward_scatter(const AdArgs &a, const float *state, const float *cot_out, float *cot_in, hipStream_t s) {
-    const dim3 pg((a.n + 255) / 256), wg(256);
-    if (a.direct) hipLaunchKernelGGL(k_ad_g2p_vjp<false>, pg, wg, 0, s, a, state, cot_out, cot_in);
-    else hipLaunchKernelGGL(k_ad_g2p_vjp<true>, pg, wg, 0, s, a, state, cot_out, cot_in);
-}
-
-void launch_backward_gather(const AdArgs &a, const float *state, const float *logE, float *cot_in, float *logE_cot,
-                            hipStream_t s) {
-    const dim3 pg((a.n + 255) / 256), wg(256);
-    if (a.direct) hipLaunchKernelGGL(k_ad_p2g_vjp<false>, pg, wg, 0, s, a, state, logE, cot_in, logE_cot);
-    else hipLaunchKernelGGL(k_ad_p2g_vjp<true>, pg, wg, 0, s, a, state, logE, cot_in, logE_cot);
 }
 
 mpm_status check_call(const mpm_ad_ctx *c, int64_t n, int64_t stride, const float *state, double dt) {
@@ -1091,18 +1263,16 @@ mpm_status mpm_ad_create(const mpm_config *cfg, const mpm_material *mat, mpm_ad_
     c->direct = c->cap == c->nbv;
     c->nodes = c->direct ? (long long)(cfg->n_cells[0] + 1) * (cfg->n_cells[1] + 1) * (cfg->n_cells[2] + 1)
                          : (long long)(c->cap + 1) * 64;
-    const size_t bytes = (size_t)kGridPlanes * 2 * c->nodes * sizeof(float);
+    const size_t bytes = 3 * 2 * (size_t)c->nodes * sizeof(float4);
     const size_t nbv2 = 2 * (size_t)c->nbv;
-    bool ok = hipMalloc(&c->grid, bytes) == hipSuccess && hipMalloc(&c->cnt, 2 * sizeof(unsigned int)) == hipSuccess &&
+    bool ok = hipMalloc(&c->grid, bytes) == hipSuccess && hipMalloc(&c->ctl, kCtlWords * sizeof(unsigned int)) == hipSuccess &&
               hipMalloc(&c->status, sizeof(unsigned int)) == hipSuccess;
-    if (!c->direct)   // page tables, slot list and marks of the block-sparse pool
-        ok = ok && hipMalloc(&c->page, nbv2 * sizeof(int)) == hipSuccess &&
-             hipMalloc(&c->blist, 2 * (size_t)c->cap * sizeof(int)) == hipSuccess &&
-             hipMalloc(&c->flag, nbv2) == hipSuccess && hipMemset(c->flag, 0, nbv2) == hipSuccess;
-    // the scatter targets (m, p, v~b) start at zero and every call leaves the nodes it
-    // swept at zero; no block is marked between calls
+    if (!c->direct)   // page tables and marks of the block-sparse pool
+        ok = ok && hipMalloc(&c->page, nbv2 * sizeof(int)) == hipSuccess && hipMalloc(&c->flag, nbv2) == hipSuccess && hipMemset(c->flag, 0, nbv2) == hipSuccess;
+    // the scatter targets start at zero, and every call clears what the call before left
+    // in the arrays that the next one uses; no block is marked between calls
     ok = ok && hipMemset(c->grid, 0, bytes) == hipSuccess &&
-         hipMemset(c->cnt, 0, 2 * sizeof(unsigned int)) == hipSuccess &&
+         hipMemset(c->ctl, 0, kCtlWords * sizeof(unsigned int)) == hipSuccess &&
          hipMemset(c->status, 0, sizeof(unsigned int)) == hipSuccess;
     if (!ok) {
         free_buffers(c);
@@ -1130,10 +1300,11 @@ mpm_status mpm_ad_forward(mpm_ad_ctx *c, int64_t n, int64_t stride, const float 
     if (hipSetDevice(c->device) != hipSuccess) return MPM_E_HIP;
     hipStream_t s = (hipStream_t)stream;
     const AdArgs a = make_args(c, n, stride, dt);
-    enqueue_forward_grid(a, state_in, logE, 1, s);
     if (n > 0) {
-        if (a.direct) hipLaunchKernelGGL(k_ad_g2p<false>, dim3((n + 255) / 256), dim3(256), 0, s, a, state_in, state_out);
-        else hipLaunchKernelGGL(k_ad_g2p<true>, dim3((n + 255) / 256), dim3(256), 0, s, a, state_in, state_out);
+        const dim3 pg(a.pgrid), wg(256);
+        enqueue_p2g(a, state_in, logE, s);
+        if (a.direct) hipLaunchKernelGGL(k_ad_g2p<false>, pg, wg, 0, s, a, state_in, state_out);
+        else hipLaunchKernelGGL(k_ad_g2p<true>, pg, wg, 0, s, a, state_in, state_out);
     }
     return hipGetLastError() == hipSuccess ? MPM_OK : MPM_E_HIP;
 }
@@ -1146,13 +1317,17 @@ mpm_status mpm_ad_backward(mpm_ad_ctx *c, int64_t n, int64_t stride, const float
     if (hipSetDevice(c->device) != hipSuccess) return MPM_E_HIP;
     hipStream_t s = (hipStream_t)stream;
     const AdArgs a = make_args(c, n, stride, dt);
-    enqueue_forward_grid(a, state_in, logE, 0, s);
-    if (n > 0)
-        launch_backward_scatter(a, state_in, cot_out, cot_in, s);
-    if (a.direct) hipLaunchKernelGGL(k_ad_grid_vjp<false>, dim3(sweep_blocks(a)), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(k_ad_grid_vjp<true>, dim3(sweep_blocks(a)), dim3(256), 0, s, a);
-    if (n > 0)
-        launch_backward_gather(a, state_in, logE, cot_in, logE_cot, s);
+    if (n > 0) {
+        const dim3 pg(a.pgrid), wg(256);
+        enqueue_p2g(a, state_in, logE, s);
+        if (a.direct) {
+            hipLaunchKernelGGL(k_ad_g2p_vjp<false>, pg, wg, 0, s, a, state_in, cot_out, cot_in);
+            hipLaunchKernelGGL(k_ad_p2g_vjp<false>, pg, wg, 0, s, a, state_in, logE, cot_in, logE_cot);
+        } else {
+            hipLaunchKernelGGL(k_ad_g2p_vjp<true>, pg, wg, 0, s, a, state_in, cot_out, cot_in);
+            hipLaunchKernelGGL(k_ad_p2g_vjp<true>, pg, wg, 0, s, a, state_in, logE, cot_in, logE_cot);
+        }
+    }
     return hipGetLastError() == hipSuccess ? MPM_OK : MPM_E_HIP;
 }
 
@@ -1163,7 +1338,7 @@ mpm_status mpm_ad_sync(mpm_ad_ctx *c, void *stream) {
     unsigned int bits = 0;
     if (hipMemcpy(&bits, c->status, sizeof bits, hipMemcpyDeviceToHost) != hipSuccess) return MPM_E_HIP;
     const unsigned int zero = 0;
-    if (hipMemcpy(c->status, &zero, sizeof zero, hipMemcpyHostToDevice) != hipSuccess) return MPM_E_HIP;
+    if (bits != 0 && hipMemcpy(c->status, &zero, sizeof zero, hipMemcpyHostToDevice) != hipSuccess) return MPM_E_HIP;
     return status_from_bits(bits);
 }
 

@@ -38,7 +38,7 @@ class AdContext:
 def ad_config(sc, direct_budget_mib: int = 256) -> ckmpm.mpm_config:
     """mpm_config for the differentiable step on scene sc: a pool slot for every
     4x4x4-node block of the lattice (no per-call marking) when that costs at most
-    `direct_budget_mib` MiB of device memory (7 KiB per block), else the block-sparse
+    `direct_budget_mib` MiB of device memory (counted at 7 KiB per block), else the block-sparse
     pool sized as for the main step."""
     nb = 1
     for a in range(3):
