@@ -241,7 +241,8 @@ mpm_status mpm_get_stats(mpm_ctx *ctx, mpm_stats *out, void *stream);
 
 /* Per-phase timing with HIP events on the launch stream: enable, read totals (ms) and
  * interval counts of the phases {sort+activate, p2g, grid update, g2p, fused g2p+p2g}
- * since enabling (n_phases <= 5 are filled).  In mpm_step the steps after the first
+ * since enabling (n_phases <= 5 are filled).  In mpm_step every step but the last has
+ * its grid update inside its g2p.  With MPM_FLAG_FUSED_G2P2G the steps after the first
  * time the fused kernel as phase 4 and have no separate g2p; the last step's sort and
  * G2P together count as g2p. */
 mpm_status mpm_profile_enable(mpm_ctx *ctx, int32_t enable);

@@ -41,6 +41,7 @@ struct mpm_ctx {
     int grid_pool = 0, grid_table = 0;   // the grid the last p2g (or fused step) wrote: pool and page table
     int next_table = 0;                  // page table the next sort builds
     int written = -1;                    // buffer the last g2p wrote (mpm_current_buffer)
+    bool counts_clean = false;           // the block counts were zeroed by work of this very call
     unsigned int *host_counters = nullptr;
     // profiling
     bool prof = false;
@@ -241,15 +242,20 @@ mpm_status enqueue_p2g(mpm_ctx *ctx, const mpm_particles *p, double dt, hipStrea
     const bool keep_orders = physics && ready && !ctx->d.quadratic && ctx->d.transfer == MPM_TRANSFER_MLS &&
                              !(ctx->cfg.flags & MPM_FLAG_FUSED_G2P2G);
     if (ev) (void)hipEventRecord(ev[0], s);
-    if (!ready) launch_flag_keys(ctx->d, pa, 1, s);
+    if (!ready) {
+        // counts left by a G2P whose keys are not used, or by a sort without a G2P
+        if (!ctx->counts_clean) launch_clear_counts(ctx->d, s);
+        launch_flag_keys(ctx->d, pa, 1, s);
+    }
+    ctx->counts_clean = false;
     // deterministic mode recomputes the stress from F every step, so that a run
     // resumed from its particle state sees the same stress as the uninterrupted run;
-    // the stress pass also adds the state's contribution bound, which the bucket scan
+    // the stress pass also adds the state's contribution bound, which the bucketing
     // below hands to the P2G
     if (physics && (!ready || ctx->d.det)) launch_stress(ctx->d, pa, s);
     const int t = ctx->next_table;
     launch_compact(ctx->d, t, s);
-    launch_bucket(ctx->d, pa.n, t, t, s, keep_orders);
+    launch_bucket(ctx->d, pa.n, t, t, s, keep_orders, !ready);
     ctx->next_table = t ^ 1;
     if (ev) (void)hipEventRecord(ev[1], s);
     if (!physics) {
@@ -344,6 +350,9 @@ mpm_status carve_buffers(DevCtx &d, const mpm_config &cfg, Take take) {
                     take_buffer(take, &d.bslots, (size_t)kBoundWords) &&
                     take_buffer(take, &d.nbrs, 27 * nb) &&
                     (!d.det || take_buffer(take, &d.stage, nb * (size_t)kStageFloats));
+    // the grid stamps take the first half of their buffer, the chunks' particle counts
+    // (one per kCompactChunk blocks) the second
+    d.chunk_n = ok ? d.gflag + stamp_stride(d.nbv) : nullptr;
     return ok ? MPM_OK : MPM_E_OOM;
 }
 
@@ -672,6 +681,7 @@ mpm_status mpm_invalidate(mpm_ctx *ctx) {
 mpm_status mpm_get_stats(mpm_ctx *ctx, mpm_stats *out, void *stream) {
     if (!ctx || !out) return MPM_E_INVALID;
     DeviceGuard g(ctx->device);
+    launch_stats(ctx->d, (hipStream_t)stream);
     if (hipStreamSynchronize((hipStream_t)stream) != hipSuccess) return MPM_E_HIP;
     if (hipMemcpy(ctx->host_counters, ctx->d.counters, C_COUNT * sizeof(unsigned int), hipMemcpyDeviceToHost) != hipSuccess)
         return MPM_E_HIP;
@@ -723,17 +733,6 @@ mpm_status noalloc_scratch(int dev, unsigned char **out) {
     return MPM_OK;
 }
 
-__global__ void k_fill_words(uint32_t *p, uint32_t value, long long n) {
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-        p[i] = value;
-}
-
-void fill_words(void *p, uint32_t value, long long n, hipStream_t s) {
-    const long long blocks = (n + 255) / 256;
-    hipLaunchKernelGGL(k_fill_words, dim3((unsigned)(blocks < 1024 ? (blocks > 0 ? blocks : 1) : 1024)), dim3(256), 0, s,
-                       static_cast<uint32_t *>(p), value, n);
-}
-
 // mpm_status code of the status bits, in mpm_sync's order.
 __global__ void k_status_code(const unsigned int *counters, int32_t *out) {
     const unsigned int b = counters[C_STATUS];
@@ -775,19 +774,11 @@ mpm_status mpm_step_noalloc(const mpm_config *cfg, const mpm_material *mats, int
     });
     if (sc != MPM_OK) return MPM_E_SCRATCH;
     // the previous call's contents stay in the array: reset what a new context starts
-    // from (epoch stamps, page tables, block ranks, block starts, counters), with fill
-    // kernels on the caller's stream
+    // from (counts, stamps, page tables, block ranks, block starts, counters), with a
+    // kernel on the caller's stream
     hipStream_t s = (hipStream_t)stream;
-    const long long nv = d.nbv, nb = cfg->max_blocks;
-    fill_words(d.pflag, 0u, 2 * stamp_stride(nv), s);
-    fill_words(d.gflag, 0u, 2 * stamp_stride(nv), s);
-    fill_words(d.page[0], 0xffffffffu, nv, s);
-    fill_words(d.page[1], 0xffffffffu, nv, s);
-    fill_words(d.prank, 0xffffffffu, nv, s);
-    fill_words(d.bchg, 0xffffffffu, nv, s);
-    fill_words(d.pstart, 0u, nb + 1, s);
-    fill_words(d.counters, 0u, C_COUNT, s);
-    fill_words(d.bslots, 0u, kBoundWords, s);
+    launch_reset(d, s);
+    ctx.counts_clean = true;
     mpm_status st = last_error();
     if (st == MPM_OK) st = step_sequence(&ctx, p, dt, nsteps, s);
     if (st == MPM_OK && status) {

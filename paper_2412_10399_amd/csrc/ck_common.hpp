@@ -32,8 +32,8 @@ enum Counter : int {
     C_NGB = 1,      // grid blocks of page table 0 (table 1: C_NGB1)
     C_STATUS = 2,   // status bits
     C_EPOCH = 3,    // current activation epoch
-    C_MAXPB = 4,    // largest particle count of a block
-    C_TOTAL = 5,    // particles placed by the sort
+    C_MAXPB = 4,    // largest particle count of a block (formed when statistics are asked for)
+    C_SORT = 5,     // epoch of the sort in progress: set by its compaction, made current by its bucketing
     C_NGB1 = 6,
     C_BOUND_X = 7,  // P2G contribution bound, as X + dt Y (FP32 bit patterns, maxima from bslots):
     C_BOUND_Y = 8,  //   the stress pass's exact form, or headroom times the previous P2G's largest
@@ -77,9 +77,12 @@ struct DevCtx {
     uint32_t *bucket;      // [max_blocks][kMaxBlockParticles]: particle indices of each particle
                            // block, in arrival order
     uint32_t *perm;        // exact stable sort order
-    int *pflag, *gflag;    // [2][stamp_stride(nbv)] epoch stamps ("holds particles" / "within one block of a
-                           // block holding particles"), double-buffered by epoch parity so that
-                           // stamping the next step never disturbs readers of the current one
+    int *pflag;            // [2][stamp_stride(nbv)] particles per virtual block, one half per epoch parity:
+                           // the G2P of a step counts the next step's particles into the other half
+                           // and zeroes this step's entries, so that a half is all zero before
+                           // it is counted into again
+    int *gflag;            // [stamp_stride(nbv)] epoch in which the block was last within one block of
+                           // a block holding particles (no kernel that stamps reads stamps)
     int *page[2];          // two page tables: per virtual block the physical pool block, or -1
     int *prank;            // per virtual block: rank among the particle blocks
     int *bchg;             // per virtual block: epoch of the last step whose G2P changed the set or the
@@ -90,9 +93,9 @@ struct DevCtx {
     int *nbrs;             // per particle block: pool blocks of its 3 x 3 x 3 neighbourhood in the
                            // step's page table (-1: none), written by P2G and read by G2P
     int *pstart;           // first sorted position of each particle block (+1 sentinel)
-    int *bcount;           // particles per particle block
+    int *bcount;           // particles in the bucket of each particle block (none where the order is kept)
     int *glist[2];         // per page table: virtual id of each physical pool block
-    int *chunk_p, *chunk_g;
+    int *chunk_p, *chunk_g, *chunk_n;   // per compaction chunk: particle blocks, grid blocks, particles
     float *pool[2];        // two grids of max_blocks * 512 floats (the fused step reads one and
                            // writes the other)
     float *tau;            // [6][max_particles] Kirchhoff stress of the state G2P wrote, at its sorted position
@@ -101,7 +104,7 @@ struct DevCtx {
     int det;               // deterministic P2G: block tiles go to `stage`, then a fixed-order gather
     float *stage;          // [max_blocks][4 channels][kTileNodes] per particle block (deterministic mode)
     unsigned int *bslots;  // [2][kBoundSlots][32]: partial maxima of the contribution bound (X, then Y),
-                           // one 128-byte line per slot, reduced into the counters by the bucket scan
+                           // one 128-byte line per slot, reduced into the counters by the bucketing
 };
 
 // One of the context's two pools, page tables or block lists: a selection between two
@@ -227,12 +230,46 @@ __device__ __forceinline__ int vblock_id(const Geometry &g, int bx, int by, int 
     return (bz * g.NB[1] + by) * g.NB[0] + bx;
 }
 
-// Stamp array of a given epoch (double buffer indexed by the epoch's parity).
-// Each epoch's stamps start at a multiple of 64 entries, so that both halves are
-// 256-byte aligned for vector loads.
+// The stamp arrays are padded to a multiple of 64 entries, so that both halves of the
+// counts are 256-byte aligned for vector loads.
 __host__ __device__ constexpr long long stamp_stride(long long nbv) { return (nbv + 63) / 64 * 64; }
-__device__ __forceinline__ int *stamps(int *base, long long nbv, int epoch) {
-    return base + (epoch & 1) * stamp_stride(nbv);
+// Particle counts of the virtual blocks in a given epoch.
+__device__ __forceinline__ int *block_counts(const DevCtx &d, int epoch) {
+    return d.pflag + (epoch & 1) * stamp_stride(d.nbv);
+}
+
+// For the sort of epoch E: `count` particles in block (bx,by,bz), whose 3 x 3 x 3
+// neighbourhood becomes grid blocks (it holds the particles' 16-node stencils, and also
+// their stencils after a move of up to three cells, which lets one sort serve the grid
+// that the next step's fused transfer writes).  Called by every lane of a wave with the
+// same arguments: lanes 0..26 stamp one neighbour each.
+__device__ __forceinline__ void stamp_block(const DevCtx &d, int bx, int by, int bz, int count, int E) {
+    const int lane = threadIdx.x & 63;
+    const Geometry &g = d.geo;
+    if (lane < 27) {
+        const int x = bx + lane % 3 - 1, y = by + (lane / 3) % 3 - 1, z = bz + lane / 9 - 1;
+        if (x >= 0 && y >= 0 && z >= 0 && x < g.NB[0] && y < g.NB[1] && z < g.NB[2]) d.gflag[vblock_id(g, x, y, z)] = E;
+    } else if (lane == 27) {
+        atomicAdd(&block_counts(d, E)[vblock_id(g, bx, by, bz)], count);
+    }
+}
+
+// The same for the blocks of a wave's lanes (on: the lane has one), once per run of equal
+// blocks: particles in block order mostly share a few blocks per wave.  Every lane calls
+// it.
+__device__ __forceinline__ void wave_stamp(const DevCtx &d, bool on, int bx, int by, int bz, int E) {
+    const int lane = threadIdx.x & 63;
+    const int vb = on ? vblock_id(d.geo, bx, by, bz) : -1;
+    const int prev = __shfl_up(vb, 1);
+    const unsigned long long starts = __ballot(lane == 0 || prev != vb);
+    unsigned long long lead = starts & __ballot(on);
+    while (lead) {
+        const int l = __ffsll((long long)lead) - 1;
+        lead &= lead - 1;
+        const unsigned long long after = starts & ~((2ull << l) - 1ull);   // (l = 63: 2 << 63 is 0)
+        stamp_block(d, __builtin_amdgcn_readlane(bx, l), __builtin_amdgcn_readlane(by, l), __builtin_amdgcn_readlane(bz, l),
+                    (after ? __ffsll((long long)after) - 1 : 64) - l, E);
+    }
 }
 
 // Cell of a position on grid G- (particle keys) and the fractional coordinates on
@@ -804,11 +841,19 @@ struct Allocator {
 };
 
 void launch_flag_keys(const DevCtx &d, const PartArgs &pa, int epoch_offset, hipStream_t s);
-void launch_clear_flags(const DevCtx &d, hipStream_t s);
+// Zeroes the block counts of both epochs: before keys are computed afresh.
+void launch_clear_counts(const DevCtx &d, hipStream_t s);
+// Puts the buffers of a context into the state a new one starts from, and its statistics
+// into the counters.
+void launch_reset(const DevCtx &d, hipStream_t s);
+void launch_stats(const DevCtx &d, hipStream_t s);
 void launch_compact(const DevCtx &d, int table, hipStream_t s);
+// marked: the keys were computed by launch_flag_keys, which leaves marks in place of the
+// block counts: the blocks' ranges of sorted positions are formed after the bucketing.
 // reuse: as for launch_p2g (blocks whose order the P2G keeps get their position range
 // instead of a filled bucket)
-void launch_bucket(const DevCtx &d, int n, int zero_pool, int zero_table, hipStream_t s, bool reuse = false);
+void launch_bucket(const DevCtx &d, int n, int zero_pool, int zero_table, hipStream_t s, bool reuse = false,
+                   bool marked = false);
 void launch_block_sort(const DevCtx &d, hipStream_t s);
 void launch_stress(const DevCtx &d, const PartArgs &pa, hipStream_t s);
 // carried: the B planes of pa.in hold Q, the first remainder plane the packed remainder,

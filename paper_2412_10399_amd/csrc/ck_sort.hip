@@ -3,10 +3,11 @@
 // The particles are sorted stably by key = (4^3-cell block) * 64 + (cell in block),
 // the G- cell being floor((x - origin)/dx + 1/4) per axis.  A stable sort by key is
 // the same as a sort by (key, index), which we build in two exact stages:
-//   1. bucket by block: blocks holding particles are enumerated in increasing
-//      virtual id (compaction of per-block epoch stamps), every particle takes a slot
-//      in its block's fixed-size bucket with one wave-aggregated atomic, and a scan
-//      of the bucket sizes gives each block its range of sorted positions;
+//   1. bucket by block: whoever writes a particle's key (the previous G2P, or the pass
+//      over the positions below) counts it into its block; the compaction enumerates
+//      the blocks holding particles in increasing virtual id and, from a prefix sum of
+//      the counts, gives each its range of sorted positions; every particle then takes a
+//      slot in its block's fixed-size bucket with one atomic per run of particles;
 //   2. inside each block (in the P2G workgroup, in LDS): order by (cell, index).
 // Atomics only decide where a particle waits inside its bucket, never its final
 // position, so the resulting permutation is deterministic and exact.
@@ -20,27 +21,23 @@ namespace {
 
 __device__ __forceinline__ int wave_lane() { return __lane_id(); }
 
-// Stamp the virtual blocks a particle needs: its own block (it holds particles) and,
-// as grid blocks, the 3 x 3 x 3 blocks around it.  That neighbourhood holds the
-// particle's 16-node stencil, and also the stencil after a move of up to three
-// cells, which lets one sort serve the grid that the next step's fused transfer
-// writes.
-__device__ __forceinline__ void stamp_blocks(const DevCtx &d, int bx, int by, int bz, int epoch) {
-    const Geometry &g = d.geo;
-    int *pf = stamps(d.pflag, d.nbv, epoch);
-    int *gf = stamps(d.gflag, d.nbv, epoch);
-    pf[vblock_id(g, bx, by, bz)] = epoch;
-    for (int z = max(bz - 1, 0); z <= min(bz + 1, g.NB[2] - 1); ++z)
-        for (int y = max(by - 1, 0); y <= min(by + 1, g.NB[1] - 1); ++y)
-            for (int x = max(bx - 1, 0); x <= min(bx + 1, g.NB[0] - 1); ++x) gf[vblock_id(g, x, y, z)] = epoch;
-}
-
+// kMark: marks in place of block counts, written with the neighbourhood's stamps by the
+// first lane of every run of equal blocks.  Particles in creation order come in short runs
+// (four cells of a row): one atomic per run and stamps run by run made the pass over 4.2M
+// particles 147 us (254 before the XCD order below) against 61; one scan of the bucket
+// sizes afterwards takes 8.  The multi-job form counts: its jobs' other launches
+// are shared with jobs that have counts.
+template <bool kMark>
 __device__ __forceinline__ void b_flag_keys(const DevCtx &d, const PartArgs &pa, int epoch_offset) {
-    const int i = blockIdx.x * kThreads + threadIdx.x;
-
+    // each XCD (workgroups go to the 8 of them round-robin by index) takes a contiguous
+    // eighth of the particles: rows of cells that count into the same blocks then meet in
+    // one L2 (75 -> 61 us at 4.2M particles)
+    const int per = (int)(gridDim.x + 7) >> 3;
+    const int b = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    const int i = b * kThreads + (int)threadIdx.x;
     const int epoch = (int)d.counters[C_EPOCH] + epoch_offset;
     bool ok = i < pa.n;
-    CellCoord cc;
+    CellCoord cc = {};
     if (ok) {
         const float x[3] = {pa.in[i], pa.in[pa.stride + i], pa.in[2 * pa.stride + i]};
         const float xr[3] = {pa.in[kPlaneR * pa.stride + i], pa.in[(kPlaneR + 1) * pa.stride + i],
@@ -51,301 +48,330 @@ __device__ __forceinline__ void b_flag_keys(const DevCtx &d, const PartArgs &pa,
             set_status(d.counters, ST_DOMAIN);
         }
     }
-    // every lane takes part in the neighbour comparison below
-    const int vb = ok ? vblock_id(d.geo, cc.c[0] >> 2, cc.c[1] >> 2, cc.c[2] >> 2) : -1;
+    if (ok) {
+        d.key[i] = cell_key(d.geo, cc);
+        d.sub[i] = (uint16_t)sub_code(cc);
+    }
+    // every lane takes part
+    const int bx = cc.c[0] >> 2, by = cc.c[1] >> 2, bz = cc.c[2] >> 2;
+    if (!kMark) {
+        wave_stamp(d, ok, bx, by, bz, epoch);
+        return;
+    }
+    const Geometry &g = d.geo;
+    const int vb = ok ? vblock_id(g, bx, by, bz) : -1;
     const int prev = __shfl_up(vb, 1);
-    if (!ok) return;
-    d.key[i] = cell_key(d.geo, cc);
-    d.sub[i] = (uint16_t)sub_code(cc);
-    // one stamping lane per run of equal blocks (particles mostly arrive sorted)
-    if ((threadIdx.x & 63) == 0 || prev != vb) stamp_blocks(d, cc.c[0] >> 2, cc.c[1] >> 2, cc.c[2] >> 2, epoch);
+    if (!ok || ((threadIdx.x & 63) != 0 && prev == vb)) return;
+    block_counts(d, epoch)[vb] = 1;
+    for (int z = max(bz - 1, 0); z <= min(bz + 1, g.NB[2] - 1); ++z)
+        for (int y = max(by - 1, 0); y <= min(by + 1, g.NB[1] - 1); ++y)
+            for (int x = max(bx - 1, 0); x <= min(bx + 1, g.NB[0] - 1); ++x) d.gflag[vblock_id(g, x, y, z)] = epoch;
 }
 
-__global__ void __launch_bounds__(kThreads) k_flag_keys(DevCtx d, PartArgs pa, int epoch_offset) { b_flag_keys(d, pa, epoch_offset); }
+__global__ void __launch_bounds__(kThreads) k_flag_keys(DevCtx d, PartArgs pa, int epoch_offset) {
+    b_flag_keys<true>(d, pa, epoch_offset);
+}
 
 // one launch for many jobs: workgroup row y runs job y
 __global__ void __launch_bounds__(kThreads) k_flag_keys_multi(const JobStep *__restrict__ jobs) {
     const JobStep &J = jobs[blockIdx.y];
     if (!J.first) return;
-    b_flag_keys(J.d, J.pa, 1);
+    b_flag_keys<false>(J.d, J.pa, 1);
 }
 
-__global__ void k_clear_flags(DevCtx d) {
-    const long long nst = 2 * stamp_stride(d.nbv);
-    for (long long v = blockIdx.x * (long long)blockDim.x + threadIdx.x; v < nst; v += (long long)gridDim.x * blockDim.x) {
-        d.pflag[v] = 0;
-        d.gflag[v] = 0;
-    }
-}
-
-// Workgroup-wide sum of two counters (256 threads).
-__device__ __forceinline__ void wg_sum2(int &a, int &b, int *sh) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        a += __shfl_down(a, off);
-        b += __shfl_down(b, off);
-    }
-    const int w = threadIdx.x >> 6;
-    if (wave_lane() == 0) {
-        sh[2 * w] = a;
-        sh[2 * w + 1] = b;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int sa = 0, sb = 0;
-        for (int k = 0; k < kThreads / 64; ++k) {
-            sa += sh[2 * k];
-            sb += sh[2 * k + 1];
-        }
-        sh[2 * (kThreads / 64)] = sa;
-        sh[2 * (kThreads / 64) + 1] = sb;
-    }
-    __syncthreads();
-    a = sh[2 * (kThreads / 64)];
-    b = sh[2 * (kThreads / 64) + 1];
-}
-
-constexpr int kPerThread = kCompactChunk / kThreads;   // 4 virtual blocks per thread
-// up to this many chunks (a 1,024-block chunk each; 1,024 chunks is a 1,024^3-cell
-// grid) the emitting workgroups form their own chunk offsets
-constexpr int kPrefixChunks = 1024;
-
-// Flags (stamp == E) of the kPerThread consecutive virtual blocks from `base`, both
-// stamp arrays in one 16-byte load each (every epoch's stamps are 256-byte aligned);
-// element loads where the range ends inside them.
-__device__ __forceinline__ void load_flags(const DevCtx &d, const int *pf, const int *gf, long long base, int E,
-                                           int (&fp)[kPerThread], int (&fg)[kPerThread]) {
-    static_assert(kPerThread == 4, "one int4 per array");
-    if (base + kPerThread <= d.nbv) {
-        const int4 a = *reinterpret_cast<const int4 *>(pf + base);
-        const int4 b = *reinterpret_cast<const int4 *>(gf + base);
-        fp[0] = a.x == E;
-        fp[1] = a.y == E;
-        fp[2] = a.z == E;
-        fp[3] = a.w == E;
-        fg[0] = b.x == E;
-        fg[1] = b.y == E;
-        fg[2] = b.z == E;
-        fg[3] = b.w == E;
-    } else {
-#pragma unroll
-        for (int k = 0; k < kPerThread; ++k) {
-            const long long v = base + k;
-            fp[k] = (v < d.nbv) && (pf[v] == E);
-            fg[k] = (v < d.nbv) && (gf[v] == E);
-        }
-    }
-}
-
-__device__ __forceinline__ void b_compact_count(const DevCtx &d) {
-    __shared__ int sh[16];
-    const int E = (int)d.counters[C_EPOCH] + 1;
-    const int *pf = stamps(d.pflag, d.nbv, E);
-    const int *gf = stamps(d.gflag, d.nbv, E);
-    const long long base = (long long)blockIdx.x * kCompactChunk + threadIdx.x * kPerThread;
-    int fp[kPerThread], fg[kPerThread];
-    load_flags(d, pf, gf, base, E, fp, fg);
-    int cp = 0, cg = 0;
-#pragma unroll
-    for (int k = 0; k < kPerThread; ++k) {
-        cp += fp[k];
-        cg += fg[k];
-    }
-    wg_sum2(cp, cg, sh);
-    if (threadIdx.x == 0) {
-        d.chunk_p[blockIdx.x] = cp;
-        d.chunk_g[blockIdx.x] = cg;
-    }
-}
-
-__global__ void __launch_bounds__(kThreads) k_compact_count(DevCtx d) { b_compact_count(d); }
-
-// one launch for many jobs: workgroup row y runs job y
-__global__ void __launch_bounds__(kThreads) k_compact_count_multi(const JobStep *__restrict__ jobs) {
-    const JobStep &J = jobs[blockIdx.y];
-    if ((long long)blockIdx.x * kCompactChunk >= J.d.nbv) return;
-    b_compact_count(J.d);
-}
-
-// Exclusive scans of two arrays of `n` ints in place by one workgroup of T threads,
-// side by side (every load of both in flight together); returns the two totals.
-template <int T>
-__device__ void wg_scan2_inplace(int *da, int *db, int n, int *sh, int &ta, int &tb) {
-    const int per = (n + T - 1) / T;
-    const int beg = min(n, threadIdx.x * per), end = min(n, beg + per);
-    int la = 0, lb = 0;
+// Ranges of sorted positions from the bucket sizes, where the blocks were only marked
+// (one workgroup).
+__global__ void __launch_bounds__(1024) k_bucket_scan(DevCtx d) {
+    __shared__ int sh[1024 / 64];
+    const int np = (int)d.counters[C_NPB];
+    const int per = (np + 1023) / 1024;
+    const int beg = min(np, (int)threadIdx.x * per), end = min(np, beg + per);
+    int sum = 0, mx = 0;
+#pragma unroll 8
     for (int i = beg; i < end; ++i) {
-        la += da[i];
-        lb += db[i];
+        const int c = d.bcount[i];
+        sum += c;
+        mx = max(mx, c);
     }
-    // inclusive scans of the per-thread sums across the workgroup
-    int va = la, vb = lb;
-    const int lane = wave_lane();
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int t = __shfl_up(va, off), u = __shfl_up(vb, off);
-        if (lane >= off) {
-            va += t;
-            vb += u;
-        }
-    }
-    const int w = threadIdx.x >> 6;
-    constexpr int W = T / 64;
-    if (lane == 63) {
-        sh[w] = va;
-        sh[W + 1 + w] = vb;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int aa = 0, ab = 0;
-        for (int k = 0; k < W; ++k) {
-            const int t = sh[k], u = sh[W + 1 + k];
-            sh[k] = aa;
-            sh[W + 1 + k] = ab;
-            aa += t;
-            ab += u;
-        }
-        sh[W] = aa;
-        sh[2 * W + 1] = ab;
-    }
-    __syncthreads();
-    int ra = sh[w] + va - la, rb = sh[W + 1 + w] + vb - lb;
-    for (int i = beg; i < end; ++i) {
-        const int t = da[i], u = db[i];
-        da[i] = ra;
-        db[i] = rb;
-        ra += t;
-        rb += u;
-    }
-    ta = sh[W];
-    tb = sh[2 * W + 1];
-    __syncthreads();
-}
-
-__device__ __forceinline__ void b_compact_scan(const DevCtx &d, int nchunks, int table) {
-    __shared__ int sh[2 * (1024 / 64) + 2];
-    int np, ng;
-    wg_scan2_inplace<1024>(d.chunk_p, d.chunk_g, nchunks, sh, np, ng);
-    if (threadIdx.x == 0) {
-        if (ng > d.max_blocks || np > d.max_blocks) set_status(d.counters, ST_CAPACITY);
-        d.counters[C_NPB] = (unsigned)min(np, d.max_blocks);
-        d.counters[ngb_slot(table)] = (unsigned)min(ng, d.max_blocks);
-        d.counters[C_MAXPB] = 0u;
-        d.counters[C_TOTAL] = 0u;
-    }
-}
-
-__global__ void __launch_bounds__(1024) k_compact_scan(DevCtx d, int nchunks, int table) { b_compact_scan(d, nchunks, table); }
-
-// one launch for many jobs: workgroup row y runs job y
-__global__ void __launch_bounds__(1024) k_compact_scan_multi(const JobStep *__restrict__ jobs) {
-    const JobStep &J = jobs[blockIdx.y];
-    b_compact_scan(J.d, (int)((J.d.nbv + kCompactChunk - 1) / kCompactChunk), J.table);
-}
-
-// Workgroup exclusive scan of one int per thread (256 threads); returns the total.
-__device__ __forceinline__ int wg_excl_scan(int x, int &excl, int *sh) {
-    int v = x;
-    const int lane = wave_lane();
+    if (mx > kMaxBlockParticles) set_status(d.counters, ST_CAPACITY);
+    int v = sum;
+    const int lane = wave_lane(), w = threadIdx.x >> 6;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const int t = __shfl_up(v, off);
         if (lane >= off) v += t;
     }
-    const int w = threadIdx.x >> 6;
     if (lane == 63) sh[w] = v;
     __syncthreads();
-    int pre = 0, tot = 0;
-#pragma unroll
-    for (int k = 0; k < kThreads / 64; ++k) {
-        const int t = sh[k];
-        pre += (k < w) ? t : 0;
-        tot += t;
+    int run = v - sum;
+    for (int k = 0; k < w; ++k) run += sh[k];
+    for (int i = beg; i < end; ++i) {
+        d.pstart[i] = run;
+        run += d.bcount[i];
     }
-    excl = pre + v - x;
-    __syncthreads();
-    return tot;
+    if (threadIdx.x == 1023) d.pstart[np] = run;
 }
 
-// prefix: the chunks' exclusive offsets come from the chunk scan (false), or each
-// workgroup sums the counts of the chunks before its own (true; the last one then
-// writes the totals), which saves the scan's launch when there are few chunks.
-template <bool kPrefix = false>
-__device__ __forceinline__ void b_compact_emit(const DevCtx &d, int table, int nchunks = 0) {
-    __shared__ int sh[8];
-    __shared__ int pre[2 * (kThreads / 64)];
-    const int E = (int)d.counters[C_EPOCH] + 1;
-    const int *pf = stamps(d.pflag, d.nbv, E);
-    const int *gf = stamps(d.gflag, d.nbv, E);
-    const long long base = (long long)blockIdx.x * kCompactChunk + threadIdx.x * kPerThread;
-    int fp[kPerThread], fg[kPerThread];
-    load_flags(d, pf, gf, base, E, fp, fg);
-    int cbp = 0, cbg = 0;   // counts of the chunks before this one
-    if (kPrefix) {
-        for (int c = threadIdx.x; c < (int)blockIdx.x; c += kThreads) {
-            cbp += d.chunk_p[c];
-            cbg += d.chunk_g[c];
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            cbp += __shfl_xor(cbp, off);
-            cbg += __shfl_xor(cbg, off);
+__global__ void k_clear_counts(DevCtx d) {
+    const long long n = 2 * stamp_stride(d.nbv) / 4;
+    int4 *c = reinterpret_cast<int4 *>(d.pflag);
+    for (long long v = blockIdx.x * (long long)blockDim.x + threadIdx.x; v < n; v += (long long)gridDim.x * blockDim.x)
+        c[v] = make_int4(0, 0, 0, 0);
+}
+
+__global__ void k_reset(DevCtx d) {
+    const long long t0 = blockIdx.x * (long long)blockDim.x + threadIdx.x, step = (long long)gridDim.x * blockDim.x;
+    const long long nst = 2 * stamp_stride(d.nbv);
+    for (long long v = t0; v < nst; v += step) {
+        d.pflag[v] = 0;
+        if (v < nst / 2) d.gflag[v] = 0;
+        if (v < d.nbv) {
+            d.page[0][v] = -1;
+            d.page[1][v] = -1;
+            d.prank[v] = -1;
+            d.bchg[v] = -1;
         }
     }
-    int cp = 0, cg = 0;
+    for (long long k = t0; k <= d.max_blocks; k += step) d.pstart[k] = 0;
+    for (long long k = t0; k < kBoundWords; k += step) d.bslots[k] = 0u;
+    if (t0 < C_COUNT) d.counters[t0] = 0u;
+}
+
+// Largest particle count of a block (one workgroup; the counters' other entries are
+// formed by the steps).
+__global__ void __launch_bounds__(1024) k_stats(DevCtx d) {
+    __shared__ int m;
+    if (threadIdx.x == 0) m = 0;
+    __syncthreads();
+    const int np = (int)d.counters[C_NPB];
+    int mx = 0;
+    for (int r = threadIdx.x; r < np; r += 1024) mx = max(mx, d.pstart[r + 1] - d.pstart[r]);
+    atomicMax(&m, mx);
+    __syncthreads();
+    if (threadIdx.x == 0) d.counters[C_MAXPB] = (unsigned)m;
+}
+
+// Workgroup-wide sums of three counters (256 threads).
+__device__ __forceinline__ void wg_sum3(int (&a)[3], int *sh) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) a[k] += __shfl_xor(a[k], off);
+    const int w = threadIdx.x >> 6;
+    if (wave_lane() == 0)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) sh[3 * w + k] = a[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        a[k] = 0;
+#pragma unroll
+        for (int q = 0; q < kThreads / 64; ++q) a[k] += sh[3 * q + k];
+    }
+    __syncthreads();
+}
+
+constexpr int kPerThread = kCompactChunk / kThreads;   // 4 virtual blocks per thread
+// Chunks of 1,024 blocks up to which one launch does the compaction, every workgroup
+// counting the chunks before its own itself; up to which each emitting workgroup sums the
+// counts of the chunks before its own; above that a scan of the counts stands between.
+// One launch takes 3.5 us at 5 chunks against 3.4 + 3.3 for two, but 10.2 us at 36 chunks
+// against 4.7 + 4.8; the lone workgroup of a scan adds 7 us where the sums are still short.
+constexpr int kSingleChunks = 12;
+constexpr int kPrefixChunks = 4096;
+
+// Particle counts and grid flags (stamp == E) of the kPerThread consecutive virtual blocks
+// from `base`, each array in one 16-byte load (both arrays are 256-byte aligned and padded
+// to a multiple of 64 entries; entries past the last block are never counted or stamped).
+__device__ __forceinline__ void load_flags(const DevCtx &d, const int *pc, long long base, int E, int (&fn)[kPerThread],
+                                           int (&fg)[kPerThread]) {
+    static_assert(kPerThread == 4, "one int4 per array");
+    int4 a = make_int4(0, 0, 0, 0), b = make_int4(0, 0, 0, 0);
+    if (base < stamp_stride(d.nbv)) {
+        a = *reinterpret_cast<const int4 *>(pc + base);
+        b = *reinterpret_cast<const int4 *>(d.gflag + base);
+    }
+    fn[0] = a.x;
+    fn[1] = a.y;
+    fn[2] = a.z;
+    fn[3] = a.w;
+    fg[0] = b.x == E;
+    fg[1] = b.y == E;
+    fg[2] = b.z == E;
+    fg[3] = b.w == E;
+}
+
+__device__ __forceinline__ void add_flags(const int (&fn)[kPerThread], const int (&fg)[kPerThread], int (&c)[3]) {
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) {
-        cp += fp[k];
-        cg += fg[k];
+        c[0] += fn[k] != 0;
+        c[1] += fg[k];
+        c[2] += fn[k];
     }
-    if (kPrefix) {
-        const int w = threadIdx.x >> 6;
-        if ((threadIdx.x & 63) == 0) {
-            pre[w] = cbp;
-            pre[kThreads / 64 + w] = cbg;
-        }
+}
+
+__device__ __forceinline__ void b_compact_count(const DevCtx &d) {
+    __shared__ int sh[3 * (kThreads / 64)];
+    const int E = (int)d.counters[C_EPOCH] + 1;
+    const long long base = (long long)blockIdx.x * kCompactChunk + threadIdx.x * kPerThread;
+    int fn[kPerThread], fg[kPerThread], c[3] = {0, 0, 0};
+    load_flags(d, block_counts(d, E), base, E, fn, fg);
+    add_flags(fn, fg, c);
+    wg_sum3(c, sh);
+    if (threadIdx.x == 0) {
+        d.chunk_p[blockIdx.x] = c[0];
+        d.chunk_g[blockIdx.x] = c[1];
+        d.chunk_n[blockIdx.x] = c[2];
     }
-    int ep, eg;
-    wg_excl_scan(cp, ep, sh);
-    const int gtot = wg_excl_scan(cg, eg, sh);   // (the scans' barriers publish pre)
-    int offp, offg;
-    if (kPrefix) {
-        int bp = 0, bg = 0;
+}
+
+__global__ void __launch_bounds__(kThreads) k_compact_count(DevCtx d) { b_compact_count(d); }
+
+__device__ __forceinline__ int chunk_count(const DevCtx &d) { return (int)((d.nbv + kCompactChunk - 1) / kCompactChunk); }
+
+// one launch for many jobs: workgroup row y runs job y
+__global__ void __launch_bounds__(kThreads) k_compact_count_multi(const JobStep *__restrict__ jobs) {
+    const JobStep &J = jobs[blockIdx.y];
+    if ((int)blockIdx.x >= chunk_count(J.d)) return;
+    b_compact_count(J.d);
+}
+
+// Exclusive scan of an array of `n` ints in place by one workgroup of T threads.
+template <int T>
+__device__ void wg_scan_inplace(int *da, int n, int *sh) {
+    const int per = (n + T - 1) / T;
+    const int beg = min(n, (int)threadIdx.x * per), end = min(n, beg + per);
+    int la = 0;
+    for (int i = beg; i < end; ++i) la += da[i];
+    // inclusive scan of the per-thread sums across the workgroup
+    int va = la;
+    const int lane = wave_lane();
 #pragma unroll
-        for (int k = 0; k < kThreads / 64; ++k) {
-            bp += pre[k];
-            bg += pre[kThreads / 64 + k];
-        }
-        offp = bp + ep;
-        offg = bg + eg;
-        if ((int)blockIdx.x == nchunks - 1 && threadIdx.x == kThreads - 1) {
-            const int np = bp + ep + cp, ng = bg + eg + cg;
-            if (ng > d.max_blocks || np > d.max_blocks) set_status(d.counters, ST_CAPACITY);
-            d.counters[C_NPB] = (unsigned)min(np, d.max_blocks);
-            d.counters[ngb_slot(table)] = (unsigned)min(ng, d.max_blocks);
-            d.counters[C_MAXPB] = 0u;
-            d.counters[C_TOTAL] = 0u;
-        }
-    } else {
-        offp = d.chunk_p[blockIdx.x] + ep;
-        offg = d.chunk_g[blockIdx.x] + eg;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int t = __shfl_up(va, off);
+        if (lane >= off) va += t;
     }
-    int rp = offp, rg = offg;
+    const int w = threadIdx.x >> 6;
+    if (lane == 63) sh[w] = va;
+    __syncthreads();
+    int pre = 0;
+    for (int k = 0; k < w; ++k) pre += sh[k];
+    int ra = pre + va - la;
+    for (int i = beg; i < end; ++i) {
+        const int t = da[i];
+        da[i] = ra;
+        ra += t;
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ void b_compact_scan(const DevCtx &d, int nchunks) {
+    __shared__ int sh[1024 / 64];
+    wg_scan_inplace<1024>(d.chunk_p, nchunks, sh);
+    wg_scan_inplace<1024>(d.chunk_g, nchunks, sh);
+    wg_scan_inplace<1024>(d.chunk_n, nchunks, sh);
+}
+
+__global__ void __launch_bounds__(1024) k_compact_scan(DevCtx d, int nchunks) { b_compact_scan(d, nchunks); }
+
+// one launch for many jobs: workgroup row y runs job y
+__global__ void __launch_bounds__(1024) k_compact_scan_multi(const JobStep *__restrict__ jobs) {
+    const JobStep &J = jobs[blockIdx.y];
+    b_compact_scan(J.d, chunk_count(J.d));
+}
+
+// Workgroup exclusive scan of three ints per thread (256 threads).
+__device__ __forceinline__ void wg_excl_scan3(const int (&x)[3], int (&excl)[3], int *sh) {
+    int v[3] = {x[0], x[1], x[2]};
+    const int lane = wave_lane();
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const int t = __shfl_up(v[q], off);
+            if (lane >= off) v[q] += t;
+        }
+    const int w = threadIdx.x >> 6;
+    if (lane == 63)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) sh[3 * w + q] = v[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        int pre = 0;
+#pragma unroll
+        for (int k = 0; k < kThreads / 64; ++k) pre += (k < w) ? sh[3 * k + q] : 0;
+        excl[q] = pre + v[q] - x[q];
+    }
+}
+
+// How the emission learns what the chunks before its own hold.
+enum EmitFrom {
+    EMIT_FLAGS = 0,    // counts them itself from the counts and stamps (no other launch)
+    EMIT_COUNTS = 1,   // sums the chunk counts before its own
+    EMIT_SCAN = 2      // the chunk counts have been scanned
+};
+
+// Page table entries, block lists, and the particle blocks' ranges of sorted positions
+// for one chunk of virtual blocks.
+template <int kFrom>
+__device__ __forceinline__ void b_compact_emit(const DevCtx &d, int table, int nchunks) {
+    __shared__ int sh[3 * (kThreads / 64)], sh2[3 * (kThreads / 64)];
+    const int E = (int)d.counters[C_EPOCH] + 1;
+    const int *pc = block_counts(d, E);
+    const long long base = (long long)blockIdx.x * kCompactChunk + threadIdx.x * kPerThread;
+    int fn[kPerThread], fg[kPerThread], c[3] = {0, 0, 0}, before[3] = {0, 0, 0}, ex[3];
+    load_flags(d, pc, base, E, fn, fg);
+    if (kFrom == EMIT_FLAGS) {
+#pragma unroll 4
+        for (int q = 0; q < (int)blockIdx.x; ++q) {
+            int an[kPerThread], ag[kPerThread];
+            load_flags(d, pc, (long long)q * kCompactChunk + threadIdx.x * kPerThread, E, an, ag);
+            add_flags(an, ag, before);
+        }
+        wg_sum3(before, sh2);
+    } else if (kFrom == EMIT_COUNTS) {
+        for (int q = threadIdx.x; q < (int)blockIdx.x; q += kThreads) {
+            before[0] += d.chunk_p[q];
+            before[1] += d.chunk_g[q];
+            before[2] += d.chunk_n[q];
+        }
+        wg_sum3(before, sh2);
+    } else {
+        before[0] = d.chunk_p[blockIdx.x];
+        before[1] = d.chunk_g[blockIdx.x];
+        before[2] = d.chunk_n[blockIdx.x];
+    }
+    add_flags(fn, fg, c);
+    wg_excl_scan3(c, ex, sh);
+    int rp = before[0] + ex[0], rg = before[1] + ex[1], rn = before[2] + ex[2];
+    if ((int)blockIdx.x == nchunks - 1 && threadIdx.x == kThreads - 1) {
+        const int np = rp + c[0], ng = rg + c[1];
+        if (ng > d.max_blocks || np > d.max_blocks) set_status(d.counters, ST_CAPACITY);
+        d.counters[C_NPB] = (unsigned)min(np, d.max_blocks);
+        d.counters[ngb_slot(table)] = (unsigned)min(ng, d.max_blocks);
+        d.counters[C_SORT] = (unsigned)E;
+        if (np <= d.max_blocks) d.pstart[np] = rn + c[2];
+    }
     int ph[kPerThread];
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) {
         const int v = (int)(base + k);
-        if (fp[k]) {
+        if (fn[k]) {
             if (rp < d.max_blocks) {
                 d.plist[rp] = v;
                 d.prank[v] = rp;
+                d.pstart[rp] = rn;
                 d.bcount[rp] = 0;
                 d.blo[rp] = 0xffffffffu;
                 d.bhi[rp] = 0u;
+                if (fn[k] > kMaxBlockParticles) set_status(d.counters, ST_CAPACITY);
             } else {
+                if (rp == d.max_blocks) d.pstart[rp] = rn;
                 d.prank[v] = -1;
             }
             ++rp;
+            rn += fn[k];
         }
         ph[k] = -1;
         if (fg[k]) {
@@ -364,44 +390,93 @@ __device__ __forceinline__ void b_compact_emit(const DevCtx &d, int table, int n
         for (int k = 0; k < kPerThread; ++k)
             if (base + k < d.nbv) page_of(d, table)[base + k] = ph[k];
     }
-    (void)gtot;
 }
 
+template <int kFrom>
 __global__ void __launch_bounds__(kThreads) k_compact_emit(DevCtx d, int table, int nchunks) {
-    b_compact_emit<true>(d, table, nchunks);
+    b_compact_emit<kFrom>(d, table, nchunks);
 }
-
-__global__ void __launch_bounds__(kThreads) k_compact_emit_scanned(DevCtx d, int table) { b_compact_emit(d, table); }
 
 // one launch for many jobs: workgroup row y runs job y
+template <int kFrom>
 __global__ void __launch_bounds__(kThreads) k_compact_emit_multi(const JobStep *__restrict__ jobs) {
     const JobStep &J = jobs[blockIdx.y];
-    if ((long long)blockIdx.x * kCompactChunk >= J.d.nbv) return;
-    b_compact_emit(J.d, J.table);
+    const int nchunks = chunk_count(J.d);
+    if ((int)blockIdx.x >= nchunks) return;
+    b_compact_emit<kFrom>(J.d, J.table, nchunks);
 }
 
 // Each particle takes a slot in its block's bucket and writes its index there.
 // Particles arrive nearly sorted (the previous G2P wrote them in block order), so
 // a workgroup's 1024 consecutive particles span few blocks: slots are ranked
 // inside the workgroup (a run of equal blocks gets consecutive slots) and each run
-// costs one global atomic.  Slots past the bucket capacity are not written; the
-// scan below reports the overflow.  The same launch zeroes this step's grid blocks.
+// costs one global atomic.  Slots past the bucket capacity are not written (the
+// compaction reports such a block).  The same launch zeroes this step's grid blocks,
+// makes the sort's epoch the current one and reduces the P2G contribution bound.
 constexpr int kCountPer = 4;                       // consecutive particles per thread
 constexpr int kCountTile = kThreads * kCountPer;   // particles per workgroup
+
+// By the first workgroup of the bucketing, whose other workgroups read neither: the
+// sort's epoch becomes the current one, and the contribution bound for the P2G about to
+// run is formed from the maxima of the slots the previous P2G (or the stress pass)
+// filled, which are cleared for the next.  Empty slots (a sequence of fused steps, which
+// form no bound) leave the last bound in place.
+__device__ __forceinline__ void end_sort(const DevCtx &d, int E) {
+    static_assert(kBoundSlots == 64, "one wave reduces the slots");
+    const int tid = threadIdx.x;
+    if (tid < kBoundSlots) {
+        unsigned int *sx = d.bslots + tid * 32, *sy = d.bslots + (kBoundSlots + tid) * 32;
+        unsigned int bxv = *sx, byv = *sy;
+        *sx = 0u;
+        *sy = 0u;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            bxv = max(bxv, (unsigned int)__shfl_xor((int)bxv, off));
+            byv = max(byv, (unsigned int)__shfl_xor((int)byv, off));
+        }
+        if (tid == 0) {
+            d.counters[C_EPOCH] = (unsigned)E;
+            if ((bxv | byv) != 0u) {
+                d.counters[C_BOUND_X] = bxv;
+                d.counters[C_BOUND_Y] = byv;
+            }
+        }
+    }
+}
 
 // reuse: the state is the one the context's previous G2P wrote; a block that G2P
 // left unchanged keeps its order in the P2G (its particles sit at consecutive
 // positions), so its bucket is not filled: the run's first and last positions go to
 // the block's position range instead.
 __device__ __forceinline__ void b_bucket_count(const DevCtx &d, int n, int zero_pool, int zero_table, bool reuse) {
-    __shared__ int rblk[kCountTile];   // particle block rank of each particle of the tile (-1: skipped)
-    __shared__ int base_of[kCountTile];
-    __shared__ unsigned char kept_of[kCountTile];   // per run start: the block's order is kept
+    constexpr uint32_t kNone = 0xffffffffu >> 6;   // block of a particle that is not placed
+    __shared__ uint32_t vblk[kCountTile];   // virtual block of each particle of the tile
+    __shared__ int rank_of[kCountTile];     // per run start: particle block, -1 when nothing is written
+    __shared__ int base_of[kCountTile];     // and the run's first slot
     __shared__ int wmax[kThreads / 64];
     const int tid = threadIdx.x, lane = wave_lane(), w = tid >> 6;
-    const int E = (int)d.counters[C_EPOCH] + 1;   // the epoch of this sort (the bucket scan ends it)
-    const int *pf = stamps(d.pflag, d.nbv, E);
-    const int base = blockIdx.x * kCountTile;
+    const int E = (int)d.counters[C_SORT];   // the epoch of this sort
+    int *pc = block_counts(d, E);
+    // the tile, each XCD taking a contiguous eighth of them
+    const int per = ((n + kCountTile - 1) / kCountTile + 7) >> 3;
+    const int tile = (int)(blockIdx.x >> 3) < per ? (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3) : -1;
+    const int base = tile >= 0 ? tile * kCountTile : n;
+    const int i0 = base + tid * kCountPer;
+    uint32_t vb[kCountPer];
+    // the thread's 4 keys in one 16-byte load (the library's buffers are 256-byte
+    // aligned), element loads at the tail
+    static_assert(kCountPer == 4, "vector loads take 4 keys");
+    if (i0 + kCountPer <= n) {
+        const uint4 k4 = *reinterpret_cast<const uint4 *>(d.key + i0);
+        vb[0] = k4.x >> 6;
+        vb[1] = k4.y >> 6;
+        vb[2] = k4.z >> 6;
+        vb[3] = k4.w >> 6;
+    } else {
+#pragma unroll
+        for (int k = 0; k < kCountPer; ++k) vb[k] = i0 + k < n ? d.key[i0 + k] >> 6 : kNone;
+    }
+    if (blockIdx.x == 0) end_sort(d, E);
     // zero a share of the pool blocks handed out this step
     {
         const long long nfl = (long long)d.counters[ngb_slot(zero_table)] * (kBlockFloats / 4);
@@ -409,51 +484,10 @@ __device__ __forceinline__ void b_bucket_count(const DevCtx &d, int n, int zero_
         for (long long t = (long long)blockIdx.x * kThreads + tid; t < nfl; t += (long long)gridDim.x * kThreads)
             pool4[t] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
-    int r[kCountPer];
-    uint16_t sb[kCountPer];
-    uint32_t kv[kCountPer];
-    {
-        // the thread's 4 keys and sub-cell codes in one 16-byte and one 8-byte load
-        // (the library's buffers are 256-byte aligned), element loads at the tail
-        const int i0 = base + tid * kCountPer;
-        if (i0 + kCountPer <= n) {
-            const uint4 k4 = *reinterpret_cast<const uint4 *>(d.key + i0);
-            const uint2 s4 = *reinterpret_cast<const uint2 *>(d.sub + i0);
-            kv[0] = k4.x;
-            kv[1] = k4.y;
-            kv[2] = k4.z;
-            kv[3] = k4.w;
-            sb[0] = (uint16_t)(s4.x & 0xffffu);
-            sb[1] = (uint16_t)(s4.x >> 16);
-            sb[2] = (uint16_t)(s4.y & 0xffffu);
-            sb[3] = (uint16_t)(s4.y >> 16);
-        } else {
+    if (base >= n) return;   // the whole workgroup: pool blocks only
 #pragma unroll
-            for (int k = 0; k < kCountPer; ++k) {
-                kv[k] = i0 + k < n ? d.key[i0 + k] : 0xffffffffu;
-                sb[k] = i0 + k < n ? d.sub[i0 + k] : (uint16_t)0;
-            }
-        }
-    }
-    static_assert(kCountPer == 4, "vector loads take 4 keys");
-#pragma unroll
-    for (int k = 0; k < kCountPer; ++k) {
-        const int i = base + tid * kCountPer + k;
-        r[k] = -1;
-        if (i < n) {
-            const uint32_t key = kv[k];
-            if (key != 0xffffffffu) {
-                // a key whose block was not stamped this step cannot be placed; the
-                // stamp and the rank are loaded together (one memory round trip)
-                const int f = pf[key >> 6];
-                const int pr = d.prank[key >> 6];
-                if (f == E) r[k] = pr;
-                else set_status(d.counters, ST_STALE);
-            }
-        }
-        rblk[tid * kCountPer + k] = r[k];
-    }
-    __syncthreads();
+    for (int k = 0; k < kCountPer; ++k) vblk[tid * kCountPer + k] = vb[k];
+    lds_barrier();
     // start of the run of equal blocks each element belongs to: inclusive max-scan
     // of (element starts a run ? position : 0)
     int st[kCountPer];
@@ -461,7 +495,7 @@ __device__ __forceinline__ void b_bucket_count(const DevCtx &d, int n, int zero_
 #pragma unroll
     for (int k = 0; k < kCountPer; ++k) {
         const int j = tid * kCountPer + k;
-        const bool starts = (j == 0) || (rblk[j - 1] != r[k]);
+        const bool starts = (j == 0) || (vblk[j - 1] != vb[k]);
         m = starts ? j : m;
         st[k] = m;
     }
@@ -472,38 +506,48 @@ __device__ __forceinline__ void b_bucket_count(const DevCtx &d, int n, int zero_
         if (lane >= off) v = max(v, t);
     }
     if (lane == 63) wmax[w] = v;
-    __syncthreads();
+    lds_barrier();
     int carry = 0;
     for (int k = 0; k < w; ++k) carry = max(carry, wmax[k]);
     const int up = __shfl_up(v, 1);                       // every lane takes part in the shuffle
     const int prev_thread = lane > 0 ? max(carry, up) : carry;   // max over all earlier threads
 #pragma unroll
     for (int k = 0; k < kCountPer; ++k) st[k] = max(st[k], prev_thread);
-    // the last element of each run takes the run's slots with one atomic
+    // the last element of each run looks its block up and takes the run's slots with one
+    // atomic
 #pragma unroll
     for (int k = 0; k < kCountPer; ++k) {
         const int j = tid * kCountPer + k;
-        if (r[k] < 0) continue;
-        const bool last = (j == kCountTile - 1) || (rblk[j + 1] != r[k]);
-        if (last) {
-            base_of[st[k]] = atomicAdd(&d.bcount[r[k]], j - st[k] + 1);
-            const bool keep = reuse && d.bchg[kv[k] >> 6] != E;
-            kept_of[st[k]] = keep ? 1 : 0;
-            if (keep) {
-                atomicMin(&d.blo[r[k]], (uint32_t)(base + st[k]));
-                atomicMax(&d.bhi[r[k]], (uint32_t)(base + j));
+        const bool last = (j == kCountTile - 1) || (vblk[j + 1] != vb[k]);
+        if (!last) continue;
+        int r = -1;
+        if (vb[k] != kNone) {
+            // a key whose block counts no particles this step cannot be placed
+            const int f = pc[vb[k]], pr = d.prank[vb[k]], chg = d.bchg[vb[k]];
+            if (f == 0) {
+                set_status(d.counters, ST_STALE);
+            } else if (pr < 0) {
+                pc[vb[k]] = 0;   // past the capacity: no G2P visits this block
+            } else if (reuse && chg != E) {
+                atomicMin(&d.blo[pr], (uint32_t)(base + st[k]));
+                atomicMax(&d.bhi[pr], (uint32_t)(base + j));
+            } else {
+                r = pr;
+                base_of[st[k]] = atomicAdd(&d.bcount[pr], j - st[k] + 1);
             }
         }
+        rank_of[st[k]] = r;
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int k = 0; k < kCountPer; ++k) {
         const int j = tid * kCountPer + k;
-        if (r[k] < 0 || kept_of[st[k]]) continue;
+        const int r = rank_of[st[k]];
+        if (r < 0) continue;
         const int slot = base_of[st[k]] + (j - st[k]);
         if (slot < kMaxBlockParticles) {
-            d.bucket[(size_t)r[k] * kMaxBlockParticles + slot] = (uint32_t)(base + j);
-            d.bsub[(size_t)r[k] * kMaxBlockParticles + slot] = sb[k];
+            d.bucket[(size_t)r * kMaxBlockParticles + slot] = (uint32_t)(base + j);
+            d.bsub[(size_t)r * kMaxBlockParticles + slot] = d.sub[base + j];
         }
     }
 }
@@ -519,149 +563,86 @@ __global__ void __launch_bounds__(kThreads) k_bucket_count_multi(const JobStep *
     b_bucket_count(J.d, J.pa.n, J.table, J.table, !J.first);
 }
 
-// Exclusive scan of the bucket sizes into the first sorted position of every
-// particle block (one workgroup of 1024 threads).  In a pass, element
-// base + 1024 u + t (row u) belongs to thread t: the 16 loads of a thread are
-// coalesced across the workgroup and all in flight together.  Each row is scanned
-// across the workgroup (wave scans, then the wave totals through LDS), and the rows
-// follow each other.
-__device__ __forceinline__ void b_bucket_scan(const DevCtx &d) {
-    constexpr int kRows = 16, kPass = kRows * 1024;
-    __shared__ int wtot[kRows][16];   // per row: wave totals, then their exclusive scan
-    __shared__ int rtot[kRows];       // per row: total
-    __shared__ int wmx[16];
-    const int np = (int)d.counters[C_NPB];
-    const int tid = threadIdx.x, lane = wave_lane(), w = tid >> 6;
-    int mx = 0, carry = 0;
-    for (int base = 0; base < np; base += kPass) {
-        int c[kRows], incl[kRows];
-#pragma unroll
-        for (int u = 0; u < kRows; ++u) {
-            const int k = base + u * 1024 + tid;
-            c[u] = k < np ? d.bcount[k] : 0;
-        }
-#pragma unroll
-        for (int u = 0; u < kRows; ++u) {
-            int v = c[u];
-            mx = max(mx, v);
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int t = __shfl_up(v, off);
-                if (lane >= off) v += t;
-            }
-            incl[u] = v;
-            if (lane == 63) wtot[u][w] = v;
-        }
-        __syncthreads();
-        if (tid < kRows) {
-            int run = 0;
-            for (int k = 0; k < 16; ++k) {
-                const int t = wtot[tid][k];
-                wtot[tid][k] = run;
-                run += t;
-            }
-            rtot[tid] = run;
-        }
-        __syncthreads();
-        int run = carry;
-#pragma unroll
-        for (int u = 0; u < kRows; ++u) {
-            const int k = base + u * 1024 + tid;
-            if (k < np) d.pstart[k] = run + wtot[u][w] + incl[u] - c[u];
-            run += rtot[u];
-        }
-        carry = run;
-        __syncthreads();   // wtot and rtot are rewritten by the next pass
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = max(mx, __shfl_down(mx, off));
-    if (lane == 0) wmx[w] = mx;
-    __syncthreads();
-    if (tid == 0) {
-        int m = 0;
-        for (int k = 0; k < 16; ++k) m = max(m, wmx[k]);
-        d.pstart[np] = carry;
-        d.counters[C_MAXPB] = (unsigned)m;
-        d.counters[C_TOTAL] = (unsigned)carry;
-        // the sort's epoch becomes the current one (every kernel of the sort read the
-        // previous value)
-        d.counters[C_EPOCH] += 1u;
-        if (m > kMaxBlockParticles) set_status(d.counters, ST_CAPACITY);
-    }
-    // the contribution bound for the P2G about to run: maxima of the slots the previous
-    // P2G (or the stress pass) filled, which are cleared for the next.  Empty slots (a
-    // sequence of fused steps, which form no bound) leave the last bound in place.
-    static_assert(kBoundSlots == 64, "one wave reduces the slots");
-    if (tid < kBoundSlots) {
-        unsigned int *sx = d.bslots + tid * 32, *sy = d.bslots + (kBoundSlots + tid) * 32;
-        unsigned int bxv = *sx, byv = *sy;
-        *sx = 0u;
-        *sy = 0u;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            bxv = max(bxv, (unsigned int)__shfl_xor((int)bxv, off));
-            byv = max(byv, (unsigned int)__shfl_xor((int)byv, off));
-        }
-        if (tid == 0 && (bxv | byv) != 0u) {
-            d.counters[C_BOUND_X] = bxv;
-            d.counters[C_BOUND_Y] = byv;
-        }
-    }
-}
+}  // namespace
 
-__global__ void __launch_bounds__(1024) k_bucket_scan(DevCtx d) { b_bucket_scan(d); }
-
-// one launch for many jobs: workgroup row y runs job y
-__global__ void __launch_bounds__(1024) k_bucket_scan_multi(const JobStep *__restrict__ jobs) {
-    const JobStep &J = jobs[blockIdx.y];
-    b_bucket_scan(J.d);
-}
-
+namespace {
+int flag_blocks(int n) { return (n + 8 * kThreads - 1) / (8 * kThreads) * 8; }
 }  // namespace
 
 void launch_flag_keys(const DevCtx &d, const PartArgs &pa, int epoch_offset, hipStream_t s) {
     if (pa.n <= 0) return;
-    hipLaunchKernelGGL(k_flag_keys, dim3((pa.n + kThreads - 1) / kThreads), dim3(kThreads), 0, s, d, pa, epoch_offset);
+    hipLaunchKernelGGL(k_flag_keys, dim3(flag_blocks(pa.n)), dim3(kThreads), 0, s, d, pa, epoch_offset);
 }
 
-void launch_clear_flags(const DevCtx &d, hipStream_t s) {
-    hipLaunchKernelGGL(k_clear_flags, dim3(1024), dim3(256), 0, s, d);
+void launch_clear_counts(const DevCtx &d, hipStream_t s) {
+    const long long wgs = (2 * stamp_stride(d.nbv) / 4 + 255) / 256;
+    hipLaunchKernelGGL(k_clear_counts, dim3((unsigned)std::min<long long>(wgs, 1024)), dim3(256), 0, s, d);
 }
+
+void launch_reset(const DevCtx &d, hipStream_t s) {
+    const long long wgs = std::max<long long>(2 * stamp_stride(d.nbv), std::max<long long>(d.max_blocks, kBoundWords)) / 256 + 1;
+    hipLaunchKernelGGL(k_reset, dim3((unsigned)std::min<long long>(wgs, 1024)), dim3(256), 0, s, d);
+}
+
+void launch_stats(const DevCtx &d, hipStream_t s) { hipLaunchKernelGGL(k_stats, dim3(1), dim3(1024), 0, s, d); }
 
 void launch_compact(const DevCtx &d, int table, hipStream_t s) {
     const int nchunks = (int)((d.nbv + kCompactChunk - 1) / kCompactChunk);
-    hipLaunchKernelGGL(k_compact_count, dim3(nchunks), dim3(kThreads), 0, s, d);
+    const dim3 grid(nchunks), wg(kThreads);
+    if (nchunks <= kSingleChunks) {
+        hipLaunchKernelGGL(k_compact_emit<EMIT_FLAGS>, grid, wg, 0, s, d, table, nchunks);
+        return;
+    }
+    hipLaunchKernelGGL(k_compact_count, grid, wg, 0, s, d);
     if (nchunks <= kPrefixChunks) {
-        // each emitting workgroup sums the chunk counts before its own
-        hipLaunchKernelGGL(k_compact_emit, dim3(nchunks), dim3(kThreads), 0, s, d, table, nchunks);
+        hipLaunchKernelGGL(k_compact_emit<EMIT_COUNTS>, grid, wg, 0, s, d, table, nchunks);
     } else {
-        hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(1024), 0, s, d, nchunks, table);
-        hipLaunchKernelGGL(k_compact_emit_scanned, dim3(nchunks), dim3(kThreads), 0, s, d, table);
+        hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(1024), 0, s, d, nchunks);
+        hipLaunchKernelGGL(k_compact_emit<EMIT_SCAN>, grid, wg, 0, s, d, table, nchunks);
     }
 }
+
+namespace {
+
+// Workgroups of the bucketing: one per tile of particles, and enough to spread the clearing
+// of the pool (at most max_blocks blocks of 128 float4, eight float4 per thread) up to
+// 1,024.
+int bucket_blocks(const DevCtx &d, int n) {
+    const int tiles = ((n + kCountTile - 1) / kCountTile + 7) / 8 * 8;
+    const int zero = (int)std::min<long long>(1024, ((long long)d.max_blocks * (kBlockFloats / 4) + 8 * kThreads - 1) / (8 * kThreads));
+    return std::max(std::max(tiles, zero), 1);
+}
+
+}  // namespace
 
 void launch_sort_multi(const JobStep *dev, const JobStep *host, int njobs, hipStream_t s) {
-    int flag_grid = 0, chunks = 1, tiles = 1024;
+    int flag_grid = 0, chunks = 1, tiles = 1;
     for (int j = 0; j < njobs; ++j) {
         const JobStep &J = host[j];
-        if (J.first) flag_grid = std::max(flag_grid, (J.pa.n + kThreads - 1) / kThreads);
+        if (J.first) flag_grid = std::max(flag_grid, flag_blocks(J.pa.n));
         chunks = std::max(chunks, (int)((J.d.nbv + kCompactChunk - 1) / kCompactChunk));
-        tiles = std::max(tiles, (J.pa.n + kCountTile - 1) / kCountTile);
+        tiles = std::max(tiles, bucket_blocks(J.d, J.pa.n));
     }
-    if (flag_grid > 0) hipLaunchKernelGGL(k_flag_keys_multi, dim3(flag_grid, njobs), dim3(kThreads), 0, s, dev);
-    hipLaunchKernelGGL(k_compact_count_multi, dim3(chunks, njobs), dim3(kThreads), 0, s, dev);
-    hipLaunchKernelGGL(k_compact_scan_multi, dim3(1, njobs), dim3(1024), 0, s, dev);
-    hipLaunchKernelGGL(k_compact_emit_multi, dim3(chunks, njobs), dim3(kThreads), 0, s, dev);
-    hipLaunchKernelGGL(k_bucket_count_multi, dim3(tiles, njobs), dim3(kThreads), 0, s, dev);
-    hipLaunchKernelGGL(k_bucket_scan_multi, dim3(1, njobs), dim3(1024), 0, s, dev);
+    const dim3 cg(chunks, njobs), wg(kThreads);
+    if (flag_grid > 0) hipLaunchKernelGGL(k_flag_keys_multi, dim3(flag_grid, njobs), wg, 0, s, dev);
+    if (chunks <= kSingleChunks) {
+        hipLaunchKernelGGL(k_compact_emit_multi<EMIT_FLAGS>, cg, wg, 0, s, dev);
+    } else {
+        hipLaunchKernelGGL(k_compact_count_multi, cg, wg, 0, s, dev);
+        if (chunks <= kPrefixChunks) {
+            hipLaunchKernelGGL(k_compact_emit_multi<EMIT_COUNTS>, cg, wg, 0, s, dev);
+        } else {
+            hipLaunchKernelGGL(k_compact_scan_multi, dim3(1, njobs), dim3(1024), 0, s, dev);
+            hipLaunchKernelGGL(k_compact_emit_multi<EMIT_SCAN>, cg, wg, 0, s, dev);
+        }
+    }
+    hipLaunchKernelGGL(k_bucket_count_multi, dim3(tiles, njobs), wg, 0, s, dev);
 }
 
-void launch_bucket(const DevCtx &d, int n, int zero_pool, int zero_table, hipStream_t s, bool reuse) {
-    // at least a few hundred workgroups, so that the pool clearing is spread wide
-    const int tiles = (n + kCountTile - 1) / kCountTile;
-    hipLaunchKernelGGL(k_bucket_count, dim3(tiles > 1024 ? tiles : 1024), dim3(kThreads), 0, s, d, n, zero_pool,
-                       zero_table, reuse ? 1 : 0);
-    hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(1024), 0, s, d);
+void launch_bucket(const DevCtx &d, int n, int zero_pool, int zero_table, hipStream_t s, bool reuse, bool marked) {
+    hipLaunchKernelGGL(k_bucket_count, dim3(bucket_blocks(d, n)), dim3(kThreads), 0, s, d, n, zero_pool, zero_table,
+                       reuse ? 1 : 0);
+    if (marked) hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(1024), 0, s, d);
 }
 
 }  // namespace ck

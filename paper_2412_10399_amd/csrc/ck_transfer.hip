@@ -39,31 +39,6 @@ __device__ __forceinline__ void load_neighbours(const DevCtx &d, int table, int 
     }
 }
 
-// Stamps, for the next sort (epoch E), every distinct block among the lanes of a
-// wave (vb < 0: none) as holding particles and its 3 x 3 x 3 neighbourhood as grid
-// blocks, lanes 0..26 writing one neighbour each.  Called by every lane of the wave;
-// particles in block order mostly share a few blocks per wave.
-__device__ __forceinline__ void wave_stamp(const DevCtx &d, int vb, int E) {
-    const int lane = threadIdx.x & 63;
-    const int prev = __shfl_up(vb, 1);
-    unsigned long long lead = __ballot(vb >= 0 && (lane == 0 || prev != vb));
-    const Geometry &g = d.geo;
-    int *pf = stamps(d.pflag, d.nbv, E);
-    int *gf = stamps(d.gflag, d.nbv, E);
-    while (lead) {
-        const int l = __ffsll((long long)lead) - 1;
-        lead &= lead - 1;
-        const int v = __shfl(vb, l);
-        const int bx = v % g.NB[0], by = (v / g.NB[0]) % g.NB[1], bz = v / (g.NB[0] * g.NB[1]);
-        if (lane < 27) {
-            const int x = bx + lane % 3 - 1, y = by + (lane / 3) % 3 - 1, z = bz + lane / 9 - 1;
-            if (x >= 0 && y >= 0 && z >= 0 && x < g.NB[0] && y < g.NB[1] && z < g.NB[2]) gf[vblock_id(g, x, y, z)] = E;
-        } else if (lane == 27) {
-            pf[v] = E;
-        }
-    }
-}
-
 // Addresses of a block's 341 tile nodes, which do not depend on the block: per entry the
 // tile node (bits 0-8: 5 x 5 x 5 of G-, then 6 x 6 x 6 of G+, x fastest), the neighbour
 // block holding it (bits 9-13, the index into nbr), its place in that pool block (bits
@@ -199,6 +174,14 @@ __device__ __forceinline__ void ld_planes(const float *base, long long stride, i
     }
 }
 
+// Whether the block's bucket holds all of its cnt particles (the counts and the keys they
+// were taken with agree); else the status reports a stale state.
+__device__ __forceinline__ bool bucket_full(const DevCtx &d, int r, int cnt) {
+    if (d.bcount[r] == cnt) return true;
+    set_status(d.counters, ST_STALE);
+    return false;
+}
+
 // ---------------------------------------------------------------- block sort
 // Exact stable order of one block's particles by (cell, particle index): counting
 // sort by cell in LDS, then each particle's rank among the equal-cell particles by
@@ -217,7 +200,8 @@ __global__ void __launch_bounds__(kThreads) k_block_sort(DevCtx d) {
         if (r < 0) continue;
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
-        if (cnt > kMaxBlockParticles) continue;   // reported by the bucket scan
+        if (cnt > kMaxBlockParticles) continue;   // reported by the compaction
+        if (!bucket_full(d, r, cnt)) continue;
         if (tid < 64) ccount[tid] = 0;
         __syncthreads();
         uint32_t pk[kSlots];
@@ -918,10 +902,11 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
         load_neighbours(d, gt, bx, by, bz, nbr, 0, d.nbrs + 27 * (size_t)r);
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
-        if (cnt > kMaxBlockParticles) continue;   // reported by the bucket scan
+        if (cnt > kMaxBlockParticles) continue;   // reported by the compaction
         if (reuse && d.bchg[vb] != E) {
             if (!kept_block_order(d, r, s, cnt, ord)) continue;
         } else {
+            if (!bucket_full(d, r, cnt)) continue;
             order_block<true>(d, r, s, cnt, bcnt, bstart, wsum, lbuf, ord, lay, lmask);
         }
         lds_barrier();
@@ -1038,7 +1023,7 @@ __global__ void __launch_bounds__(kP2GThreads, 3) k_p2g_det_multi(const JobStep 
 __device__ __forceinline__ void b_det_gather(const DevCtx &d, int gp, int gt) {
     const int ng = (int)d.counters[ngb_slot(gt)];
     const int E = (int)d.counters[C_EPOCH];
-    const int *pf = stamps(d.pflag, d.nbv, E);
+    const int *pc = block_counts(d, E);
     const int t = threadIdx.x;
     const int g = t >> 6, l = t & 63;
     const int lc[3] = {l & 3, (l >> 2) & 3, l >> 4};
@@ -1060,7 +1045,7 @@ __device__ __forceinline__ void b_det_gather(const DevCtx &d, int gp, int gt) {
                         P[2] >= d.geo.NB[2])
                         continue;
                     const int v = vblock_id(d.geo, P[0], P[1], P[2]);
-                    if (pf[v] != E) continue;   // no particles in that block this step
+                    if (pc[v] == 0) continue;   // no particles in that block this step
                     const int r = d.prank[v];
                     if (r < 0) continue;
                     // the node in block P's tile: G- [4P, 4P+4], G+ [4P-1, 4P+4] per axis
@@ -1425,7 +1410,7 @@ __device__ __forceinline__ int g2p_split(int np) { return np <= 256 * 6 / 4 ? 2 
 template <bool kCarry, bool kCarried>
 __device__ __forceinline__ void g2p_pass(const DevCtx &d, const PartArgs &pa, float dt, const float *vt, int bx,
                                          int by, int bz, int s, int cnt, uint32_t last, int j0, int step, int E,
-                                         G2PIn &cur, G2PIn &nxt, uint32_t &pnext) {
+                                         G2PIn &cur, G2PIn &nxt, uint32_t &pnext, int &stay) {
     const int j = j0 + (int)threadIdx.x;
     const bool act = j < cnt;
     if (kCarried) unpack_remainder(d.geo, cur.rp, cur.xr);
@@ -1436,8 +1421,10 @@ __device__ __forceinline__ void g2p_pass(const DevCtx &d, const PartArgs &pa, fl
     CellCoord cc;
     bool ok = act && cell_coord(d.geo, cur.x, cur.xr, cc);
     ok = ok && (cc.c[0] >> 2) == bx && (cc.c[1] >> 2) == by && (cc.c[2] >> 2) == bz;
-    // activation stamps of the next step (-1: none), deduplicated across the wave
+    // the particle's block in the next step (-1: none)
     int sig = -1;
+    CellCoord cn = {};
+    const int own = vblock_id(d.geo, bx, by, bz);
     // blocks whose particle set or bins change: this one when a particle leaves it or
     // its (octant, cell) bin, and the one it enters
     bool changed = false;
@@ -1447,20 +1434,22 @@ __device__ __forceinline__ void g2p_pass(const DevCtx &d, const PartArgs &pa, fl
         changed = true;
     } else if (ok) {
         NewState ns;
-        CellCoord cn;
         bool placed;
         sig = g2p_particle(d, pa, dt, cur, cc, bx, by, bz, vt, out, true, ns, cn, placed, true, kCarry);
         if (!placed) {
             changed = true;
-        } else if (sig != vblock_id(d.geo, bx, by, bz) || sub_code(cn) != sub_code(cc)) {
+        } else if (sig != own || sub_code(cn) != sub_code(cc)) {
             changed = true;
             d.bchg[sig] = E + 1;
         }
     }
     if (__any(changed)) {
-        if (changed) d.bchg[vblock_id(d.geo, bx, by, bz)] = E + 1;
+        if (changed) d.bchg[own] = E + 1;
     }
-    wave_stamp(d, sig, E + 1);
+    // those that stay are counted for the whole block at its end, the others at once
+    stay += __popcll(__ballot(sig == own));
+    const bool left = sig >= 0 && sig != own;
+    if (__any(left)) wave_stamp(d, left, cn.c[0] >> 2, cn.c[1] >> 2, cn.c[2] >> 2, E + 1);
 }
 
 // Gathers the velocity tile of block (bx,by,bz) (kTileNodes nodes, three channels) by
@@ -1543,6 +1532,7 @@ __device__ __forceinline__ void b_g2p(const DevCtx &d, const PartArgs &pa, float
         block_coords(d.geo, vb, bx, by, bz);
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
+        if (tid == 0 && first == 0) block_counts(d, E)[vb] = 0;   // the step's last use of them
         if (cnt <= first || cnt > kMaxBlockParticles) continue;
         // the first particle's inputs load while the tile is gathered, and the index of
         // the one after
@@ -1558,11 +1548,14 @@ __device__ __forceinline__ void b_g2p(const DevCtx &d, const PartArgs &pa, float
         lds_barrier();
         gather_tile<kFold>(d, dt, gp, nbr, bx, by, bz, vt);
         lds_barrier();
+        int stay = 0;   // the wave's particles that stay in the block
         for (int j0 = first; j0 < cnt; j0 += 2 * step) {   // the same trip count for every lane
-            g2p_pass<kCarry, kCarried>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0, step, E, qa, qb, pnext);
+            g2p_pass<kCarry, kCarried>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0, step, E, qa, qb, pnext, stay);
             if (j0 + step < cnt)
-                g2p_pass<kCarry, kCarried>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0 + step, step, E, qb, qa, pnext);
+                g2p_pass<kCarry, kCarried>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0 + step, step, E, qb, qa, pnext,
+                                           stay);
         }
+        if (stay > 0) stamp_block(d, bx, by, bz, stay, E + 1);
         lds_barrier();
     }
 }
@@ -1752,6 +1745,7 @@ __global__ void __launch_bounds__(kP2GThreads) k_p2g_grad(DevCtx d, PartArgs pa,
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
         if (cnt > kMaxBlockParticles) continue;
+        if (!bucket_full(d, r, cnt)) continue;
         order_block<true>(d, r, s, cnt, bcnt, bstart, wsum, lbuf, ord, lay, lmask);
         load_neighbours(d, gt, bx, by, bz, nbr);
         lds_barrier();
@@ -1799,6 +1793,7 @@ __global__ void __launch_bounds__(kG2PThreads) k_g2p_grad(DevCtx d, PartArgs pa,
         block_coords(d.geo, vb, bx, by, bz);
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
+        if (tid == 0) block_counts(d, E)[vb] = 0;   // the step's last use of them
         if (cnt > kMaxBlockParticles) continue;
         G2PIn nxt;
         if (tid < cnt) g2p_load(d, pa, (uint32_t)(s + tid), nxt);
@@ -1817,6 +1812,7 @@ __global__ void __launch_bounds__(kG2PThreads) k_g2p_grad(DevCtx d, PartArgs pa,
             bool ok = act && cell_coord(d.geo, q.x, q.xr, cc);
             ok = ok && (cc.c[0] >> 2) == bx && (cc.c[1] >> 2) == by && (cc.c[2] >> 2) == bz;
             int sig = -1;
+            CellCoord cn = {};
             if (act && !ok) {
                 set_status(d.counters, ST_STALE);
                 st_at(d.key, out, 0xffffffffu);
@@ -1881,11 +1877,10 @@ __global__ void __launch_bounds__(kG2PThreads) k_g2p_grad(DevCtx d, PartArgs pa,
                 }
                 const DevMaterial M = material_of(d, q.mat);
                 NewState ns;
-                CellCoord cn;
                 bool placed;
                 sig = g2p_finish_c(d, pa, dt, q, M, vn, Bh, Cc, out, true, ns, cn, placed);
             }
-            wave_stamp(d, sig, E + 1);
+            wave_stamp(d, sig >= 0, cn.c[0] >> 2, cn.c[1] >> 2, cn.c[2] >> 2, E + 1);
         }
         lds_barrier();
     }
@@ -2030,7 +2025,8 @@ __global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_quad(DevCtx d, PartArgs 
         block_coords(d.geo, vb, bx, by, bz);
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
-        if (cnt > kMaxBlockParticles) continue;   // reported by the bucket scan
+        if (cnt > kMaxBlockParticles) continue;   // reported by the compaction
+        if (!bucket_full(d, r, cnt)) continue;
         order_block<true>(d, r, s, cnt, bcnt, bstart, wsum, lbuf, ord, lay, lmask);
         load_neighbours(d, gt, bx, by, bz, nbr);
         lds_barrier();
@@ -2090,6 +2086,7 @@ __global__ void __launch_bounds__(kG2PThreads) k_g2p_quad(DevCtx d, PartArgs pa,
         block_coords(d.geo, vb, bx, by, bz);
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
+        if (tid == 0) block_counts(d, E)[vb] = 0;   // the step's last use of them
         if (cnt > kMaxBlockParticles) continue;
         G2PIn nxt;
         if (tid < cnt) g2p_load(d, pa, (uint32_t)(s + tid), nxt);
@@ -2118,6 +2115,7 @@ __global__ void __launch_bounds__(kG2PThreads) k_g2p_quad(DevCtx d, PartArgs pa,
             int lb[3];
             const bool inside = ok && quad_coords(d.geo, cc, bx, by, bz, xi, lb);
             int sig = -1;
+            CellCoord cn = {};
             if (act && !ok) {
                 set_status(d.counters, ST_STALE);
                 st_at(d.key, out, 0xffffffffu);
@@ -2158,11 +2156,10 @@ __global__ void __launch_bounds__(kG2PThreads) k_g2p_quad(DevCtx d, PartArgs pa,
                 const float Di[9] = {4.0f, 0.0f, 0.0f, 0.0f, 4.0f, 0.0f, 0.0f, 0.0f, 4.0f};
                 const DevMaterial M = material_of(d, q.mat);
                 NewState ns;
-                CellCoord cn;
                 bool placed;
                 sig = g2p_finish(d, pa, dt, q, M, vn, Bh, Di, out, true, ns, cn, placed);
             }
-            wave_stamp(d, sig, E + 1);
+            wave_stamp(d, sig >= 0, cn.c[0] >> 2, cn.c[1] >> 2, cn.c[2] >> 2, E + 1);
         }
         lds_barrier();
     }
@@ -2185,6 +2182,7 @@ __global__ void __launch_bounds__(kP2GThreads) k_block_order(DevCtx d) {
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
         if (cnt > kMaxBlockParticles) continue;
+        if (!bucket_full(d, r, cnt)) continue;
         order_block<true>(d, r, s, cnt, bcnt, bstart, wsum, lbuf, ord, lay, lmask);
         lds_barrier();
     }
@@ -2234,7 +2232,9 @@ __global__ void __launch_bounds__(kP2GThreads, 2) k_g2p2g(DevCtx d, PartArgs pa,
         block_coords(d.geo, vb, bx, by, bz);
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
-        if (cnt > kMaxBlockParticles) continue;   // reported by the bucket scan
+        if (tid == 0) block_counts(d, E)[vb] = 0;   // the step's last use of them
+        if (cnt > kMaxBlockParticles) continue;   // reported by the compaction
+        if (!bucket_full(d, r, cnt)) continue;
         order_block<true>(d, r, s, cnt, bcnt, bstart, wsum, lbuf, ord, lay, lmask);
         load_neighbours(d, gt_in, bx, by, bz, nbr_in);
         load_neighbours(d, gt_out, bx, by, bz, nbr_out, 64);
@@ -2264,6 +2264,7 @@ __global__ void __launch_bounds__(kP2GThreads, 2) k_g2p2g(DevCtx d, PartArgs pa,
             bool ok = act && cell_coord(d.geo, q.x, q.xr, cc);
             ok = ok && (cc.c[0] >> 2) == bx && (cc.c[1] >> 2) == by && (cc.c[2] >> 2) == bz;
             int sig = -1;
+            CellCoord cn = {};
             Staged st;
             st.on = false;
             if (act && !ok) {
@@ -2271,7 +2272,6 @@ __global__ void __launch_bounds__(kP2GThreads, 2) k_g2p2g(DevCtx d, PartArgs pa,
                 st_at(d.key, out, 0xffffffffu);
             } else if (ok) {
                 NewState ns;
-                CellCoord cn;
                 bool placed;
                 sig = g2p_particle(d, pa, dt, q, cc, bx, by, bz, vt, out, false, ns, cn, placed, false);
                 if (placed) {
@@ -2279,7 +2279,7 @@ __global__ void __launch_bounds__(kP2GThreads, 2) k_g2p2g(DevCtx d, PartArgs pa,
                     stage_compute(d, M, cn, ns.v, ns.B, ns.tau, dt, st);
                 }
             }
-            wave_stamp(d, sig, E + 1);
+            wave_stamp(d, sig >= 0, cn.c[0] >> 2, cn.c[1] >> 2, cn.c[2] >> 2, E + 1);
             if (st.on) {
                 const int lx = st.c[0] - 4 * bx + 1, ly = st.c[1] - 4 * by + 1, lz = st.c[2] - 4 * bz + 1;
                 if (lx >= 0 && ly >= 0 && lz >= 0 && lx <= 5 && ly <= 5 && lz <= 5)
@@ -2452,7 +2452,7 @@ void launch_step_run(const JobStep *dev, const JobStep *host, int njobs, hipStre
     for (int j = 0; j < njobs; ++j)
         if (host[j].first || host[j].d.det)
             stress_grid = std::max(stress_grid, (host[j].pa.n + kThreads - 1) / kThreads);
-    // the stress pass adds the contribution bound that the sort's bucket scan hands to P2G
+    // the stress pass adds the contribution bound that the sort's bucketing hands to P2G
     if (stress_grid > 0) hipLaunchKernelGGL(k_stress_multi, dim3(stress_grid, njobs), dim3(kThreads), 0, s, dev);
     launch_sort_multi(dev, host, njobs, s);
     bool any_det = false, any_plain = false;
