@@ -236,11 +236,9 @@ mpm_status enqueue_p2g(mpm_ctx *ctx, const mpm_particles *p, double dt, hipStrea
     // when the previous mpm_g2p wrote this very buffer
     const bool ready = ctx->next_ready == pa.in && ctx->next_n == pa.n;
     const bool carried_in = ready && ctx->carried == pa.in;
-    // the compact-kernel MLS G2P records the blocks it changes, so the next P2G may keep
-    // the order of the others (the quadratic and exact-gradient kernels do not; the fused
-    // step orders the first sort's blocks again from their buckets)
-    const bool keep_orders = physics && ready && !ctx->d.quadratic && ctx->d.transfer == MPM_TRANSFER_MLS &&
-                             !(ctx->cfg.flags & MPM_FLAG_FUSED_G2P2G);
+    // the G2P records the blocks it changes, so the next P2G may keep the order of the
+    // others (the fused step orders the first sort's blocks again from their buckets)
+    const bool keep_orders = physics && ready && !(ctx->cfg.flags & MPM_FLAG_FUSED_G2P2G);
     if (ev) (void)hipEventRecord(ev[0], s);
     if (!ready) {
         // counts left by a G2P whose keys are not used, or by a sort without a G2P

@@ -856,14 +856,43 @@ __device__ __forceinline__ double block_scale(float bnd, unsigned int *bmax) {
     return m > 0.0f ? ldexp(1.0, 39 - ilogbf(m)) : 1.0;
 }
 
+// What P2G's block loop takes from a transfer: the staged particle, its contribution
+// bound, its scatter into the block's fixed-point tile (kTileWords words) or straight into
+// the pool, and the tile's flush.  This one: MLS on the two staggered grids (kCarried: the
+// state between the steps of a sequence).
+template <bool kCarried>
+struct MlsTransfer {
+    using Particle = Staged;
+    static constexpr int kTileWords = 4 * (kTileMStride + kTilePStride);   // [4][G-] and [4][G+]
+    static __device__ __forceinline__ void stage(const DevCtx &d, const PartArgs &pa, int p, int bx, int by, int bz,
+                                                 float dt, Staged &st) {
+        stage_particle<kCarried>(d, pa, p, bx, by, bz, dt, st);
+    }
+    static __device__ __forceinline__ float bound(const Staged &st) { return contribution_bound(st); }
+    static __device__ __forceinline__ void scatter(const Staged &st, int bx, int by, int bz, unsigned long long *tile,
+                                                   double S) {
+        scatter_particle_unit<kTY, kTZ, kTileMStride, kTilePStride>(st, st.c[0] - 4 * bx, st.c[1] - 4 * by,
+                                                                    st.c[2] - 4 * bz, tile, tile + 4 * kTileMStride, S);
+    }
+    static __device__ __forceinline__ void direct(const DevCtx &d, float *pool, const int *nbr, int bx, int by, int bz,
+                                                  const Staged &st) {
+        scatter_pool(d, pool, nbr, bx, by, bz, st);
+    }
+    static __device__ __forceinline__ void flush(const DevCtx &d, float *pool, const int *nbr, int, int, int,
+                                                 const unsigned long long *tile, double inv) {
+        flush_tile(d, pool, nbr, tile, tile + 4 * kTileMStride, inv);
+    }
+};
+
 // P2G of the particle blocks.  kFixed (deterministic mode): the fixed-point tile,
 // whose sums are exact and so independent of the order of the atomics; each pass
 // stages two particles per thread, takes the block's unit from their bounds, then
-// scatters them.  Otherwise an FP64 tile: every thread stages and scatters one
-// particle at a time (no unit to agree on first), and the block takes a single pass.
+// scatters them.  Otherwise the same tile in the step-global unit: every thread stages
+// and scatters one particle at a time (no unit to agree on first), and the block takes a
+// single pass.
 // reuse: the input is the state the context's previous G2P wrote, so that the order
 // of a block that G2P left unchanged is kept (kept_block_order).
-template <bool kFixed, bool kCarried = false>
+template <bool kFixed, class Transfer>
 __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt, bool reuse) {
     __shared__ int bcnt[kBins];                 // counts, then placement cursors
     __shared__ int bstart[kBins + 1];
@@ -871,15 +900,13 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
     __shared__ unsigned int bmax;
     __shared__ int nbr[27];
     __shared__ uint32_t ord[kMaxBlockParticles];   // particle index at each position of the block order
-    // ordering buffer, then the fixed-point tile [4][G-] and [4][G+]
-    constexpr int kTileWords = 4 * (kTileMStride + kTilePStride);
+    // ordering buffer, then the fixed-point tile
+    constexpr int kTileWords = Transfer::kTileWords;
     constexpr int kAreaWords = kTileWords > kOrderWords ? kTileWords : kOrderWords;
     __shared__ unsigned long long area[kAreaWords];
     __shared__ int lay[kLayWords];
     __shared__ unsigned long long lmask[kLayMaskWords];
     uint32_t *lbuf = reinterpret_cast<uint32_t *>(area);
-    unsigned long long *tile_m = area;
-    unsigned long long *tile_p = area + 4 * kTileMStride;
     const int np = (int)d.counters[C_NPB];
     const int E = (int)d.counters[C_EPOCH];
     const int tid = threadIdx.x;
@@ -917,30 +944,28 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
             // thread stages and scatters one particle at a time (the first one loads while
             // the tile is cleared).  A particle above the bound (a state changed in place
             // without mpm_invalidate) adds to the pool with float atomics instead.
-            Staged st;
+            typename Transfer::Particle st;
             st.on = false;
-            if (tid < cnt) stage_particle<kCarried>(d, pa, (int)ord[tid], bx, by, bz, dt, st);
+            if (tid < cnt) Transfer::stage(d, pa, (int)ord[tid], bx, by, bz, dt, st);
             for (int q = tid; q < kTileWords; q += kP2GThreads) area[q] = 0ull;
             lds_barrier();
             for (int j = tid; j < cnt; j += kP2GThreads) {
-                if (j > tid) stage_particle<kCarried>(d, pa, (int)ord[j], bx, by, bz, dt, st);
+                if (j > tid) Transfer::stage(d, pa, (int)ord[j], bx, by, bz, dt, st);
                 if (!st.on) continue;
-                const float cb = contribution_bound(st);
+                const float cb = Transfer::bound(st);
                 seen = fmaxf(seen, cb);
-                if (cb <= bound)
-                    scatter_particle_unit<kTY, kTZ, kTileMStride, kTilePStride>(
-                        st, st.c[0] - 4 * bx, st.c[1] - 4 * by, st.c[2] - 4 * bz, tile_m, tile_p, S);
-                else
-                    scatter_pool(d, pool_of(d, gp), nbr, bx, by, bz, st);
+                if (cb <= bound) Transfer::scatter(st, bx, by, bz, area, S);
+                else Transfer::direct(d, pool_of(d, gp), nbr, bx, by, bz, st);
             }
             lds_barrier();
-            flush_tile(d, pool_of(d, gp), nbr, tile_m, tile_p, inv_unit);
+            Transfer::flush(d, pool_of(d, gp), nbr, bx, by, bz, area, inv_unit);
             lds_barrier();
             continue;
         }
 
         // ---- fixed-point tile, kChunk particles per pass (one pass unless the block is dense)
         // (in deterministic mode a block without valid particles still writes a zero tile)
+        unsigned long long *tile_m = area, *tile_p = area + 4 * kTileMStride;
         const int cend = (d.det && cnt == 0) ? 1 : cnt;
         for (int c0 = 0; c0 < cend; c0 += kChunk) {
             for (int q = tid; q < kTileWords; q += kP2GThreads) area[q] = 0ull;
@@ -988,15 +1013,15 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
 // Four waves per SIMD (128 VGPRs, none spilled; 40 KiB of LDS, four workgroups per
 // CU): 0.263 ms on the sand column against 0.303 ms at three.
 __global__ void __launch_bounds__(kP2GThreads, 4) k_p2g(DevCtx d, PartArgs pa, float dt, int gp, int gt, int reuse) {
-    b_p2g<false>(d, pa, dt, gp, gt, reuse != 0);
+    b_p2g<false, MlsTransfer<false>>(d, pa, dt, gp, gt, reuse != 0);
 }
 // the same on a state whose B planes carry Q (the intermediate states of mpm_step)
 __global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_carried(DevCtx d, PartArgs pa, float dt, int gp, int gt,
                                                                  int reuse) {
-    b_p2g<false, true>(d, pa, dt, gp, gt, reuse != 0);
+    b_p2g<false, MlsTransfer<true>>(d, pa, dt, gp, gt, reuse != 0);
 }
 __global__ void __launch_bounds__(kP2GThreads, 3) k_p2g_det(DevCtx d, PartArgs pa, float dt, int gp, int gt, int reuse) {
-    b_p2g<true>(d, pa, dt, gp, gt, reuse != 0);
+    b_p2g<true, MlsTransfer<false>>(d, pa, dt, gp, gt, reuse != 0);
 }
 
 // one launch for many jobs: workgroup row y runs job y (rows of deterministic-mode
@@ -1004,12 +1029,12 @@ __global__ void __launch_bounds__(kP2GThreads, 3) k_p2g_det(DevCtx d, PartArgs p
 __global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_multi(const JobStep *__restrict__ jobs) {
     const JobStep &J = jobs[blockIdx.y];
     if (J.d.det) return;
-    b_p2g<false>(J.d, J.pa, J.dt, J.table, J.table, !J.first);
+    b_p2g<false, MlsTransfer<false>>(J.d, J.pa, J.dt, J.table, J.table, !J.first);
 }
 __global__ void __launch_bounds__(kP2GThreads, 3) k_p2g_det_multi(const JobStep *__restrict__ jobs) {
     const JobStep &J = jobs[blockIdx.y];
     if (!J.d.det) return;
-    b_p2g<true>(J.d, J.pa, J.dt, J.table, J.table, !J.first);
+    b_p2g<true, MlsTransfer<false>>(J.d, J.pa, J.dt, J.table, J.table, !J.first);
 }
 
 // ---------------------------------------------------------------- deterministic P2G sums
@@ -1159,10 +1184,6 @@ __device__ __forceinline__ void g2p_load_index(const PartArgs &pa, uint32_t p, G
     ld_planes(pa.in, S, kPlaneH, p, q.H);
 }
 
-__device__ __forceinline__ void g2p_load(const DevCtx &d, const PartArgs &pa, uint32_t pos, G2PIn &q) {
-    g2p_load_index(pa, ld_at(d.perm, pos), q);
-}
-
 // G2P of one particle (section 4.3 gather, section 4.5 affine matrix, F update,
 // return mapping, advection) on the velocity tile vt of block (bx,by,bz): writes the
 // new state at position `out` of the output buffer (and its stress when write_tau),
@@ -1173,11 +1194,23 @@ struct NewState {
     float x[3], v[3], B[9], tau[6];
 };
 
+// Transfers of the G2P kernels.
+enum { G2P_MLS = 0, G2P_GRAD = 1, G2P_QUAD = 2 };
+
 __device__ __forceinline__ int g2p_finish(const DevCtx &d, const PartArgs &pa, float dt, const G2PIn &q,
                                           const DevMaterial &M, const float (&vn)[3], const float (&Bh)[9],
                                           const float (&Di)[9], uint32_t out, bool write_tau, NewState &ns,
                                           CellCoord &cn, bool &placed, bool write_vB = true, bool carry = false);
+__device__ __forceinline__ int g2p_finish_c(const DevCtx &d, const PartArgs &pa, float dt, const G2PIn &q,
+                                            const DevMaterial &M, const float (&vn)[3], const float (&Bh)[9],
+                                            const float (&Cc)[9], uint32_t out, bool write_tau, NewState &ns,
+                                            CellCoord &cn, bool &placed, bool write_vB = true, bool carry = false);
 
+// kMode G2P_GRAD: the exact velocity gradient C = 1/2 sum v~ grad w^T in place of B D^-1
+// (APIC keeps B, PIC has none).  Per axis the two weights' derivatives are -g and g, g =
+// 1 - cos(2 pi xi) (the G- cosine is minus the G+ one), so the gradient's sums are separable
+// as the weights' are.
+template <int kMode = G2P_MLS>
 __device__ __forceinline__ int g2p_particle(const DevCtx &d, const PartArgs &pa, float dt, const G2PIn &q,
                                             const CellCoord &cc, int bx, int by, int bz, const float *vt, uint32_t out,
                                             bool write_tau, NewState &ns, CellCoord &cn, bool &placed,
@@ -1185,8 +1218,14 @@ __device__ __forceinline__ int g2p_particle(const DevCtx &d, const PartArgs &pa,
     const DevMaterial M = material_of(d, q.mat);
     Weights w;
     axis_weights(cc, w);
-    float Di[9];
-    moment_inverse(cc, w, Di);
+    float Di[9], cp[3], Gs[9];
+    if (kMode == G2P_MLS) moment_inverse(cc, w, Di);
+    if (kMode == G2P_GRAD) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) cp[a] = __builtin_amdgcn_cosf(cc.xp[a]);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) Gs[i] = 0.0f;
+    }
     // Gather.  The affine matrix sums w v~ (x_i - x_p)^T, whose weights have a
     // zero dual-grid first moment; subtracting one stencil node's velocity c
     // first keeps the FP32 sums at the size of the velocity differences, and c
@@ -1201,17 +1240,18 @@ __device__ __forceinline__ int g2p_particle(const DevCtx &d, const PartArgs &pa,
     float Bh[9];
 #pragma unroll
     for (int i = 0; i < 9; ++i) Bh[i] = 0.0f;
+    // separable sums over the 2x2x2 nodes of each grid: S = sum w v, M_b = sum w v o_b, and
+    // sum_o w v (o - xi)^T = M - S xi^T
 #pragma unroll
-    for (int g = 0; g < 2; ++g) {
-        const float *xi = g == 0 ? cc.xm : cc.xp;
-        const int t0 = g == 0 ? tm0 : tp0;
-        const int sy = g == 0 ? 5 : 6, sz = g == 0 ? 25 : 36;
-        const float(*wa)[2] = g == 0 ? w.wm : w.wp;
-        // separable sums over the 2x2x2 nodes: S = sum w v, M_b = sum w v o_b
-        float S3[3], Mx[3], My[3], Mz[3];
+    for (int a = 0; a < 3; ++a) {
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
+        for (int g = 0; g < 2; ++g) {
+            const float *xi = g == 0 ? cc.xm : cc.xp;
+            const int t0 = g == 0 ? tm0 : tp0;
+            const int sy = g == 0 ? 5 : 6, sz = g == 0 ? 25 : 36;
+            const float(*wa)[2] = g == 0 ? w.wm : w.wp;
             float A[2][2], X[2][2];   // [oz][oy]: x-reduced sum and x-moment
+            float D[2][2];            // and x-difference (gradient)
 #pragma unroll
             for (int oz = 0; oz < 2; ++oz)
 #pragma unroll
@@ -1220,6 +1260,7 @@ __device__ __forceinline__ int g2p_particle(const DevCtx &d, const PartArgs &pa,
                     const float v0 = vt[t] - cref[a], v1 = vt[t + 1] - cref[a];
                     X[oz][oy] = wa[0][1] * v1;
                     A[oz][oy] = wa[0][0] * v0 + X[oz][oy];
+                    if (kMode == G2P_GRAD) D[oz][oy] = v1 - v0;
                 }
             float Bz[2], BXz[2], BYz[2];
 #pragma unroll
@@ -1228,18 +1269,22 @@ __device__ __forceinline__ int g2p_particle(const DevCtx &d, const PartArgs &pa,
                 Bz[oz] = wa[1][0] * A[oz][0] + BYz[oz];
                 BXz[oz] = wa[1][0] * X[oz][0] + wa[1][1] * X[oz][1];
             }
-            Mz[a] = wa[2][1] * Bz[1];
-            S3[a] = wa[2][0] * Bz[0] + Mz[a];
-            Mx[a] = wa[2][0] * BXz[0] + wa[2][1] * BXz[1];
-            My[a] = wa[2][0] * BYz[0] + wa[2][1] * BYz[1];
-        }
-        // sum_o w v (o - xi)^T = M - S xi^T
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            vs[a] += S3[a];
-            Bh[3 * a] += Mx[a] - S3[a] * xi[0];
-            Bh[3 * a + 1] += My[a] - S3[a] * xi[1];
-            Bh[3 * a + 2] += Mz[a] - S3[a] * xi[2];
+            const float Mz = wa[2][1] * Bz[1];
+            const float S3 = wa[2][0] * Bz[0] + Mz;
+            const float Mx = wa[2][0] * BXz[0] + wa[2][1] * BXz[1];
+            const float My = wa[2][0] * BYz[0] + wa[2][1] * BYz[1];
+            if (kMode == G2P_GRAD) {
+                const float gx = g == 0 ? 1.0f + cp[0] : 1.0f - cp[0], gy = g == 0 ? 1.0f + cp[1] : 1.0f - cp[1],
+                            gz = g == 0 ? 1.0f + cp[2] : 1.0f - cp[2];
+                Gs[3 * a] += gx * (wa[2][0] * (wa[1][0] * D[0][0] + wa[1][1] * D[0][1]) +
+                                   wa[2][1] * (wa[1][0] * D[1][0] + wa[1][1] * D[1][1]));
+                Gs[3 * a + 1] += gy * (wa[2][0] * (A[0][1] - A[0][0]) + wa[2][1] * (A[1][1] - A[1][0]));
+                Gs[3 * a + 2] += gz * (Bz[1] - Bz[0]);
+            }
+            vs[a] += S3;
+            Bh[3 * a] += Mx - S3 * xi[0];
+            Bh[3 * a + 1] += My - S3 * xi[1];
+            Bh[3 * a + 2] += Mz - S3 * xi[2];
         }
     }
     float vn[3];
@@ -1247,6 +1292,18 @@ __device__ __forceinline__ int g2p_particle(const DevCtx &d, const PartArgs &pa,
     for (int a = 0; a < 3; ++a) vn[a] = cref[a] + 0.5f * vs[a];
 #pragma unroll
     for (int i = 0; i < 9; ++i) Bh[i] *= 0.5f;
+    if (kMode == G2P_GRAD) {
+        const bool pic = d.transfer == 2;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            Bh[i] = pic ? 0.0f : Bh[i];
+            Gs[i] *= 0.5f;
+            // held back to its stores, B's sums would keep the gathered velocities live through
+            // the return mapping (205 VGPRs and two waves per SIMD in place of 158 and three)
+            asm volatile("" : "+v"(Bh[i]));
+        }
+        return g2p_finish_c(d, pa, dt, q, M, vn, Bh, Gs, out, write_tau, ns, cn, placed, write_vB, carry);
+    }
     return g2p_finish(d, pa, dt, q, M, vn, Bh, Di, out, write_tau, ns, cn, placed, write_vB, carry);
 }
 
@@ -1257,7 +1314,7 @@ __device__ __forceinline__ int g2p_particle(const DevCtx &d, const PartArgs &pa,
 __device__ __forceinline__ int g2p_finish_c(const DevCtx &d, const PartArgs &pa, float dt, const G2PIn &q,
                                             const DevMaterial &M, const float (&vn)[3], const float (&Bh)[9],
                                             const float (&Cc)[9], uint32_t out, bool write_tau, NewState &ns,
-                                            CellCoord &cn, bool &placed, bool write_vB = true, bool carry = false) {
+                                            CellCoord &cn, bool &placed, bool write_vB, bool carry) {
     const long long S = pa.stride;
     int sig = -1;
     placed = false;
@@ -1391,501 +1448,6 @@ __device__ __forceinline__ int g2p_finish(const DevCtx &d, const PartArgs &pa, f
 // column; the quadratic and gradient G2P gain 9 %).
 constexpr int kG2PThreads = 128;
 
-// Workgroups per particle block, as a shift: 1, 2 or 4 of them, each taking every 2nd or
-// 4th pass of the block's particles and gathering the tile for itself.  A block of 512
-// particles is four passes one after the other, each bound by its chain of dependent
-// instructions; while the blocks leave workgroup slots of the GPU empty (256 CUs of six
-// 128-thread workgroups), the passes run side by side.  The lines: four workgroups up to
-// one round of the slots, two up to 10 workgroups per CU.  Measured (us per mpm_step step
-// at 124 / 343 / 576 / 897 / 1728 blocks of moving sand): one workgroup 66 / 74 / 77 / 86 /
-// 125, two - / - / 68.4 / 84.2 / 132, four 54 / 61 / 69.8 / - / -; G2P alone at 125 blocks
-// 23.4 -> 13.9 us.
-__device__ __forceinline__ int g2p_split(int np) { return np <= 256 * 6 / 4 ? 2 : np <= 256 * 10 / 2 ? 1 : 0; }
-
-// One pass of the G2P particle loop over particles j0 + thread of a block: `cur` holds
-// the particle's inputs (loaded a pass before); `nxt` loads those of the next pass from
-// the index pnext (loaded a pass before), and pnext the index after that.  Lanes past
-// the end load the block's last particle again: loads on every path let the first
-// use of a particle's inputs wait for that particle's loads alone.
-template <bool kCarry, bool kCarried>
-__device__ __forceinline__ void g2p_pass(const DevCtx &d, const PartArgs &pa, float dt, const float *vt, int bx,
-                                         int by, int bz, int s, int cnt, uint32_t last, int j0, int step, int E,
-                                         G2PIn &cur, G2PIn &nxt, uint32_t &pnext, int &stay) {
-    const int j = j0 + (int)threadIdx.x;
-    const bool act = j < cnt;
-    if (kCarried) unpack_remainder(d.geo, cur.rp, cur.xr);
-    const uint32_t pn = pnext;   // the index first, then the next particle's inputs
-    pnext = ld_at(d.perm, min((uint32_t)(s + j + 2 * step), last));
-    g2p_load_index(pa, pn, nxt, kCarried);
-    const uint32_t out = (uint32_t)(s + j);
-    CellCoord cc;
-    bool ok = act && cell_coord(d.geo, cur.x, cur.xr, cc);
-    ok = ok && (cc.c[0] >> 2) == bx && (cc.c[1] >> 2) == by && (cc.c[2] >> 2) == bz;
-    // the particle's block in the next step (-1: none)
-    int sig = -1;
-    CellCoord cn = {};
-    const int own = vblock_id(d.geo, bx, by, bz);
-    // blocks whose particle set or bins change: this one when a particle leaves it or
-    // its (octant, cell) bin, and the one it enters
-    bool changed = false;
-    if (act && !ok) {
-        set_status(d.counters, ST_STALE);
-        st_at(d.key, out, 0xffffffffu);
-        changed = true;
-    } else if (ok) {
-        NewState ns;
-        bool placed;
-        sig = g2p_particle(d, pa, dt, cur, cc, bx, by, bz, vt, out, true, ns, cn, placed, true, kCarry);
-        if (!placed) {
-            changed = true;
-        } else if (sig != own || sub_code(cn) != sub_code(cc)) {
-            changed = true;
-            d.bchg[sig] = E + 1;
-        }
-    }
-    if (__any(changed)) {
-        if (changed) d.bchg[own] = E + 1;
-    }
-    // those that stay are counted for the whole block at its end, the others at once
-    stay += __popcll(__ballot(sig == own));
-    const bool left = sig >= 0 && sig != own;
-    if (__any(left)) wave_stamp(d, left, cn.c[0] >> 2, cn.c[1] >> 2, cn.c[2] >> 2, E + 1);
-}
-
-// Gathers the velocity tile of block (bx,by,bz) (kTileNodes nodes, three channels) by
-// the workgroup's threads; nodes outside active blocks are at rest.  The loads of all of
-// a thread's nodes are issued before any is used: one memory round trip for the tile.
-// kFold: the pool still holds the P2G's momenta, and the grid update is applied to each
-// node as it is gathered.  A node is gathered by 2.7 blocks on average in the interior of
-// a body, but that costs less than the update's own pass over the grid and its launch:
-// sand column, update 11 us + G2P 213.7 us -> G2P 221.5 us; 1,000 particles, a step
-// 47.2 -> 45.1 us; 262,144 particles in deterministic mode, 109 -> 104 us.
-template <bool kFold>
-__device__ __forceinline__ void gather_tile(const DevCtx &d, float dt, int gp, const int *nbr, int bx, int by, int bz,
-                                            float *vt) {
-    constexpr int kPer = (kTileNodes + kG2PThreads - 1) / kG2PThreads;
-    const float *pool = pool_of(d, gp);
-    float m[kPer], p[kPer][3];
-    TileNode q[kPer];
-    int ph[kPer];
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        q[k] = tile_entry(kTile.e[min((int)threadIdx.x + k * kG2PThreads, kTileNodes - 1)]);
-        ph[k] = nbr[q[k].nb];
-    }
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const float *a = pool + (size_t)max(ph[k], 0) * kBlockFloats + q[k].at;
-        if (kFold) m[k] = a[0];
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) p[k][ch] = a[(1 + ch) * 64];
-    }
-    // (uniform) no node of the tile lies on a wall
-    const bool inner = kFold && 4 * min(bx, min(by, bz)) - 1 >= max(d.geo.stick_lo[0], d.geo.stick_lo[1]) &&
-                       4 * bx + 4 <= min(d.geo.stick_hi[0][0], d.geo.stick_hi[1][0]) &&
-                       4 * by + 4 <= min(d.geo.stick_hi[0][1], d.geo.stick_hi[1][1]) &&
-                       4 * bz + 4 <= min(d.geo.stick_hi[0][2], d.geo.stick_hi[1][2]);
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        float v[3];
-        if (kFold) {
-            const float mk = ph[k] >= 0 ? m[k] : 0.0f;
-            if (inner) {
-                const float im = fast_rcp(mk);
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch) v[ch] = mk > 0.0f ? p[k][ch] * im + dt * d.gravity[ch] : 0.0f;
-            } else {
-                const int nb = q[k].nb, l = q[k].at & 63;
-                node_velocity(d, dt, q[k].g, 4 * (bx + nb % 3 - 1) + (l & 3), 4 * (by + nb / 3 % 3 - 1) + ((l >> 2) & 3),
-                              4 * (bz + nb / 9 - 1) + (l >> 4), mk, p[k][0], p[k][1], p[k][2], v);
-            }
-        } else {
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) v[ch] = ph[k] >= 0 ? p[k][ch] : 0.0f;
-        }
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) vt[ch * kTileNodes + q[k].ni] = v[ch];
-    }
-}
-
-// kCarry: the output is the carried state for the next P2G of the same step sequence
-// (Q in the B planes, the packed remainder); kCarried: so is the input.  The particle
-// loop runs two passes per trip, each reading the inputs the other loaded: the two
-// sets of registers then take turns, where one set copied into the other at the end
-// of every pass would wait for every store of the pass.  kKept: the step's P2G was
-// b_p2g, which kept every block's neighbourhood (one load, not a page lookup that
-// waits for the block's id).
-template <bool kCarry = false, bool kCarried = false, bool kKept = false, bool kFold = false>
-__device__ __forceinline__ void b_g2p(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt) {
-    __shared__ float vt[3 * kTileNodes];
-    __shared__ int nbr[27];
-    const int np = (int)d.counters[C_NPB];
-    const int E = (int)d.counters[C_EPOCH];
-    const int tid = threadIdx.x;
-    const int sh = g2p_split(np), step = kG2PThreads << sh;
-    for (int base = 0; base < np << sh; base += gridDim.x) {
-        const int u = round_block(base, np << sh);
-        if (u < 0) continue;
-        const int r = u >> sh, first = (u & ((1 << sh) - 1)) * kG2PThreads;
-        const int vb = d.plist[r];
-        int bx, by, bz;
-        block_coords(d.geo, vb, bx, by, bz);
-        const int s = d.pstart[r];
-        const int cnt = d.pstart[r + 1] - s;
-        if (tid == 0 && first == 0) block_counts(d, E)[vb] = 0;   // the step's last use of them
-        if (cnt <= first || cnt > kMaxBlockParticles) continue;
-        // the first particle's inputs load while the tile is gathered, and the index of
-        // the one after
-        const uint32_t last = (uint32_t)(s + cnt - 1);
-        G2PIn qa, qb;
-        g2p_load_index(pa, ld_at(d.perm, min((uint32_t)(s + first + tid), last)), qa, kCarried);
-        uint32_t pnext = ld_at(d.perm, min((uint32_t)(s + first + tid + step), last));
-        if (kKept) {
-            if (tid < 27) nbr[tid] = d.nbrs[27 * (size_t)r + tid];
-        } else {
-            load_neighbours(d, gt, bx, by, bz, nbr);
-        }
-        lds_barrier();
-        gather_tile<kFold>(d, dt, gp, nbr, bx, by, bz, vt);
-        lds_barrier();
-        int stay = 0;   // the wave's particles that stay in the block
-        for (int j0 = first; j0 < cnt; j0 += 2 * step) {   // the same trip count for every lane
-            g2p_pass<kCarry, kCarried>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0, step, E, qa, qb, pnext, stay);
-            if (j0 + step < cnt)
-                g2p_pass<kCarry, kCarried>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0 + step, step, E, qb, qa, pnext,
-                                           stay);
-        }
-        if (stay > 0) stamp_block(d, bx, by, bz, stay, E + 1);
-        lds_barrier();
-    }
-}
-
-__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p(DevCtx d, PartArgs pa, float dt, int gp, int gt) { b_g2p(d, pa, dt, gp, gt); }
-// The forms inside an mpm_step sequence, whose P2G (b_p2g) kept every block's
-// neighbourhood; every one but the last step's folds the grid update into its gather.
-__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_fold(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
-    b_g2p<false, false, true, true>(d, pa, dt, gp, gt);
-}
-__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_carry(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
-    b_g2p<true, false, true, true>(d, pa, dt, gp, gt);
-}
-__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_cc(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
-    b_g2p<true, true, true, true>(d, pa, dt, gp, gt);
-}
-__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_cf(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
-    b_g2p<false, true, true>(d, pa, dt, gp, gt);
-}
-
-// one launch for many jobs: workgroup row y runs job y (every job's P2G of the round,
-// plain or deterministic, was b_p2g, which kept the neighbourhoods; nobody reads the
-// grid of a served job, so its update is folded into the gather)
-__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_multi(const JobStep *__restrict__ jobs) {
-    const JobStep &J = jobs[blockIdx.y];
-    b_g2p<false, false, true, true>(J.d, J.pa, J.dt, J.table, J.table);
-}
-
-// ---------------------------------------------------------------- exact-gradient transfers
-// APIC (section 4.4) and PIC (section 4.3) on the two staggered grids: the stress
-// force uses the exact kernel gradient, f_i = -sum_p V0 tau grad w_ip, and G2P takes
-// the velocity gradient as 1/2 sum_k sum_i v~_i grad w^T; APIC keeps the affine
-// momentum m B D^-1 (x_i - x_p) and carries B, PIC transfers m v alone and carries no
-// B.  Per axis on grid k with fraction xi the two weights 1 - xi + s, xi - s have
-// x_p-derivatives (cos(2 pi xi) - 1)/dx and (1 - cos(2 pi xi))/dx, and the G- cosine
-// is minus the G+ one (the fractions differ by half a cell).
-struct GStaged {
-    float xm[3], sp[3], cp[3];   // G- fraction, G+ sine and cosine per axis
-    float mass, base[3], Q[9];   // affine part as in the MLS staging (Q = 0 for PIC)
-    float T[9];                  // -dt V0 tau / dx: force per unit weight gradient (cell units)
-    int c[3], oct;
-    bool on;
-};
-
-__device__ __forceinline__ void grad_stage(const DevCtx &d, const PartArgs &pa, int p, int bx, int by, int bz,
-                                           float dt, bool pic, GStaged &r) {
-    r.on = false;
-    const long long S = pa.stride;
-    const uint32_t up = (uint32_t)p;
-    float x[3], xr[3], v[3], B[9], tau[6];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) x[a] = ld_at(pa.in + a * S, up);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) xr[a] = ld_at(pa.in + (kPlaneR + a) * S, up);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) v[a] = ld_at(pa.in + (3 + a) * S, up);
-#pragma unroll
-    for (int a = 0; a < 9; ++a) B[a] = pic ? 0.0f : ld_at(pa.in + (6 + a) * S, up);
-#pragma unroll
-    for (int i = 0; i < 6; ++i) tau[i] = ld_at(d.tau + i * d.tau_stride, up);
-    const int mi = pa.mat_in ? (int)ld_at(pa.mat_in, up) : 0;
-    const DevMaterial M = material_of(d, mi);
-    CellCoord cc;
-    if (!cell_coord(d.geo, x, xr, cc)) {
-        set_status(d.counters, ST_DOMAIN);
-        return;
-    }
-    if ((cc.c[0] >> 2) != bx || (cc.c[1] >> 2) != by || (cc.c[2] >> 2) != bz) {
-        set_status(d.counters, ST_STALE);
-        return;
-    }
-    r.oct = (int)(sub_code(cc) & 7u);
-    Weights w;
-    axis_weights(cc, w);
-    float Di[9];
-    moment_inverse(cc, w, Di);
-    const float sc = d.geo.inv_dx_f;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            r.Q[3 * i + j] = sc * M.mass * (B[3 * i] * Di[j] + B[3 * i + 1] * Di[3 + j] + B[3 * i + 2] * Di[6 + j]);
-    const float Tf[9] = {tau[0], tau[3], tau[4], tau[3], tau[1], tau[5], tau[4], tau[5], tau[2]};
-    const float k = -dt * M.vol0 * sc;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) r.T[i] = k * Tf[i];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        r.c[a] = cc.c[a];
-        r.xm[a] = cc.xm[a];
-        r.sp[a] = w.sp[a];
-        r.cp[a] = __builtin_amdgcn_cosf(cc.xp[a]);
-        r.base[a] = M.mass * v[a] - (r.Q[3 * a] * cc.xm[0] + r.Q[3 * a + 1] * cc.xm[1] + r.Q[3 * a + 2] * cc.xm[2]);
-    }
-    r.mass = M.mass;
-    r.on = true;
-}
-
-__device__ __forceinline__ float grad_bound(const GStaged &r) {
-    if (!r.on) return 0.0f;
-    float b = r.mass;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-        b = fmaxf(b, fabsf(r.base[a]) + 1.5f * (fabsf(r.Q[3 * a]) + fabsf(r.Q[3 * a + 1]) + fabsf(r.Q[3 * a + 2])) +
-                         2.0f * (fabsf(r.T[3 * a]) + fabsf(r.T[3 * a + 1]) + fabsf(r.T[3 * a + 2])));
-    return b;
-}
-
-// Per-axis weights and x_p-derivatives (cell units) of both grids, the G+ base offset
-// and the affine momentum at each grid's base node.
-__device__ __forceinline__ void grad_axes(const GStaged &r, float (&w)[2][3][2], float (&dw)[2][3][2], int (&up)[3],
-                                          float (&m0)[2][3]) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        up[a] = (r.oct >> a) & 1;
-        const float xp = up[a] ? r.xm[a] - 0.5f : r.xm[a] + 0.5f;
-        w[0][a][0] = 1.0f - r.xm[a] - r.sp[a];
-        w[0][a][1] = r.xm[a] + r.sp[a];
-        w[1][a][0] = 1.0f - xp + r.sp[a];
-        w[1][a][1] = xp - r.sp[a];
-        dw[1][a][0] = r.cp[a] - 1.0f;
-        dw[1][a][1] = 1.0f - r.cp[a];
-        dw[0][a][0] = -r.cp[a] - 1.0f;
-        dw[0][a][1] = 1.0f + r.cp[a];
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        m0[0][a] = r.base[a];
-        m0[1][a] = r.base[a] + ((float)up[0] - 0.5f) * r.Q[3 * a] + ((float)up[1] - 0.5f) * r.Q[3 * a + 1] +
-                   ((float)up[2] - 0.5f) * r.Q[3 * a + 2];
-    }
-}
-
-// Adds the particle's 16 contributions to the fixed-point tile (layout of k_p2g's).
-__device__ __forceinline__ void grad_scatter(const GStaged &r, int lx, int ly, int lz, unsigned long long *tile_m,
-                                             unsigned long long *tile_p, double S) {
-    float w[2][3][2], dw[2][3][2], m0[2][3];
-    int up[3];
-    grad_axes(r, w, dw, up, m0);
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-        unsigned long long *tile = g == 0 ? tile_m : tile_p;
-        const int ntile = g == 0 ? kTileMStride : kTilePStride;
-        const int t0 = g == 0 ? lz * kTZ + ly * kTY + lx : (lz + up[2]) * kTZ + (ly + up[1]) * kTY + (lx + up[0]);
-#pragma unroll
-        for (int o = 0; o < 8; ++o) {
-            const int ox = o & 1, oy = (o >> 1) & 1, oz = o >> 2;
-            const float wx = w[g][0][ox], wy = w[g][1][oy], wz = w[g][2][oz];
-            const float wt = wx * wy * wz;
-            const float gx = dw[g][0][ox] * wy * wz, gy = wx * dw[g][1][oy] * wz, gz = wx * wy * dw[g][2][oz];
-            const int t = t0 + ox + oy * kTY + oz * kTZ;
-            atomicAdd(&tile[t], to_fixed(wt * r.mass, S));
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const float mom = wt * (m0[g][a] + ox * r.Q[3 * a] + oy * r.Q[3 * a + 1] + oz * r.Q[3 * a + 2]) +
-                                  r.T[3 * a] * gx + r.T[3 * a + 1] * gy + r.T[3 * a + 2] * gz;
-                atomicAdd(&tile[(1 + a) * ntile + t], to_fixed(mom, S));
-            }
-        }
-    }
-}
-
-__global__ void __launch_bounds__(kP2GThreads) k_p2g_grad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
-    __shared__ int bcnt[kBins];
-    __shared__ int bstart[kBins + 1];
-    __shared__ int wsum[kP2GThreads / 64];
-    __shared__ unsigned int bmax;
-    __shared__ int nbr[27];
-    __shared__ uint32_t ord[kMaxBlockParticles];
-    constexpr int kTileWords = 4 * (kTileMStride + kTilePStride);
-    constexpr int kAreaWords = kTileWords > kOrderWords ? kTileWords : kOrderWords;
-    __shared__ unsigned long long area[kAreaWords];
-    __shared__ int lay[kLayWords];
-    __shared__ unsigned long long lmask[kLayMaskWords];
-    uint32_t *lbuf = reinterpret_cast<uint32_t *>(area);
-    unsigned long long *tile_m = area;
-    unsigned long long *tile_p = area + 4 * kTileMStride;
-    const bool pic = d.transfer == 2;
-    const int np = (int)d.counters[C_NPB];
-    const int tid = threadIdx.x;
-    for (int base = 0; base < np; base += gridDim.x) {
-        const int r = round_block(base, np);
-        if (r < 0) continue;
-        const int vb = d.plist[r];
-        int bx, by, bz;
-        block_coords(d.geo, vb, bx, by, bz);
-        const int s = d.pstart[r];
-        const int cnt = d.pstart[r + 1] - s;
-        if (cnt > kMaxBlockParticles) continue;
-        if (!bucket_full(d, r, cnt)) continue;
-        order_block<true>(d, r, s, cnt, bcnt, bstart, wsum, lbuf, ord, lay, lmask);
-        load_neighbours(d, gt, bx, by, bz, nbr);
-        lds_barrier();
-        for (int c0 = 0; c0 < cnt; c0 += kChunk) {
-            for (int q = tid; q < kTileWords; q += kP2GThreads) area[q] = 0ull;
-            if (tid == 0) bmax = 0u;
-            GStaged st[2];
-            float bnd = 0.0f;
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                st[k].on = false;
-                const int j = c0 + tid + k * kP2GThreads;
-                if (j < cnt) grad_stage(d, pa, (int)ord[j], bx, by, bz, dt, pic, st[k]);
-                bnd = fmaxf(bnd, grad_bound(st[k]));
-            }
-            lds_barrier();
-            const double S = block_scale(bnd, &bmax);
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-                if (st[k].on)
-                    grad_scatter(st[k], st[k].c[0] - 4 * bx, st[k].c[1] - 4 * by, st[k].c[2] - 4 * bz, tile_m, tile_p, S);
-            lds_barrier();
-            flush_tile(d, pool_of(d, gp), nbr, tile_m, tile_p, 1.0 / S);
-            lds_barrier();
-        }
-    }
-}
-
-// G2P with the exact velocity gradient: v = 1/2 sum w v~, B = 1/2 sum w v~ d^T (APIC;
-// zero for PIC), C = 1/2 sum v~ grad w^T, all relative to the velocity of one stencil
-// node (the weights of a grid sum to one, their gradients to zero).
-__global__ void __launch_bounds__(kG2PThreads) k_g2p_grad(DevCtx d, PartArgs pa, float dt, int gp, int gt,
-                                                          int fold) {
-    __shared__ float vt[3 * kTileNodes];
-    __shared__ int nbr[27];
-    const bool pic = d.transfer == 2;
-    const int np = (int)d.counters[C_NPB];
-    const int E = (int)d.counters[C_EPOCH];
-    const int tid = threadIdx.x;
-    for (int base = 0; base < np; base += gridDim.x) {
-        const int r = round_block(base, np);
-        if (r < 0) continue;
-        const int vb = d.plist[r];
-        int bx, by, bz;
-        block_coords(d.geo, vb, bx, by, bz);
-        const int s = d.pstart[r];
-        const int cnt = d.pstart[r + 1] - s;
-        if (tid == 0) block_counts(d, E)[vb] = 0;   // the step's last use of them
-        if (cnt > kMaxBlockParticles) continue;
-        G2PIn nxt;
-        if (tid < cnt) g2p_load(d, pa, (uint32_t)(s + tid), nxt);
-        load_neighbours(d, gt, bx, by, bz, nbr);
-        lds_barrier();
-        if (fold) gather_tile<true>(d, dt, gp, nbr, bx, by, bz, vt);
-        else gather_tile<false>(d, dt, gp, nbr, bx, by, bz, vt);
-        lds_barrier();
-        for (int j0 = 0; j0 < cnt; j0 += kG2PThreads) {
-            const int j = j0 + tid;
-            const bool act = j < cnt;
-            const G2PIn q = nxt;
-            if (j + kG2PThreads < cnt) g2p_load(d, pa, (uint32_t)(s + j + kG2PThreads), nxt);
-            const uint32_t out = (uint32_t)(s + j);
-            CellCoord cc;
-            bool ok = act && cell_coord(d.geo, q.x, q.xr, cc);
-            ok = ok && (cc.c[0] >> 2) == bx && (cc.c[1] >> 2) == by && (cc.c[2] >> 2) == bz;
-            int sig = -1;
-            CellCoord cn = {};
-            if (act && !ok) {
-                set_status(d.counters, ST_STALE);
-                st_at(d.key, out, 0xffffffffu);
-            } else if (ok) {
-                Weights wt;
-                axis_weights(cc, wt);
-                float cp[3];
-#pragma unroll
-                for (int a = 0; a < 3; ++a) cp[a] = __builtin_amdgcn_cosf(cc.xp[a]);
-                const int tm0 = ((cc.c[2] - 4 * bz) * 5 + (cc.c[1] - 4 * by)) * 5 + (cc.c[0] - 4 * bx);
-                const int tp0 = kTileMinus + ((cc.bp[2] - 4 * bz + 1) * 6 + (cc.bp[1] - 4 * by + 1)) * 6 +
-                                (cc.bp[0] - 4 * bx + 1);
-                const float cref[3] = {vt[tm0], vt[kTileNodes + tm0], vt[2 * kTileNodes + tm0]};
-                float vs[3] = {0.0f, 0.0f, 0.0f}, Bh[9], Cc[9];
-#pragma unroll
-                for (int i = 0; i < 9; ++i) {
-                    Bh[i] = 0.0f;
-                    Cc[i] = 0.0f;
-                }
-#pragma unroll
-                for (int g = 0; g < 2; ++g) {
-                    const float *xi = g == 0 ? cc.xm : cc.xp;
-                    const int t0 = g == 0 ? tm0 : tp0;
-                    const int sy = g == 0 ? 5 : 6, sz = g == 0 ? 25 : 36;
-                    const float(*wa)[2] = g == 0 ? wt.wm : wt.wp;
-#pragma unroll
-                    for (int o = 0; o < 8; ++o) {
-                        const int ox = o & 1, oy = (o >> 1) & 1, oz = o >> 2;
-                        const int off[3] = {ox, oy, oz};
-                        float wv = 1.0f, gd[3];
-                        float wa3[3], dwa3[3];
-#pragma unroll
-                        for (int a = 0; a < 3; ++a) {
-                            wa3[a] = wa[a][off[a]];
-                            const float c = g == 0 ? -cp[a] : cp[a];
-                            dwa3[a] = off[a] ? 1.0f - c : c - 1.0f;
-                            wv *= wa3[a];
-                        }
-                        gd[0] = dwa3[0] * wa3[1] * wa3[2];
-                        gd[1] = wa3[0] * dwa3[1] * wa3[2];
-                        gd[2] = wa3[0] * wa3[1] * dwa3[2];
-                        const int t = t0 + ox + oy * sy + oz * sz;
-#pragma unroll
-                        for (int a = 0; a < 3; ++a) {
-                            const float dv = vt[a * kTileNodes + t] - cref[a];
-                            vs[a] += wv * dv;
-#pragma unroll
-                            for (int b = 0; b < 3; ++b) {
-                                Bh[3 * a + b] += wv * dv * ((float)off[b] - xi[b]);
-                                Cc[3 * a + b] += dv * gd[b];
-                            }
-                        }
-                    }
-                }
-                float vn[3];
-#pragma unroll
-                for (int a = 0; a < 3; ++a) vn[a] = cref[a] + 0.5f * vs[a];
-#pragma unroll
-                for (int i = 0; i < 9; ++i) {
-                    Bh[i] = pic ? 0.0f : 0.5f * Bh[i];
-                    Cc[i] *= 0.5f;
-                }
-                const DevMaterial M = material_of(d, q.mat);
-                NewState ns;
-                bool placed;
-                sig = g2p_finish_c(d, pa, dt, q, M, vn, Bh, Cc, out, true, ns, cn, placed);
-            }
-            wave_stamp(d, sig >= 0, cn.c[0] >> 2, cn.c[1] >> 2, cn.c[2] >> 2, E + 1);
-        }
-        lds_barrier();
-    }
-}
-
 // ---------------------------------------------------------------- quadratic B-spline
 // The single-grid quadratic B-spline kernel the paper measures the compact kernel
 // against (section 6).  Node i sits at origin + i dx; a particle at X (cells) reaches
@@ -2001,168 +1563,569 @@ __device__ __forceinline__ void quad_scatter(const QStaged &r, unsigned long lon
         }
 }
 
-__global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_quad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
-    __shared__ int bcnt[kBins];
-    __shared__ int bstart[kBins + 1];
-    __shared__ int wsum[kP2GThreads / 64];
-    __shared__ unsigned int bmax;
-    __shared__ int nbr[27];
-    __shared__ uint32_t ord[kMaxBlockParticles];
-    constexpr int kTileWords = 4 * kQStride;
-    constexpr int kAreaWords = kTileWords > kOrderWords ? kTileWords : kOrderWords;
-    __shared__ unsigned long long area[kAreaWords];
-    __shared__ int lay[kLayWords];
-    __shared__ unsigned long long lmask[kLayMaskWords];
-    uint32_t *lbuf = reinterpret_cast<uint32_t *>(area);
-    unsigned long long *tile = area;
-    const int np = (int)d.counters[C_NPB];
-    const int tid = threadIdx.x;
-    for (int base = 0; base < np; base += gridDim.x) {
-        const int r = round_block(base, np);
-        if (r < 0) continue;
-        const int vb = d.plist[r];
-        int bx, by, bz;
-        block_coords(d.geo, vb, bx, by, bz);
-        const int s = d.pstart[r];
-        const int cnt = d.pstart[r + 1] - s;
-        if (cnt > kMaxBlockParticles) continue;   // reported by the compaction
-        if (!bucket_full(d, r, cnt)) continue;
-        order_block<true>(d, r, s, cnt, bcnt, bstart, wsum, lbuf, ord, lay, lmask);
-        load_neighbours(d, gt, bx, by, bz, nbr);
-        lds_barrier();
-        for (int c0 = 0; c0 < cnt; c0 += kChunk) {
-            for (int q = tid; q < kTileWords; q += kP2GThreads) area[q] = 0ull;
-            if (tid == 0) bmax = 0u;
-            QStaged st[2];
-            float bnd = 0.0f;
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                st[k].on = false;
-                const int j = c0 + tid + k * kP2GThreads;
-                if (j < cnt) quad_stage(d, pa, (int)ord[j], bx, by, bz, dt, st[k]);
-                bnd = fmaxf(bnd, quad_bound(st[k]));
-            }
-            lds_barrier();   // tile cleared, bmax reset
-            const double S = block_scale(bnd, &bmax);
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-                if (st[k].on) quad_scatter(st[k], tile, S);
-            lds_barrier();
-            const double inv = 1.0 / S;
-            for (int ni = tid; ni < kQNodes; ni += kP2GThreads) {
-                const int lx = ni % 7, ly = (ni / 7) % 7, lz = ni / 49;
-                const int t = lx + ly * kQTY + lz * kQTZ;
-                float val[4];
-#pragma unroll
-                for (int ch = 0; ch < 4; ++ch) val[ch] = (float)((double)(long long)tile[ch * kQStride + t] * inv);
-                if (val[0] == 0.0f && val[1] == 0.0f && val[2] == 0.0f && val[3] == 0.0f) continue;
-                const int ix = 4 * bx - 1 + lx, iy = 4 * by - 1 + ly, iz = 4 * bz - 1 + lz;
-                const long long a = pool_index(d, nbr, bx, by, bz, 0, ix, iy, iz, 0);
+// Straight into the pool, for a particle above the step's contribution bound.
+__device__ __forceinline__ void quad_pool(const DevCtx &d, float *pool, const int *nbr, int bx, int by, int bz,
+                                          const QStaged &r) {
+    float w[3][3];
+    quad_weights(r.xi, w);
+    for (int oz = 0; oz < 3; ++oz)
+        for (int oy = 0; oy < 3; ++oy)
+            for (int ox = 0; ox < 3; ++ox) {
+                const float wt = (ox == 0 ? w[0][0] : ox == 1 ? w[0][1] : w[0][2]) *
+                                 (oy == 0 ? w[1][0] : oy == 1 ? w[1][1] : w[1][2]) *
+                                 (oz == 0 ? w[2][0] : oz == 1 ? w[2][1] : w[2][2]);
+                const long long a = pool_index(d, nbr, bx, by, bz, 0, 4 * bx - 1 + r.lb[0] + ox,
+                                               4 * by - 1 + r.lb[1] + oy, 4 * bz - 1 + r.lb[2] + oz, 0);
                 if (a < 0) {
                     set_status(d.counters, ST_CAPACITY);
                     continue;
                 }
+                atomicAdd(&pool[a], wt * r.mass);
 #pragma unroll
-                for (int ch = 0; ch < 4; ++ch)
-                    if (val[ch] != 0.0f) atomicAdd(&pool_of(d, gp)[a + ch * 64], val[ch]);
+                for (int c = 0; c < 3; ++c)
+                    atomicAdd(&pool[a + (1 + c) * 64],
+                              wt * (r.mom0[c] + r.Qc[3 * c] * ox + r.Qc[3 * c + 1] * oy + r.Qc[3 * c + 2] * oz));
             }
-            lds_barrier();
+}
+
+struct QuadTransfer {
+    using Particle = QStaged;
+    static constexpr int kTileWords = 4 * kQStride;
+    static __device__ __forceinline__ void stage(const DevCtx &d, const PartArgs &pa, int p, int bx, int by, int bz,
+                                                 float dt, QStaged &st) {
+        quad_stage(d, pa, p, bx, by, bz, dt, st);
+    }
+    static __device__ __forceinline__ float bound(const QStaged &st) { return quad_bound(st); }
+    static __device__ __forceinline__ void scatter(const QStaged &st, int, int, int, unsigned long long *tile, double S) {
+        quad_scatter(st, tile, S);
+    }
+    static __device__ __forceinline__ void direct(const DevCtx &d, float *pool, const int *nbr, int bx, int by, int bz,
+                                                  const QStaged &st) {
+        quad_pool(d, pool, nbr, bx, by, bz, st);
+    }
+    static __device__ __forceinline__ void flush(const DevCtx &d, float *pool, const int *nbr, int bx, int by, int bz,
+                                                 const unsigned long long *tile, double inv) {
+        for (int ni = threadIdx.x; ni < kQNodes; ni += kP2GThreads) {
+            const int lx = ni % 7, ly = (ni / 7) % 7, lz = ni / 49;
+            const int t = lx + ly * kQTY + lz * kQTZ;
+            float val[4];
+#pragma unroll
+            for (int ch = 0; ch < 4; ++ch) val[ch] = (float)((double)(long long)tile[ch * kQStride + t] * inv);
+            if (val[0] == 0.0f && val[1] == 0.0f && val[2] == 0.0f && val[3] == 0.0f) continue;
+            const long long a = pool_index(d, nbr, bx, by, bz, 0, 4 * bx - 1 + lx, 4 * by - 1 + ly, 4 * bz - 1 + lz, 0);
+            if (a < 0) {
+                set_status(d.counters, ST_CAPACITY);
+                continue;
+            }
+#pragma unroll
+            for (int ch = 0; ch < 4; ++ch)
+                if (val[ch] != 0.0f) atomicAdd(&pool[a + ch * 64], val[ch]);
         }
+    }
+};
+
+// The velocity tile of a block's 7^3 nodes, as gather_tile.
+template <bool kFold>
+__device__ __forceinline__ void quad_gather_tile(const DevCtx &d, float dt, int gp, const int *nbr, int bx, int by, int bz,
+                                                 float *vt) {
+    constexpr int kPer = (kQNodes + kG2PThreads - 1) / kG2PThreads;
+    const float *pool = pool_of(d, gp);
+    float m[kPer], p[kPer][3];
+    bool on[kPer];
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));   // the tile coordinates are formed again for every block, not held through it
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int ni = min(t + k * kG2PThreads, kQNodes - 1);
+        const long long a = pool_index(d, nbr, bx, by, bz, 0, 4 * bx - 1 + ni % 7, 4 * by - 1 + (ni / 7) % 7,
+                                       4 * bz - 1 + ni / 49, 0);
+        on[k] = a >= 0;
+        const float *q = pool + (on[k] ? a : 0);
+        if (kFold) m[k] = q[0];
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) p[k][ch] = q[(1 + ch) * 64];
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int ni = min(t + k * kG2PThreads, kQNodes - 1);
+        float v[3] = {p[k][0], p[k][1], p[k][2]};
+        if (kFold)
+            node_velocity(d, dt, 0, 4 * bx - 1 + ni % 7, 4 * by - 1 + (ni / 7) % 7, 4 * bz - 1 + ni / 49,
+                          on[k] ? m[k] : 0.0f, p[k][0], p[k][1], p[k][2], v);
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) vt[ch * kQNodes + ni] = on[k] ? v[ch] : 0.0f;
     }
 }
 
-__global__ void __launch_bounds__(kG2PThreads) k_g2p_quad(DevCtx d, PartArgs pa, float dt, int gp, int gt,
-                                                          int fold) {
-    __shared__ float vt[3 * kQNodes];
+// G2P of one particle: v = sum w v~, Bh = sum w v~ (o - xi)^T, relative to the velocity c
+// of the middle node (the weights sum to one and have zero first moment); the sums over
+// the 3 x 3 x 3 nodes are separable (x, then y, then z sums and first moments).
+__device__ __forceinline__ int quad_particle(const DevCtx &d, const PartArgs &pa, float dt, const G2PIn &q,
+                                             const CellCoord &cc, int bx, int by, int bz, const float *vt, uint32_t out,
+                                             NewState &ns, CellCoord &cn, bool &placed) {
+    placed = false;
+    float xi[3];
+    int lb[3];
+    if (!quad_coords(d.geo, cc, bx, by, bz, xi, lb)) {
+        set_status(d.counters, ST_DOMAIN);
+        st_at(d.key, out, 0xffffffffu);
+        return -1;
+    }
+    float w[3][3];
+    quad_weights(xi, w);
+    const int t0 = lb[0] + lb[1] * 7 + lb[2] * 49;
+    float vn[3], Bh[9];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float *va = vt + a * kQNodes + t0;
+        const float cref = va[57];   // node (1, 1, 1)
+        float S = 0.0f, Mx = 0.0f, My = 0.0f, Mz = 0.0f;
+#pragma unroll
+        for (int oz = 0; oz < 3; ++oz) {
+            float B = 0.0f, BX = 0.0f, BY = 0.0f;
+#pragma unroll
+            for (int oy = 0; oy < 3; ++oy) {
+                const float *vr = va + oy * 7 + oz * 49;
+                const float x1 = w[0][1] * (vr[1] - cref), x2 = w[0][2] * (vr[2] - cref);
+                const float A = w[0][0] * (vr[0] - cref) + x1 + x2, X = x1 + 2.0f * x2;
+                const float wA = w[1][oy] * A;
+                B += wA;
+                BX += w[1][oy] * X;
+                if (oy) BY += (float)oy * wA;
+            }
+            const float wB = w[2][oz] * B;
+            S += wB;
+            Mx += w[2][oz] * BX;
+            My += w[2][oz] * BY;
+            if (oz) Mz += (float)oz * wB;
+        }
+        vn[a] = cref + S;
+        Bh[3 * a] = Mx - S * xi[0];
+        Bh[3 * a + 1] = My - S * xi[1];
+        Bh[3 * a + 2] = Mz - S * xi[2];
+        // one component at a time: unpinned, the three components' loads overlap in 181 VGPRs
+        // (two waves per SIMD), pinned in 148 (three)
+        asm volatile("" : "+v"(vn[a]), "+v"(Bh[3 * a]), "+v"(Bh[3 * a + 1]), "+v"(Bh[3 * a + 2])::"memory");
+    }
+    const float Di[9] = {4.0f, 0.0f, 0.0f, 0.0f, 4.0f, 0.0f, 0.0f, 0.0f, 4.0f};
+    const DevMaterial M = material_of(d, q.mat);
+    return g2p_finish(d, pa, dt, q, M, vn, Bh, Di, out, true, ns, cn, placed);
+}
+
+
+// Workgroups per particle block, as a shift: 1, 2 or 4 of them, each taking every 2nd or
+// 4th pass of the block's particles and gathering the tile for itself.  A block of 512
+// particles is four passes one after the other, each bound by its chain of dependent
+// instructions; while the blocks leave workgroup slots of the GPU empty (256 CUs of six
+// 128-thread workgroups), the passes run side by side.  The lines: four workgroups up to
+// one round of the slots, two up to 10 workgroups per CU.  Measured (us per mpm_step step
+// at 124 / 343 / 576 / 897 / 1728 blocks of moving sand): one workgroup 66 / 74 / 77 / 86 /
+// 125, two - / - / 68.4 / 84.2 / 132, four 54 / 61 / 69.8 / - / -; G2P alone at 125 blocks
+// 23.4 -> 13.9 us.
+__device__ __forceinline__ int g2p_split(int np) { return np <= 256 * 6 / 4 ? 2 : np <= 256 * 10 / 2 ? 1 : 0; }
+
+// One pass of the G2P particle loop over particles j0 + thread of a block: `cur` holds
+// the particle's inputs (loaded a pass before); `nxt` loads those of the next pass from
+// the index pnext (loaded a pass before), and pnext the index after that.  Lanes past
+// the end load the block's last particle again: loads on every path let the first
+// use of a particle's inputs wait for that particle's loads alone.
+template <bool kCarry, bool kCarried, int kMode>
+__device__ __forceinline__ void g2p_pass(const DevCtx &d, const PartArgs &pa, float dt, const float *vt, int bx,
+                                         int by, int bz, int s, int cnt, uint32_t last, int j0, int step, int E,
+                                         G2PIn &cur, G2PIn &nxt, uint32_t &pnext, int &stay) {
+    const int j = j0 + (int)threadIdx.x;
+    const bool act = j < cnt;
+    if (kCarried) unpack_remainder(d.geo, cur.rp, cur.xr);
+    const uint32_t pn = pnext;   // the index first, then the next particle's inputs
+    pnext = ld_at(d.perm, min((uint32_t)(s + j + 2 * step), last));
+    g2p_load_index(pa, pn, nxt, kCarried);
+    const uint32_t out = (uint32_t)(s + j);
+    CellCoord cc;
+    bool ok = act && cell_coord(d.geo, cur.x, cur.xr, cc);
+    ok = ok && (cc.c[0] >> 2) == bx && (cc.c[1] >> 2) == by && (cc.c[2] >> 2) == bz;
+    // the particle's block in the next step (-1: none)
+    int sig = -1;
+    CellCoord cn = {};
+    const int own = vblock_id(d.geo, bx, by, bz);
+    // blocks whose particle set or bins change: this one when a particle leaves it or
+    // its (octant, cell) bin, and the one it enters
+    bool changed = false;
+    if (act && !ok) {
+        set_status(d.counters, ST_STALE);
+        st_at(d.key, out, 0xffffffffu);
+        changed = true;
+    } else if (ok) {
+        NewState ns;
+        bool placed;
+        if (kMode == G2P_QUAD) sig = quad_particle(d, pa, dt, cur, cc, bx, by, bz, vt, out, ns, cn, placed);
+        else sig = g2p_particle<kMode>(d, pa, dt, cur, cc, bx, by, bz, vt, out, true, ns, cn, placed, true, kCarry);
+        if (!placed) {
+            changed = true;
+        } else if (sig != own || sub_code(cn) != sub_code(cc)) {
+            changed = true;
+            d.bchg[sig] = E + 1;
+        }
+    }
+    if (__any(changed)) {
+        if (changed) d.bchg[own] = E + 1;
+    }
+    // those that stay are counted for the whole block at its end, the others at once
+    stay += __popcll(__ballot(sig == own));
+    const bool left = sig >= 0 && sig != own;
+    if (__any(left)) wave_stamp(d, left, cn.c[0] >> 2, cn.c[1] >> 2, cn.c[2] >> 2, E + 1);
+}
+
+// Gathers the velocity tile of block (bx,by,bz) (kTileNodes nodes, three channels) by
+// the workgroup's threads; nodes outside active blocks are at rest.  The loads of all of
+// a thread's nodes are issued before any is used: one memory round trip for the tile.
+// kFold: the pool still holds the P2G's momenta, and the grid update is applied to each
+// node as it is gathered.  A node is gathered by 2.7 blocks on average in the interior of
+// a body, but that costs less than the update's own pass over the grid and its launch:
+// sand column, update 11 us + G2P 213.7 us -> G2P 221.5 us; 1,000 particles, a step
+// 47.2 -> 45.1 us; 262,144 particles in deterministic mode, 109 -> 104 us.
+template <bool kFold>
+__device__ __forceinline__ void gather_tile(const DevCtx &d, float dt, int gp, const int *nbr, int bx, int by, int bz,
+                                            float *vt) {
+    constexpr int kPer = (kTileNodes + kG2PThreads - 1) / kG2PThreads;
+    const float *pool = pool_of(d, gp);
+    float m[kPer], p[kPer][3];
+    TileNode q[kPer];
+    int ph[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        q[k] = tile_entry(kTile.e[min((int)threadIdx.x + k * kG2PThreads, kTileNodes - 1)]);
+        ph[k] = nbr[q[k].nb];
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const float *a = pool + (size_t)max(ph[k], 0) * kBlockFloats + q[k].at;
+        if (kFold) m[k] = a[0];
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) p[k][ch] = a[(1 + ch) * 64];
+    }
+    // (uniform) no node of the tile lies on a wall
+    const bool inner = kFold && 4 * min(bx, min(by, bz)) - 1 >= max(d.geo.stick_lo[0], d.geo.stick_lo[1]) &&
+                       4 * bx + 4 <= min(d.geo.stick_hi[0][0], d.geo.stick_hi[1][0]) &&
+                       4 * by + 4 <= min(d.geo.stick_hi[0][1], d.geo.stick_hi[1][1]) &&
+                       4 * bz + 4 <= min(d.geo.stick_hi[0][2], d.geo.stick_hi[1][2]);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        float v[3];
+        if (kFold) {
+            const float mk = ph[k] >= 0 ? m[k] : 0.0f;
+            if (inner) {
+                const float im = fast_rcp(mk);
+#pragma unroll
+                for (int ch = 0; ch < 3; ++ch) v[ch] = mk > 0.0f ? p[k][ch] * im + dt * d.gravity[ch] : 0.0f;
+            } else {
+                const int nb = q[k].nb, l = q[k].at & 63;
+                node_velocity(d, dt, q[k].g, 4 * (bx + nb % 3 - 1) + (l & 3), 4 * (by + nb / 3 % 3 - 1) + ((l >> 2) & 3),
+                              4 * (bz + nb / 9 - 1) + (l >> 4), mk, p[k][0], p[k][1], p[k][2], v);
+            }
+        } else {
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) v[ch] = ph[k] >= 0 ? p[k][ch] : 0.0f;
+        }
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) vt[ch * kTileNodes + q[k].ni] = v[ch];
+    }
+}
+
+// kCarry: the output is the carried state for the next P2G of the same step sequence
+// (Q in the B planes, the packed remainder); kCarried: so is the input.  The particle
+// loop runs two passes per trip, each reading the inputs the other loaded: the two
+// sets of registers then take turns, where one set copied into the other at the end
+// of every pass would wait for every store of the pass.  kKept: the step's P2G was
+// b_p2g, which kept every block's neighbourhood (one load, not a page lookup that
+// waits for the block's id).
+template <bool kCarry = false, bool kCarried = false, bool kKept = false, bool kFold = false, int kMode = G2P_MLS>
+__device__ __forceinline__ void b_g2p(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt) {
+    __shared__ float vt[3 * (kMode == G2P_QUAD ? kQNodes : kTileNodes)];
     __shared__ int nbr[27];
     const int np = (int)d.counters[C_NPB];
     const int E = (int)d.counters[C_EPOCH];
     const int tid = threadIdx.x;
-    for (int base = 0; base < np; base += gridDim.x) {
-        const int r = round_block(base, np);
-        if (r < 0) continue;
+    const int sh = g2p_split(np), step = kG2PThreads << sh;
+    for (int base = 0; base < np << sh; base += gridDim.x) {
+        const int u = round_block(base, np << sh);
+        if (u < 0) continue;
+        const int r = u >> sh, first = (u & ((1 << sh) - 1)) * kG2PThreads;
         const int vb = d.plist[r];
         int bx, by, bz;
         block_coords(d.geo, vb, bx, by, bz);
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
-        if (tid == 0) block_counts(d, E)[vb] = 0;   // the step's last use of them
-        if (cnt > kMaxBlockParticles) continue;
-        G2PIn nxt;
-        if (tid < cnt) g2p_load(d, pa, (uint32_t)(s + tid), nxt);
-        load_neighbours(d, gt, bx, by, bz, nbr);
-        lds_barrier();
-        for (int ni = tid; ni < kQNodes; ni += kG2PThreads) {
-            const int ix = 4 * bx - 1 + ni % 7, iy = 4 * by - 1 + (ni / 7) % 7, iz = 4 * bz - 1 + ni / 49;
-            const long long a = pool_index(d, nbr, bx, by, bz, 0, ix, iy, iz, 0);
-            const float *q = pool_of(d, gp) + (a >= 0 ? a : 0);
-            float v[3] = {q[64], q[128], q[192]};
-            if (fold) node_velocity(d, dt, 0, ix, iy, iz, a >= 0 ? q[0] : 0.0f, v[0], v[1], v[2], v);
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) vt[ch * kQNodes + ni] = a >= 0 ? v[ch] : 0.0f;
+        if (tid == 0 && first == 0) block_counts(d, E)[vb] = 0;   // the step's last use of them
+        if (cnt <= first || cnt > kMaxBlockParticles) continue;
+        // the first particle's inputs load while the tile is gathered, and the index of
+        // the one after
+        const uint32_t last = (uint32_t)(s + cnt - 1);
+        G2PIn qa, qb;
+        g2p_load_index(pa, ld_at(d.perm, min((uint32_t)(s + first + tid), last)), qa, kCarried);
+        uint32_t pnext = ld_at(d.perm, min((uint32_t)(s + first + tid + step), last));
+        if (kKept) {
+            if (tid < 27) nbr[tid] = d.nbrs[27 * (size_t)r + tid];
+        } else {
+            load_neighbours(d, gt, bx, by, bz, nbr);
         }
         lds_barrier();
-        for (int j0 = 0; j0 < cnt; j0 += kG2PThreads) {
-            const int j = j0 + tid;
-            const bool act = j < cnt;
-            const G2PIn q = nxt;
-            if (j + kG2PThreads < cnt) g2p_load(d, pa, (uint32_t)(s + j + kG2PThreads), nxt);
-            const uint32_t out = (uint32_t)(s + j);
-            CellCoord cc;
-            bool ok = act && cell_coord(d.geo, q.x, q.xr, cc);
-            ok = ok && (cc.c[0] >> 2) == bx && (cc.c[1] >> 2) == by && (cc.c[2] >> 2) == bz;
-            float xi[3];
-            int lb[3];
-            const bool inside = ok && quad_coords(d.geo, cc, bx, by, bz, xi, lb);
-            int sig = -1;
-            CellCoord cn = {};
-            if (act && !ok) {
-                set_status(d.counters, ST_STALE);
-                st_at(d.key, out, 0xffffffffu);
-            } else if (ok && !inside) {
-                set_status(d.counters, ST_DOMAIN);
-                st_at(d.key, out, 0xffffffffu);
-            } else if (ok) {
-                // v = sum w v~, Bh = sum w v~ (o - xi)^T, relative to the velocity c of
-                // the middle node (the weights sum to one and have zero first moment)
-                float w[3][3];
-                quad_weights(xi, w);
-                const int t1 = (lb[0] + 1) + (lb[1] + 1) * 7 + (lb[2] + 1) * 49;
-                const float cref[3] = {vt[t1], vt[kQNodes + t1], vt[2 * kQNodes + t1]};
-                float vs[3] = {0.0f, 0.0f, 0.0f}, Bh[9];
-#pragma unroll
-                for (int i = 0; i < 9; ++i) Bh[i] = 0.0f;
-#pragma unroll
-                for (int oz = 0; oz < 3; ++oz)
-#pragma unroll
-                    for (int oy = 0; oy < 3; ++oy)
-#pragma unroll
-                        for (int ox = 0; ox < 3; ++ox) {
-                            const float wt = w[0][ox] * w[1][oy] * w[2][oz];
-                            const int t = (lb[0] + ox) + (lb[1] + oy) * 7 + (lb[2] + oz) * 49;
-                            const float dxo = (float)ox - xi[0], dyo = (float)oy - xi[1], dzo = (float)oz - xi[2];
-#pragma unroll
-                            for (int a = 0; a < 3; ++a) {
-                                const float dv = wt * (vt[a * kQNodes + t] - cref[a]);
-                                vs[a] += dv;
-                                Bh[3 * a] += dv * dxo;
-                                Bh[3 * a + 1] += dv * dyo;
-                                Bh[3 * a + 2] += dv * dzo;
-                            }
-                        }
-                float vn[3];
-#pragma unroll
-                for (int a = 0; a < 3; ++a) vn[a] = cref[a] + vs[a];
-                const float Di[9] = {4.0f, 0.0f, 0.0f, 0.0f, 4.0f, 0.0f, 0.0f, 0.0f, 4.0f};
-                const DevMaterial M = material_of(d, q.mat);
-                NewState ns;
-                bool placed;
-                sig = g2p_finish(d, pa, dt, q, M, vn, Bh, Di, out, true, ns, cn, placed);
-            }
-            wave_stamp(d, sig >= 0, cn.c[0] >> 2, cn.c[1] >> 2, cn.c[2] >> 2, E + 1);
+        if (kMode == G2P_QUAD) quad_gather_tile<kFold>(d, dt, gp, nbr, bx, by, bz, vt);
+        else gather_tile<kFold>(d, dt, gp, nbr, bx, by, bz, vt);
+        lds_barrier();
+        int stay = 0;   // the wave's particles that stay in the block
+        for (int j0 = first; j0 < cnt; j0 += 2 * step) {   // the same trip count for every lane
+            g2p_pass<kCarry, kCarried, kMode>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0, step, E, qa, qb, pnext, stay);
+            if (j0 + step < cnt)
+                g2p_pass<kCarry, kCarried, kMode>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0 + step, step, E, qb, qa, pnext,
+                                           stay);
         }
+        if (stay > 0) stamp_block(d, bx, by, bz, stay, E + 1);
         lds_barrier();
     }
+}
+
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p(DevCtx d, PartArgs pa, float dt, int gp, int gt) { b_g2p(d, pa, dt, gp, gt); }
+// The forms inside an mpm_step sequence, whose P2G (b_p2g) kept every block's
+// neighbourhood; every one but the last step's folds the grid update into its gather.
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_fold(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_g2p<false, false, true, true>(d, pa, dt, gp, gt);
+}
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_carry(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_g2p<true, false, true, true>(d, pa, dt, gp, gt);
+}
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_cc(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_g2p<true, true, true, true>(d, pa, dt, gp, gt);
+}
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_cf(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_g2p<false, true, true>(d, pa, dt, gp, gt);
+}
+
+// one launch for many jobs: workgroup row y runs job y (every job's P2G of the round,
+// plain or deterministic, was b_p2g, which kept the neighbourhoods; nobody reads the
+// grid of a served job, so its update is folded into the gather)
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_multi(const JobStep *__restrict__ jobs) {
+    const JobStep &J = jobs[blockIdx.y];
+    b_g2p<false, false, true, true>(J.d, J.pa, J.dt, J.table, J.table);
+}
+
+// ---------------------------------------------------------------- exact-gradient transfers
+// APIC (section 4.4) and PIC (section 4.3) on the two staggered grids: the stress
+// force uses the exact kernel gradient, f_i = -sum_p V0 tau grad w_ip, and G2P takes
+// the velocity gradient as 1/2 sum_k sum_i v~_i grad w^T; APIC keeps the affine
+// momentum m B D^-1 (x_i - x_p) and carries B, PIC transfers m v alone and carries no
+// B.  Per axis on grid k with fraction xi the two weights 1 - xi + s, xi - s have
+// x_p-derivatives (cos(2 pi xi) - 1)/dx and (1 - cos(2 pi xi))/dx, and the G- cosine
+// is minus the G+ one (the fractions differ by half a cell).
+struct GStaged {
+    float xm[3], sp[3], cp[3];   // G- fraction, G+ sine and cosine per axis
+    float mass, base[3], Q[9];   // affine part as in the MLS staging (Q = 0 for PIC)
+    float T[9];                  // -dt V0 tau / dx: force per unit weight gradient (cell units)
+    int c[3], oct;
+    bool on;
+};
+
+__device__ __forceinline__ void grad_stage(const DevCtx &d, const PartArgs &pa, int p, int bx, int by, int bz,
+                                           float dt, GStaged &r) {
+    r.on = false;
+    const bool pic = d.transfer == 2;
+    const long long S = pa.stride;
+    const uint32_t up = (uint32_t)p;
+    float x[3], xr[3], v[3], B[9], tau[6];
+    ld_planes(pa.in, S, kPlaneX, up, x);
+    ld_planes(pa.in, S, kPlaneR, up, xr);
+    ld_planes(pa.in, S, kPlaneV, up, v);
+    ld_planes(pa.in, S, kPlaneB, up, B);
+    ld_planes(d.tau, d.tau_stride, 0, up, tau);
+    if (pic) {
+#pragma unroll
+        for (int a = 0; a < 9; ++a) B[a] = 0.0f;
+    }
+    const int mi = pa.mat_in ? (int)ld_at(pa.mat_in, up) : 0;
+    const DevMaterial M = material_of(d, mi);
+    CellCoord cc;
+    if (!cell_coord(d.geo, x, xr, cc)) {
+        set_status(d.counters, ST_DOMAIN);
+        return;
+    }
+    if ((cc.c[0] >> 2) != bx || (cc.c[1] >> 2) != by || (cc.c[2] >> 2) != bz) {
+        set_status(d.counters, ST_STALE);
+        return;
+    }
+    r.oct = (int)(sub_code(cc) & 7u);
+    Weights w;
+    axis_weights(cc, w);
+    float Di[9];
+    moment_inverse(cc, w, Di);
+    const float sc = d.geo.inv_dx_f;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            r.Q[3 * i + j] = sc * M.mass * (B[3 * i] * Di[j] + B[3 * i + 1] * Di[3 + j] + B[3 * i + 2] * Di[6 + j]);
+    const float Tf[9] = {tau[0], tau[3], tau[4], tau[3], tau[1], tau[5], tau[4], tau[5], tau[2]};
+    const float k = -dt * M.vol0 * sc;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) r.T[i] = k * Tf[i];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        r.c[a] = cc.c[a];
+        r.xm[a] = cc.xm[a];
+        r.sp[a] = w.sp[a];
+        r.cp[a] = __builtin_amdgcn_cosf(cc.xp[a]);
+        r.base[a] = M.mass * v[a] - (r.Q[3 * a] * cc.xm[0] + r.Q[3 * a + 1] * cc.xm[1] + r.Q[3 * a + 2] * cc.xm[2]);
+    }
+    r.mass = M.mass;
+    r.on = true;
+}
+
+__device__ __forceinline__ float grad_bound(const GStaged &r) {
+    if (!r.on) return 0.0f;
+    float b = r.mass;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        b = fmaxf(b, fabsf(r.base[a]) + 1.5f * (fabsf(r.Q[3 * a]) + fabsf(r.Q[3 * a + 1]) + fabsf(r.Q[3 * a + 2])) +
+                         2.0f * (fabsf(r.T[3 * a]) + fabsf(r.T[3 * a + 1]) + fabsf(r.T[3 * a + 2])));
+    return b;
+}
+
+// Per-axis weights and x_p-derivatives (cell units) of both grids, the G+ base offset
+// and the affine momentum at each grid's base node.
+__device__ __forceinline__ void grad_axes(const GStaged &r, float (&w)[2][3][2], float (&dw)[2][3][2], int (&up)[3],
+                                          float (&m0)[2][3]) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        up[a] = (r.oct >> a) & 1;
+        const float xp = up[a] ? r.xm[a] - 0.5f : r.xm[a] + 0.5f;
+        w[0][a][0] = 1.0f - r.xm[a] - r.sp[a];
+        w[0][a][1] = r.xm[a] + r.sp[a];
+        w[1][a][0] = 1.0f - xp + r.sp[a];
+        w[1][a][1] = xp - r.sp[a];
+        dw[1][a][0] = r.cp[a] - 1.0f;
+        dw[1][a][1] = 1.0f - r.cp[a];
+        dw[0][a][0] = -r.cp[a] - 1.0f;
+        dw[0][a][1] = 1.0f + r.cp[a];
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        m0[0][a] = r.base[a];
+        m0[1][a] = r.base[a] + ((float)up[0] - 0.5f) * r.Q[3 * a] + ((float)up[1] - 0.5f) * r.Q[3 * a + 1] +
+                   ((float)up[2] - 0.5f) * r.Q[3 * a + 2];
+    }
+}
+
+// Adds the particle's 16 contributions to the fixed-point tile (layout of k_p2g's).
+__device__ __forceinline__ void grad_scatter(const GStaged &r, int lx, int ly, int lz, unsigned long long *tile_m,
+                                             unsigned long long *tile_p, double S) {
+    float w[2][3][2], dw[2][3][2], m0[2][3];
+    int up[3];
+    grad_axes(r, w, dw, up, m0);
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        unsigned long long *tile = g == 0 ? tile_m : tile_p;
+        const int ntile = g == 0 ? kTileMStride : kTilePStride;
+        const int t0 = g == 0 ? lz * kTZ + ly * kTY + lx : (lz + up[2]) * kTZ + (ly + up[1]) * kTY + (lx + up[0]);
+#pragma unroll
+        for (int o = 0; o < 8; ++o) {
+            const int ox = o & 1, oy = (o >> 1) & 1, oz = o >> 2;
+            const float wx = w[g][0][ox], wy = w[g][1][oy], wz = w[g][2][oz];
+            const float wt = wx * wy * wz;
+            const float gx = dw[g][0][ox] * wy * wz, gy = wx * dw[g][1][oy] * wz, gz = wx * wy * dw[g][2][oz];
+            const int t = t0 + ox + oy * kTY + oz * kTZ;
+            atomicAdd(&tile[t], to_fixed(wt * r.mass, S));
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float mom = wt * (m0[g][a] + ox * r.Q[3 * a] + oy * r.Q[3 * a + 1] + oz * r.Q[3 * a + 2]) +
+                                  r.T[3 * a] * gx + r.T[3 * a + 1] * gy + r.T[3 * a + 2] * gz;
+                atomicAdd(&tile[(1 + a) * ntile + t], to_fixed(mom, S));
+            }
+        }
+    }
+}
+
+// Straight into the pool, for a particle above the step's contribution bound.
+__device__ __forceinline__ void grad_pool(const DevCtx &d, float *pool, const int *nbr, int bx, int by, int bz,
+                                          const GStaged &r) {
+    float w[2][3][2], dw[2][3][2], m0[2][3];
+    int up[3];
+    grad_axes(r, w, dw, up, m0);
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int o = 0; o < 8; ++o) {
+            const int ox = o & 1, oy = (o >> 1) & 1, oz = o >> 2;
+            const int ix = r.c[0] + (g ? up[0] - 1 : 0) + ox, iy = r.c[1] + (g ? up[1] - 1 : 0) + oy,
+                      iz = r.c[2] + (g ? up[2] - 1 : 0) + oz;
+            const long long a = pool_index(d, nbr, bx, by, bz, g, ix, iy, iz, 0);
+            if (a < 0) {
+                set_status(d.counters, ST_CAPACITY);
+                continue;
+            }
+            const float wx = w[g][0][ox], wy = w[g][1][oy], wz = w[g][2][oz], wt = wx * wy * wz;
+            const float gx = dw[g][0][ox] * wy * wz, gy = wx * dw[g][1][oy] * wz, gz = wx * wy * dw[g][2][oz];
+            atomicAdd(&pool[a], wt * r.mass);
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                atomicAdd(&pool[a + (1 + c) * 64],
+                          wt * (m0[g][c] + ox * r.Q[3 * c] + oy * r.Q[3 * c + 1] + oz * r.Q[3 * c + 2]) +
+                              r.T[3 * c] * gx + r.T[3 * c + 1] * gy + r.T[3 * c + 2] * gz);
+        }
+}
+
+struct GradTransfer {
+    using Particle = GStaged;
+    static constexpr int kTileWords = MlsTransfer<false>::kTileWords;
+    static __device__ __forceinline__ void stage(const DevCtx &d, const PartArgs &pa, int p, int bx, int by, int bz,
+                                                 float dt, GStaged &st) {
+        grad_stage(d, pa, p, bx, by, bz, dt, st);
+    }
+    static __device__ __forceinline__ float bound(const GStaged &st) { return grad_bound(st); }
+    static __device__ __forceinline__ void scatter(const GStaged &st, int bx, int by, int bz, unsigned long long *tile,
+                                                   double S) {
+        grad_scatter(st, st.c[0] - 4 * bx, st.c[1] - 4 * by, st.c[2] - 4 * bz, tile, tile + 4 * kTileMStride, S);
+    }
+    static __device__ __forceinline__ void direct(const DevCtx &d, float *pool, const int *nbr, int bx, int by, int bz,
+                                                  const GStaged &st) {
+        grad_pool(d, pool, nbr, bx, by, bz, st);
+    }
+    static __device__ __forceinline__ void flush(const DevCtx &d, float *pool, const int *nbr, int, int, int,
+                                                 const unsigned long long *tile, double inv) {
+        flush_tile(d, pool, nbr, tile, tile + 4 * kTileMStride, inv);
+    }
+};
+
+// As the MLS form: one staged particle per thread in the step-global unit, and kept orders.
+// Bound by the LDS atomics (64 per particle) and their conversions.  500,000 particles: two
+// staged particles per thread (192 VGPRs, two waves per SIMD) in a unit formed for each
+// block, and orders from scratch 63.7 us; this form 47.0 us (128 VGPRs, four waves).
+__global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_grad(DevCtx d, PartArgs pa, float dt, int gp, int gt, int reuse) {
+    b_p2g<false, GradTransfer>(d, pa, dt, gp, gt, reuse != 0);
+}
+
+// As the MLS forms, with the same loop, prefetch and sharing of blocks; three waves per
+// SIMD.  500,000 particles: 56.9 us with all 16 nodes' gradients in full (211 VGPRs, two
+// waves), 39.3 us from separable sums, 41.2 us with the grid update folded in.
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_grad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_g2p<false, false, true, false, G2P_GRAD>(d, pa, dt, gp, gt);
+}
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_grad_fold(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_g2p<false, false, true, true, G2P_GRAD>(d, pa, dt, gp, gt);
+}
+
+// ---------------------------------------------------------------- quadratic B-spline kernels
+// On the MLS forms' block loops.  Bound by the LDS atomics, 108 per particle.  500,000
+// particles: P2G with two staged particles per thread, a unit formed for each block and
+// orders from scratch 58.0 us, now 54.3 us; three waves per SIMD without spills 55.9 us.
+__global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_quad(DevCtx d, PartArgs pa, float dt, int gp, int gt, int reuse) {
+    b_p2g<false, QuadTransfer>(d, pa, dt, gp, gt, reuse != 0);
+}
+
+// 500,000 particles: 55 us with 27 products and six moments per component (two waves per
+// SIMD), 39.3 us from separable sums (three waves), 39.9 us with the grid update folded in.
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_quad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_g2p<false, false, true, false, G2P_QUAD>(d, pa, dt, gp, gt);
+}
+__global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_quad_fold(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_g2p<false, false, true, true, G2P_QUAD>(d, pa, dt, gp, gt);
 }
 
 // ---------------------------------------------------------------- exports
@@ -2385,9 +2348,9 @@ void launch_p2g(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt, h
                 bool reuse) {
     const int ru = reuse ? 1 : 0;
     if (d.quadratic)
-        hipLaunchKernelGGL(k_p2g_quad, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt);
+        hipLaunchKernelGGL(k_p2g_quad, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt, ru);
     else if (d.transfer != 0)
-        hipLaunchKernelGGL(k_p2g_grad, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt);
+        hipLaunchKernelGGL(k_p2g_grad, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt, ru);
     else if (d.det)
         hipLaunchKernelGGL(k_p2g_det, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt, ru);
     else if (carried)
@@ -2407,21 +2370,14 @@ void launch_grid_update(const DevCtx &d, float dt, int gp, int gt, hipStream_t s
 
 void launch_g2p(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt, hipStream_t s, bool carry,
                 bool carried, bool fold) {
-    const int fo = fold ? 1 : 0;
-    if (d.quadratic)
-        hipLaunchKernelGGL(k_g2p_quad, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt, fo);
-    else if (d.transfer != 0)
-        hipLaunchKernelGGL(k_g2p_grad, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt, fo);
-    else if (carry && carried)
-        hipLaunchKernelGGL(k_g2p_cc, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt);
-    else if (carry)
-        hipLaunchKernelGGL(k_g2p_carry, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt);
-    else if (carried)
-        hipLaunchKernelGGL(k_g2p_cf, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt);
-    else if (fold)
-        hipLaunchKernelGGL(k_g2p_fold, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt);
-    else
-        hipLaunchKernelGGL(k_g2p, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt);
+    using Kernel = void (*)(DevCtx, PartArgs, float, int, int);
+    Kernel k;
+    if (d.quadratic) k = fold ? k_g2p_quad_fold : k_g2p_quad;
+    else if (d.transfer != 0) k = fold ? k_g2p_grad_fold : k_g2p_grad;
+    else if (carry) k = carried ? k_g2p_cc : k_g2p_carry;
+    else if (carried) k = k_g2p_cf;
+    else k = fold ? k_g2p_fold : k_g2p;
+    hipLaunchKernelGGL(k, dim3(particle_grid(d)), dim3(kG2PThreads), 0, s, d, pa, dt, gp, gt);
 }
 
 void launch_block_order(const DevCtx &d, hipStream_t s) {
