@@ -259,7 +259,7 @@ mpm_status enqueue_p2g(mpm_ctx *ctx, const mpm_particles *p, double dt, hipStrea
     if (!physics) {
         launch_block_sort(ctx->d, s);
     } else {
-        launch_p2g(ctx->d, pa, (float)dt, t, t, s, carried_in, keep_orders);
+        launch_p2g(ctx->d, pa, (float)dt, t, t, s, carried_in);
         if (ctx->d.det) launch_det_gather(ctx->d, t, t, s);
         ctx->grid_pool = t;
         ctx->grid_table = t;

@@ -88,7 +88,8 @@ struct DevCtx {
     int *bchg;             // per virtual block: epoch of the last step whose G2P changed the set or the
                            // (octant, cell) bins of its particles (-1: never)
     uint32_t *blo, *bhi;   // per particle block whose order is kept: smallest and largest position of
-                           // its particles (the bucket is not filled for such a block)
+                           // its particles (the bucket is not filled for such a block); blo > bhi for
+                           // any other
     int *plist;            // particle blocks in increasing virtual id
     int *nbrs;             // per particle block: pool blocks of its 3 x 3 x 3 neighbourhood in the
                            // step's page table (-1: none), written by P2G and read by G2P
@@ -859,10 +860,7 @@ void launch_stress(const DevCtx &d, const PartArgs &pa, hipStream_t s);
 // carried: the B planes of pa.in hold Q, the first remainder plane the packed remainder,
 // and there is no carried stress (the state an mpm_step G2P with carry left for the
 // next step)
-// reuse: the input is the state the context's previous G2P wrote, whose blocks' orders
-// the P2G may keep where that G2P changed nothing (see DevCtx::bchg)
-void launch_p2g(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt, hipStream_t s, bool carried = false,
-                bool reuse = false);
+void launch_p2g(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt, hipStream_t s, bool carried = false);
 void launch_grid_update(const DevCtx &d, float dt, int gp, int gt, hipStream_t s);
 void launch_det_gather(const DevCtx &d, int gp, int gt, hipStream_t s);
 // carry: write the carried state (Q = (m B - dt V0 tau) D^-1 / dx in the B planes and no

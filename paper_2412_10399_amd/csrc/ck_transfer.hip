@@ -12,6 +12,7 @@
 #include "ck_common.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace ck {
 
@@ -314,7 +315,6 @@ __global__ void __launch_bounds__(kThreads) k_stress_multi(const JobStep *__rest
 constexpr int kP2GThreads = 256;
 constexpr int kBins = 512;                 // (octant, cell) bins of a block: octant * 64 + cell
 constexpr int kPerThread = kMaxBlockParticles / kP2GThreads;   // bucket entries per thread
-constexpr int kHold = 2;                   // of which kept in registers
 constexpr int kChunk = 2 * kP2GThreads;    // particles scattered per pass (two per thread)
 // a pass's node sums (< kChunk * 2^40 units) must stay below 2^51 for to_fixed and the
 // conversion back through FP64 to be exact
@@ -647,7 +647,7 @@ __device__ __forceinline__ void scatter_pool(const DevCtx &d, float *pool, const
 // instruction hits fewer equal LDS addresses.  Bins of more than kLayers particles
 // (dense blocks) keep the (octant, cell, index) order.
 constexpr int kLayers = 16;
-constexpr int kLayWords = 2 * kLayers * (kP2GThreads / 64) + kP2GThreads / 64;   // LDS ints of the layer tables
+constexpr int kLayWords = 2 * kLayers * (kP2GThreads / 64) + 2 * (kP2GThreads / 64);   // LDS ints of the layer tables
 // per (layer, wave range): the ballots of its bins holding more than q particles,
 // even and odd bins (64-bit words)
 constexpr int kLayMaskWords = 2 * kLayers * (kP2GThreads / 64);
@@ -655,143 +655,126 @@ constexpr int kLayMaskWords = 2 * kLayers * (kP2GThreads / 64);
 // fixed-point tile
 constexpr int kOrderWords = kMaxBlockParticles * 4 / 8;
 
-// Orders the particles of block r (count cnt, first sorted position s) by (half-cell
-// octant, cell, index), or in the layered order when `layered`: ord[j] = particle
-// index at position j of the block, also written to the global permutation.  Uses
-// bcnt, bstart, wsum and lbuf (LDS); the layered order also uses lay (kLayWords ints)
-// and lmask (kLayMaskWords 64-bit words).
-template <bool layered = false>
-__device__ __forceinline__ void order_block(const DevCtx &d, int r, int s, int cnt, int *bcnt, int *bstart, int *wsum,
-                                            uint32_t *lbuf, uint32_t *ord, int *lay = nullptr,
-                                            unsigned long long *lmask = nullptr) {
+// Inclusive sums over the wave's lanes, in DPP steps (a __shfl step is an LDS round trip).
+__device__ __forceinline__ int wave_sums(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast 15, 31
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+    return v;
+}
+// The wave's largest v >= 0.
+__device__ __forceinline__ int wave_largest(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Orders the particles of block r (count cnt > 0, first sorted position s) in the layered
+// order, or by (half-cell octant, cell, index) when a bin holds more than kLayers: ord[j] =
+// particle index at position j of the block, also written to the global permutation.  Uses
+// bcnt, bstart and lbuf (LDS), lay (kLayWords ints) and lmask (kLayMaskWords 64-bit words).
+// Bound by latency: one load round trip and five barriers with a few LDS operations
+// between them.  So the entries load before the bins are cleared, the counting atomic
+// gives each its slot in its bin, the scans are DPP steps, and the waves' bin sums meet at
+// one barrier (starts within a wave's 128 bins are stored; readers add the waves before).
+// A block of 1,000 moving particles is ordered in 5,200 clocks after its head has loaded,
+// against 7,700 with loads after the first barrier, two atomic passes and __shfl scans.
+__device__ __forceinline__ void order_block(const DevCtx &d, int r, int s, int cnt, int *bcnt, int *bstart,
+                                            uint32_t *lbuf, uint32_t *ord, int *lay, unsigned long long *lmask) {
+    constexpr int kWaves = kP2GThreads / 64;
+    static_assert(kBins == 2 * kP2GThreads && kWaves == 4, "two bins per thread, four waves");
     const int tid = threadIdx.x;
     const int lane = tid & 63, w = tid >> 6;
     const uint32_t *bkt = d.bucket + (size_t)r * kMaxBlockParticles;
     const uint16_t *bsb = d.bsub + (size_t)r * kMaxBlockParticles;
-    for (int b = tid; b < kBins; b += kP2GThreads) bcnt[b] = 0;
-    lds_barrier();
-    uint32_t hidx[kHold];
-    int hbin[kHold];
+    uint32_t idx[kPerThread];
+    int bin[kPerThread], slot[kPerThread];
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) {
-        const int j = tid + k * kP2GThreads;
-        if (j >= cnt) break;
-        const uint32_t idx = bkt[j];
-        const int bin = bin_of(bsb[j]);
-        if (k < kHold) {
-            hidx[k] = idx;
-            hbin[k] = bin;
-        }
-        atomicAdd(&bcnt[bin], 1);
+        if (k * kP2GThreads >= cnt) break;
+        const int j = min(tid + k * kP2GThreads, cnt - 1);
+        idx[k] = bkt[j];
+        bin[k] = bsb[j];
+    }
+    bcnt[tid] = 0;
+    bcnt[tid + kP2GThreads] = 0;
+    lds_barrier();
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k) {
+        if (k * kP2GThreads >= cnt) break;
+        bin[k] = bin_of((uint32_t)bin[k]);
+        if (tid + k * kP2GThreads < cnt) slot[k] = atomicAdd(&bcnt[bin[k]], 1);
     }
     lds_barrier();
+    int *wsum = lay + 2 * kLayers * kWaves, *wmx = wsum + kWaves;
     {
-        // exclusive scan of the 512 bins, two per thread
+        // lane l holds bins 2l and 2l + 1 of the wave's 128
         const int c0 = bcnt[2 * tid], c1 = bcnt[2 * tid + 1];
-        int v = c0 + c1;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int t = __shfl_up(v, off);
-            if (lane >= off) v += t;
-        }
-        if (lane == 63) wsum[w] = v;
-        int mx = 0;
-        if (layered) {
-            mx = max(c0, c1);
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) mx = max(mx, __shfl_xor(mx, off));
-            if (lane == 0) lay[2 * kLayers * 4 + w] = mx;
-        }
-        lds_barrier();
-        int pre = 0;
-        for (int k = 0; k < w; ++k) pre += wsum[k];
-        const int ex = pre + v - c0 - c1;
-        bstart[2 * tid] = ex;
-        bstart[2 * tid + 1] = ex + c0;
-        bcnt[2 * tid] = ex;
-        bcnt[2 * tid + 1] = ex + c0;
-        if (tid == kP2GThreads - 1) bstart[kBins] = ex + c0 + c1;
-        if (layered) {
-            // largest bin of the block; layer tables when every bin fits kLayers layers:
-            // the ballots of the wave's even and odd bins holding more than q particles
-            // (lane l holds bins 2l and 2l + 1 of the wave's 128), and lay[q * 4 + w] =
-            // the number of such bins in wave w's range
-            mx = max(max(lay[2 * kLayers * 4], lay[2 * kLayers * 4 + 1]),
-                     max(lay[2 * kLayers * 4 + 2], lay[2 * kLayers * 4 + 3]));
-            if (mx <= kLayers) {
-                for (int q = 0; q < mx; ++q) {
-                    const unsigned long long m0 = __ballot(c0 > q), m1 = __ballot(c1 > q);
-                    if (lane == 0) {
-                        lmask[2 * (q * 4 + w)] = m0;
-                        lmask[2 * (q * 4 + w) + 1] = m1;
-                        lay[q * 4 + w] = __popcll(m0) + __popcll(m1);
-                    }
-                }
+        const int v = wave_sums(c0 + c1);
+        bstart[2 * tid] = v - c0 - c1;
+        bstart[2 * tid + 1] = v - c1;
+        const int mx = wave_largest(max(c0, c1));
+        // layer tables: the ballots of the wave's even and odd bins holding more than q
+        // particles, and lay[q * 4 + w] = the number of such bins
+        if (lane < kLayers) lay[lane * kWaves + w] = 0;
+        for (int q = 0; q < min(mx, kLayers); ++q) {
+            const unsigned long long m0 = __ballot(c0 > q), m1 = __ballot(c1 > q);
+            if (lane == 0) {
+                lmask[2 * (q * kWaves + w)] = m0;
+                lmask[2 * (q * kWaves + w) + 1] = m1;
+                lay[q * kWaves + w] = __popcll(m0) + __popcll(m1);
             }
+        }
+        if (lane == 63) {
+            wsum[w] = v;
+            wmx[w] = mx;
         }
     }
     lds_barrier();
-    bool lay_on = false;
-    if (layered) {
-        const int mx = max(max(lay[2 * kLayers * 4], lay[2 * kLayers * 4 + 1]),
-                           max(lay[2 * kLayers * 4 + 2], lay[2 * kLayers * 4 + 3]));
-        lay_on = mx <= kLayers;
-        // first position of (layer q, wave range w): exclusive scan over (q, w) in order
-        if (lay_on && tid < 64) {
-            const int e = tid < mx * 4 ? lay[tid] : 0;
-            int v = e;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int t = __shfl_up(v, off);
-                if (lane >= off) v += t;
-            }
-            lay[kLayers * 4 + tid] = v - e;
-        }
+    const int w1 = wsum[0], w2 = w1 + wsum[1], w3 = w2 + wsum[2];   // particles in the waves' bins before
+    const bool lay_on = max(max(wmx[0], wmx[1]), max(wmx[2], wmx[3])) <= kLayers;
+    // first position of (layer q, wave range w): exclusive scan over (q, w) in order
+    if (w == 0) {
+        const int e = lay[lane];
+        lay[kLayers * kWaves + lane] = wave_sums(e) - e;
     }
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) {
-        const int j = tid + k * kP2GThreads;
-        if (j >= cnt) break;
-        uint32_t idx;
-        int bin;
-        if (k < kHold) {
-            idx = hidx[k];
-            bin = hbin[k];
-        } else {
-            idx = bkt[j];
-            bin = bin_of(bsb[j]);
-        }
-        lbuf[atomicAdd(&bcnt[bin], 1)] = idx;
+        if (k * kP2GThreads >= cnt) break;
+        if (tid + k * kP2GThreads >= cnt) continue;
+        const int wr = bin[k] >> 7;
+        const int lo = bstart[bin[k]] + (wr == 0 ? 0 : wr == 1 ? w1 : wr == 2 ? w2 : w3);
+        lbuf[lo + slot[k]] = idx[k];
+        slot[k] = lo;
     }
     lds_barrier();
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) {
-        const int j = tid + k * kP2GThreads;
-        if (j >= cnt) break;
-        uint32_t idx;
-        int bin;
-        if (k < kHold) {
-            idx = hidx[k];
-            bin = hbin[k];
-        } else {
-            idx = bkt[j];
-            bin = bin_of(bsb[j]);
-        }
-        const int lo = bstart[bin], hi = bstart[bin + 1];
-        int rank = lo;
-        for (int q = lo; q < hi; ++q) rank += (lbuf[q] < idx) ? 1 : 0;
+        if (k * kP2GThreads >= cnt) break;
+        if (tid + k * kP2GThreads >= cnt) continue;
+        const int lo = slot[k], n = bcnt[bin[k]];
+        int q = 0;   // rank by index within the bin
+        for (int i = 0; i < n; ++i) q += (lbuf[lo + i] < idx[k]) ? 1 : 0;
+        int rank = lo + q;
         if (lay_on) {
             // within layer q and the bin's wave range: the bins before it holding more
             // than q particles
-            const int q = rank - lo, wr = bin >> 7, l = (bin & 127) >> 1;
-            const unsigned long long m0 = lmask[2 * (q * 4 + wr)], m1 = lmask[2 * (q * 4 + wr) + 1];
+            const int wr = bin[k] >> 7, l = (bin[k] & 127) >> 1;
+            const unsigned long long m0 = lmask[2 * (q * kWaves + wr)], m1 = lmask[2 * (q * kWaves + wr) + 1];
             const unsigned long long lt = (1ull << l) - 1ull;
             int pq = __popcll(m0 & lt) + __popcll(m1 & lt);
-            if (bin & 1) pq += (int)((m0 >> l) & 1ull);
-            rank = lay[kLayers * 4 + q * 4 + wr] + pq;
+            if (bin[k] & 1) pq += (int)((m0 >> l) & 1ull);
+            rank = lay[kLayers * kWaves + q * kWaves + wr] + pq;
         }
-        ord[rank] = idx;
-        st_at(d.perm, (uint32_t)(s + rank), idx);
+        ord[rank] = idx[k];
+        st_at(d.perm, (uint32_t)(s + rank), idx[k]);
     }
 }
 
@@ -799,22 +782,16 @@ __device__ __forceinline__ void order_block(const DevCtx &d, int r, int s, int c
 // the set nor the (octant, cell) bins of the block's particles, they sit at consecutive
 // positions in the layered order of the same bins, which this step's order would
 // reproduce exactly (ranks within a bin follow the positions).  The sort then records
-// the block's smallest and largest position instead of filling its bucket; when they
-// span exactly cnt positions the block order is that range (ord and the global
-// permutation are written).  Otherwise -- which a correct change record excludes --
-// the status reports a stale state and false is returned: the block's bucket is empty.
-__device__ __forceinline__ bool kept_block_order(const DevCtx &d, int r, int s, int cnt, uint32_t *ord) {
-    const uint32_t lo = d.blo[r], hi = d.bhi[r];
-    if (cnt <= 0 || hi < lo || hi - lo + 1u != (uint32_t)cnt) {
-        set_status(d.counters, ST_STALE);
-        return false;
-    }
-    for (int j = threadIdx.x; j < cnt; j += kP2GThreads) {
-        ord[j] = lo + (uint32_t)j;
-        st_at(d.perm, (uint32_t)(s + j), lo + (uint32_t)j);
-    }
-    return true;
-}
+// the block's smallest and largest position instead of filling its bucket (blo <= bhi tells
+// the two apart); when they span exactly cnt positions the block order is that range, and
+// P2G and G2P take the particles from it without an order or a permutation.  Otherwise
+// -- which a correct change record excludes -- the status reports a stale state.
+struct BlockOrder {
+    uint32_t lo, hi;
+    __device__ __forceinline__ bool recorded() const { return lo <= hi; }
+    __device__ __forceinline__ bool spans(int cnt) const { return recorded() && hi - lo + 1u == (uint32_t)cnt; }
+};
+__device__ __forceinline__ BlockOrder block_order(const DevCtx &d, int r) { return {d.blo[r], d.bhi[r]}; }
 
 // The four channels of tile node q, converted back from the fixed-point sums.
 __device__ __forceinline__ void tile_values(const TileNode &q, const unsigned long long *tile_m,
@@ -890,13 +867,17 @@ struct MlsTransfer {
 // scatters them.  Otherwise the same tile in the step-global unit: every thread stages
 // and scatters one particle at a time (no unit to agree on first), and the block takes a
 // single pass.
-// reuse: the input is the state the context's previous G2P wrote, so that the order
-// of a block that G2P left unchanged is kept (kept_block_order).
+// The order of a block that the previous G2P left unchanged is kept (BlockOrder).  A
+// block starts with one round trip for everything that its number gives (its place, its
+// range, the record of its order) and one for what those give (the neighbourhood, and the
+// first particles of a kept block or the bucket of another).
+// Measured against a chain of five loads (place, change record, range, positions through
+// LDS, particles), with the order's own gain: k_p2g_carried 11.9 -> 10.6 us at 1,000
+// particles, 157 -> 151 us on the sand column, 514 -> 476 us at 12,000,000 particles.
 template <bool kFixed, class Transfer>
-__device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt, bool reuse) {
+__device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt) {
     __shared__ int bcnt[kBins];                 // counts, then placement cursors
-    __shared__ int bstart[kBins + 1];
-    __shared__ int wsum[kP2GThreads / 64];
+    __shared__ int bstart[kBins];
     __shared__ unsigned int bmax;
     __shared__ int nbr[27];
     __shared__ uint32_t ord[kMaxBlockParticles];   // particle index at each position of the block order
@@ -908,7 +889,6 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
     __shared__ unsigned long long lmask[kLayMaskWords];
     uint32_t *lbuf = reinterpret_cast<uint32_t *>(area);
     const int np = (int)d.counters[C_NPB];
-    const int E = (int)d.counters[C_EPOCH];
     const int tid = threadIdx.x;
     // step-global fixed-point unit (plain mode): 2^(e-39) for the contribution bound in
     // [2^e, 2^(e+1)), so that every contribution is below 2^40 units and a node's sum
@@ -923,20 +903,26 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
         const int vb = d.plist[r];
         int bx, by, bz;
         block_coords(d.geo, vb, bx, by, bz);
-        // the neighbourhood loads while the block is ordered (the ordering's barriers
-        // publish it; the previous block's last reader passed the barrier that ends
-        // its iteration), and is kept for this step's G2P, for every block G2P visits
-        load_neighbours(d, gt, bx, by, bz, nbr, 0, d.nbrs + 27 * (size_t)r);
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
+        const BlockOrder kept = block_order(d, r);
+        const int filled = d.bcount[r];
+        // the neighbourhood loads while the block is ordered or its particles load (the
+        // barriers below publish it; the previous block's last reader passed the barrier
+        // that ends its iteration), and is kept for this step's G2P, for every block G2P
+        // visits
+        load_neighbours(d, gt, bx, by, bz, nbr, 0, d.nbrs + 27 * (size_t)r);
         if (cnt > kMaxBlockParticles) continue;   // reported by the compaction
-        if (reuse && d.bchg[vb] != E) {
-            if (!kept_block_order(d, r, s, cnt, ord)) continue;
-        } else {
-            if (!bucket_full(d, r, cnt)) continue;
-            order_block<true>(d, r, s, cnt, bcnt, bstart, wsum, lbuf, ord, lay, lmask);
+        const bool keep = kept.recorded();
+        if (keep ? !kept.spans(cnt) : filled != cnt) {
+            set_status(d.counters, ST_STALE);
+            continue;
         }
-        lds_barrier();
+        if (!keep && cnt > 0) {
+            order_block(d, r, s, cnt, bcnt, bstart, lbuf, ord, lay, lmask);
+            lds_barrier();
+        }
+        const auto particle = [&](int j) { return keep ? (int)(kept.lo + (uint32_t)j) : (int)ord[j]; };
 
         if (!kFixed) {
             // ---- fixed-point tile with the step-global unit: the bound the preceding G2P
@@ -946,11 +932,11 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
             // without mpm_invalidate) adds to the pool with float atomics instead.
             typename Transfer::Particle st;
             st.on = false;
-            if (tid < cnt) Transfer::stage(d, pa, (int)ord[tid], bx, by, bz, dt, st);
+            if (tid < cnt) Transfer::stage(d, pa, particle(tid), bx, by, bz, dt, st);
             for (int q = tid; q < kTileWords; q += kP2GThreads) area[q] = 0ull;
             lds_barrier();
             for (int j = tid; j < cnt; j += kP2GThreads) {
-                if (j > tid) Transfer::stage(d, pa, (int)ord[j], bx, by, bz, dt, st);
+                if (j > tid) Transfer::stage(d, pa, particle(j), bx, by, bz, dt, st);
                 if (!st.on) continue;
                 const float cb = Transfer::bound(st);
                 seen = fmaxf(seen, cb);
@@ -976,7 +962,7 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
             for (int k = 0; k < 2; ++k) {
                 st[k].on = false;
                 const int j = c0 + tid + k * kP2GThreads;
-                if (j < cnt) stage_particle(d, pa, (int)ord[j], bx, by, bz, dt, st[k]);
+                if (j < cnt) stage_particle(d, pa, particle(j), bx, by, bz, dt, st[k]);
                 bnd = fmaxf(bnd, contribution_bound(st[k]));
             }
             lds_barrier();   // tile cleared, bmax reset
@@ -1012,16 +998,15 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
 
 // Four waves per SIMD (128 VGPRs, none spilled; 40 KiB of LDS, four workgroups per
 // CU): 0.263 ms on the sand column against 0.303 ms at three.
-__global__ void __launch_bounds__(kP2GThreads, 4) k_p2g(DevCtx d, PartArgs pa, float dt, int gp, int gt, int reuse) {
-    b_p2g<false, MlsTransfer<false>>(d, pa, dt, gp, gt, reuse != 0);
+__global__ void __launch_bounds__(kP2GThreads, 4) k_p2g(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_p2g<false, MlsTransfer<false>>(d, pa, dt, gp, gt);
 }
 // the same on a state whose B planes carry Q (the intermediate states of mpm_step)
-__global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_carried(DevCtx d, PartArgs pa, float dt, int gp, int gt,
-                                                                 int reuse) {
-    b_p2g<false, MlsTransfer<true>>(d, pa, dt, gp, gt, reuse != 0);
+__global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_carried(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_p2g<false, MlsTransfer<true>>(d, pa, dt, gp, gt);
 }
-__global__ void __launch_bounds__(kP2GThreads, 3) k_p2g_det(DevCtx d, PartArgs pa, float dt, int gp, int gt, int reuse) {
-    b_p2g<true, MlsTransfer<false>>(d, pa, dt, gp, gt, reuse != 0);
+__global__ void __launch_bounds__(kP2GThreads, 3) k_p2g_det(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_p2g<true, MlsTransfer<false>>(d, pa, dt, gp, gt);
 }
 
 // one launch for many jobs: workgroup row y runs job y (rows of deterministic-mode
@@ -1029,12 +1014,12 @@ __global__ void __launch_bounds__(kP2GThreads, 3) k_p2g_det(DevCtx d, PartArgs p
 __global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_multi(const JobStep *__restrict__ jobs) {
     const JobStep &J = jobs[blockIdx.y];
     if (J.d.det) return;
-    b_p2g<false, MlsTransfer<false>>(J.d, J.pa, J.dt, J.table, J.table, !J.first);
+    b_p2g<false, MlsTransfer<false>>(J.d, J.pa, J.dt, J.table, J.table);
 }
 __global__ void __launch_bounds__(kP2GThreads, 3) k_p2g_det_multi(const JobStep *__restrict__ jobs) {
     const JobStep &J = jobs[blockIdx.y];
     if (!J.d.det) return;
-    b_p2g<true, MlsTransfer<false>>(J.d, J.pa, J.dt, J.table, J.table, !J.first);
+    b_p2g<true, MlsTransfer<false>>(J.d, J.pa, J.dt, J.table, J.table);
 }
 
 // ---------------------------------------------------------------- deterministic P2G sums
@@ -1624,38 +1609,48 @@ struct QuadTransfer {
     }
 };
 
-// The velocity tile of a block's 7^3 nodes, as gather_tile.
+// The velocity tile of a block's 7^3 nodes, as TileGather.
 template <bool kFold>
-__device__ __forceinline__ void quad_gather_tile(const DevCtx &d, float dt, int gp, const int *nbr, int bx, int by, int bz,
-                                                 float *vt) {
-    constexpr int kPer = (kQNodes + kG2PThreads - 1) / kG2PThreads;
-    const float *pool = pool_of(d, gp);
+struct QuadTileGather {
+    static constexpr int kPer = (kQNodes + kG2PThreads - 1) / kG2PThreads;
     float m[kPer], p[kPer][3];
-    bool on[kPer];
-    int t = (int)threadIdx.x;
-    asm volatile("" : "+v"(t));   // the tile coordinates are formed again for every block, not held through it
+    int ph[kPer];
+    int t;
+
+    __device__ __forceinline__ void find(const int *nbr) {
+        t = (int)threadIdx.x;
+        asm volatile("" : "+v"(t));   // the tile coordinates are formed again for every block, not held through it
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const int ni = min(t + k * kG2PThreads, kQNodes - 1);
-        const long long a = pool_index(d, nbr, bx, by, bz, 0, 4 * bx - 1 + ni % 7, 4 * by - 1 + (ni / 7) % 7,
-                                       4 * bz - 1 + ni / 49, 0);
-        on[k] = a >= 0;
-        const float *q = pool + (on[k] ? a : 0);
-        if (kFold) m[k] = q[0];
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) p[k][ch] = q[(1 + ch) * 64];
+        for (int k = 0; k < kPer; ++k) {
+            const int ni = min(t + k * kG2PThreads, kQNodes - 1);
+            ph[k] = nbr[((ni % 7 + 3) >> 2) + 3 * ((ni / 7 % 7 + 3) >> 2) + 9 * ((ni / 49 + 3) >> 2)];
+        }
     }
+    __device__ __forceinline__ void load(const DevCtx &d, int gp) {
+        const float *pool = pool_of(d, gp);
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const int ni = min(t + k * kG2PThreads, kQNodes - 1);
-        float v[3] = {p[k][0], p[k][1], p[k][2]};
-        if (kFold)
-            node_velocity(d, dt, 0, 4 * bx - 1 + ni % 7, 4 * by - 1 + (ni / 7) % 7, 4 * bz - 1 + ni / 49,
-                          on[k] ? m[k] : 0.0f, p[k][0], p[k][1], p[k][2], v);
+        for (int k = 0; k < kPer; ++k) {
+            const int ni = min(t + k * kG2PThreads, kQNodes - 1);
+            const int l = ((ni % 7 + 3) & 3) + 4 * ((ni / 7 % 7 + 3) & 3) + 16 * ((ni / 49 + 3) & 3);
+            const float *q = pool + (size_t)max(ph[k], 0) * kBlockFloats + l;
+            if (kFold) m[k] = q[0];
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) vt[ch * kQNodes + ni] = on[k] ? v[ch] : 0.0f;
+            for (int ch = 0; ch < 3; ++ch) p[k][ch] = q[(1 + ch) * 64];
+        }
     }
-}
+    __device__ __forceinline__ void store(const DevCtx &d, float dt, int bx, int by, int bz, float *vt) {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int ni = min(t + k * kG2PThreads, kQNodes - 1);
+            float v[3] = {p[k][0], p[k][1], p[k][2]};
+            if (kFold)
+                node_velocity(d, dt, 0, 4 * bx - 1 + ni % 7, 4 * by - 1 + (ni / 7) % 7, 4 * bz - 1 + ni / 49,
+                              ph[k] >= 0 ? m[k] : 0.0f, p[k][0], p[k][1], p[k][2], v);
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) vt[ch * kQNodes + ni] = ph[k] >= 0 ? v[ch] : 0.0f;
+        }
+    }
+};
 
 // G2P of one particle: v = sum w v~, Bh = sum w v~ (o - xi)^T, relative to the velocity c
 // of the middle node (the weights sum to one and have zero first moment); the sums over
@@ -1731,13 +1726,15 @@ __device__ __forceinline__ int g2p_split(int np) { return np <= 256 * 6 / 4 ? 2 
 // use of a particle's inputs wait for that particle's loads alone.
 template <bool kCarry, bool kCarried, int kMode>
 __device__ __forceinline__ void g2p_pass(const DevCtx &d, const PartArgs &pa, float dt, const float *vt, int bx,
-                                         int by, int bz, int s, int cnt, uint32_t last, int j0, int step, int E,
-                                         G2PIn &cur, G2PIn &nxt, uint32_t &pnext, int &stay) {
+                                         int by, int bz, int s, int cnt, uint32_t last, BlockOrder kept, bool keep,
+                                         int j0, int step, int E, G2PIn &cur, G2PIn &nxt, uint32_t &pnext,
+                                         int &stay) {
     const int j = j0 + (int)threadIdx.x;
     const bool act = j < cnt;
     if (kCarried) unpack_remainder(d.geo, cur.rp, cur.xr);
     const uint32_t pn = pnext;   // the index first, then the next particle's inputs
-    pnext = ld_at(d.perm, min((uint32_t)(s + j + 2 * step), last));
+    const uint32_t j2 = min((uint32_t)(j + 2 * step), last);
+    pnext = keep ? kept.lo + j2 : ld_at(d.perm, (uint32_t)s + j2);
     g2p_load_index(pa, pn, nxt, kCarried);
     const uint32_t out = (uint32_t)(s + j);
     CellCoord cc;
@@ -1775,61 +1772,70 @@ __device__ __forceinline__ void g2p_pass(const DevCtx &d, const PartArgs &pa, fl
     if (__any(left)) wave_stamp(d, left, cn.c[0] >> 2, cn.c[1] >> 2, cn.c[2] >> 2, E + 1);
 }
 
-// Gathers the velocity tile of block (bx,by,bz) (kTileNodes nodes, three channels) by
-// the workgroup's threads; nodes outside active blocks are at rest.  The loads of all of
-// a thread's nodes are issued before any is used: one memory round trip for the tile.
+// The velocity tile of block (bx,by,bz) (kTileNodes nodes, three channels), gathered by
+// the workgroup's threads in three steps, so that other loads can go out between them:
+// find() takes the pool blocks from the neighbourhood nbr, load() issues the loads of all
+// of a thread's nodes -- one memory round trip for the tile -- and store() writes the
+// velocities; nodes outside active blocks are at rest.
 // kFold: the pool still holds the P2G's momenta, and the grid update is applied to each
 // node as it is gathered.  A node is gathered by 2.7 blocks on average in the interior of
 // a body, but that costs less than the update's own pass over the grid and its launch:
 // sand column, update 11 us + G2P 213.7 us -> G2P 221.5 us; 1,000 particles, a step
 // 47.2 -> 45.1 us; 262,144 particles in deterministic mode, 109 -> 104 us.
 template <bool kFold>
-__device__ __forceinline__ void gather_tile(const DevCtx &d, float dt, int gp, const int *nbr, int bx, int by, int bz,
-                                            float *vt) {
-    constexpr int kPer = (kTileNodes + kG2PThreads - 1) / kG2PThreads;
-    const float *pool = pool_of(d, gp);
+struct TileGather {
+    static constexpr int kPer = (kTileNodes + kG2PThreads - 1) / kG2PThreads;
     float m[kPer], p[kPer][3];
     TileNode q[kPer];
     int ph[kPer];
+
+    __device__ __forceinline__ void find(const int *nbr) {
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        q[k] = tile_entry(kTile.e[min((int)threadIdx.x + k * kG2PThreads, kTileNodes - 1)]);
-        ph[k] = nbr[q[k].nb];
-    }
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const float *a = pool + (size_t)max(ph[k], 0) * kBlockFloats + q[k].at;
-        if (kFold) m[k] = a[0];
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) p[k][ch] = a[(1 + ch) * 64];
-    }
-    // (uniform) no node of the tile lies on a wall
-    const bool inner = kFold && 4 * min(bx, min(by, bz)) - 1 >= max(d.geo.stick_lo[0], d.geo.stick_lo[1]) &&
-                       4 * bx + 4 <= min(d.geo.stick_hi[0][0], d.geo.stick_hi[1][0]) &&
-                       4 * by + 4 <= min(d.geo.stick_hi[0][1], d.geo.stick_hi[1][1]) &&
-                       4 * bz + 4 <= min(d.geo.stick_hi[0][2], d.geo.stick_hi[1][2]);
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        float v[3];
-        if (kFold) {
-            const float mk = ph[k] >= 0 ? m[k] : 0.0f;
-            if (inner) {
-                const float im = fast_rcp(mk);
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch) v[ch] = mk > 0.0f ? p[k][ch] * im + dt * d.gravity[ch] : 0.0f;
-            } else {
-                const int nb = q[k].nb, l = q[k].at & 63;
-                node_velocity(d, dt, q[k].g, 4 * (bx + nb % 3 - 1) + (l & 3), 4 * (by + nb / 3 % 3 - 1) + ((l >> 2) & 3),
-                              4 * (bz + nb / 9 - 1) + (l >> 4), mk, p[k][0], p[k][1], p[k][2], v);
-            }
-        } else {
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) v[ch] = ph[k] >= 0 ? p[k][ch] : 0.0f;
+        for (int k = 0; k < kPer; ++k) {
+            q[k] = tile_entry(kTile.e[min((int)threadIdx.x + k * kG2PThreads, kTileNodes - 1)]);
+            ph[k] = nbr[q[k].nb];
         }
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) vt[ch * kTileNodes + q[k].ni] = v[ch];
     }
-}
+    __device__ __forceinline__ void load(const DevCtx &d, int gp) {
+        const float *pool = pool_of(d, gp);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const float *a = pool + (size_t)max(ph[k], 0) * kBlockFloats + q[k].at;
+            if (kFold) m[k] = a[0];
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) p[k][ch] = a[(1 + ch) * 64];
+        }
+    }
+    __device__ __forceinline__ void store(const DevCtx &d, float dt, int bx, int by, int bz, float *vt) {
+        // (uniform) no node of the tile lies on a wall
+        const bool inner = kFold && 4 * min(bx, min(by, bz)) - 1 >= max(d.geo.stick_lo[0], d.geo.stick_lo[1]) &&
+                           4 * bx + 4 <= min(d.geo.stick_hi[0][0], d.geo.stick_hi[1][0]) &&
+                           4 * by + 4 <= min(d.geo.stick_hi[0][1], d.geo.stick_hi[1][1]) &&
+                           4 * bz + 4 <= min(d.geo.stick_hi[0][2], d.geo.stick_hi[1][2]);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            float v[3];
+            if (kFold) {
+                const float mk = ph[k] >= 0 ? m[k] : 0.0f;
+                if (inner) {
+                    const float im = fast_rcp(mk);
+#pragma unroll
+                    for (int ch = 0; ch < 3; ++ch) v[ch] = mk > 0.0f ? p[k][ch] * im + dt * d.gravity[ch] : 0.0f;
+                } else {
+                    const int nb = q[k].nb, l = q[k].at & 63;
+                    node_velocity(d, dt, q[k].g, 4 * (bx + nb % 3 - 1) + (l & 3),
+                                  4 * (by + nb / 3 % 3 - 1) + ((l >> 2) & 3), 4 * (bz + nb / 9 - 1) + (l >> 4), mk,
+                                  p[k][0], p[k][1], p[k][2], v);
+                }
+            } else {
+#pragma unroll
+                for (int ch = 0; ch < 3; ++ch) v[ch] = ph[k] >= 0 ? p[k][ch] : 0.0f;
+            }
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) vt[ch * kTileNodes + q[k].ni] = v[ch];
+        }
+    }
+};
 
 // kCarry: the output is the carried state for the next P2G of the same step sequence
 // (Q in the B planes, the packed remainder); kCarried: so is the input.  The particle
@@ -1855,29 +1861,40 @@ __device__ __forceinline__ void b_g2p(const DevCtx &d, const PartArgs &pa, float
         block_coords(d.geo, vb, bx, by, bz);
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
+        const BlockOrder kept = block_order(d, r);
+        typename std::conditional<kMode == G2P_QUAD, QuadTileGather<kFold>, TileGather<kFold>>::type tile;
+        if (kKept) tile.find(d.nbrs + 27 * (size_t)r);
         if (tid == 0 && first == 0) block_counts(d, E)[vb] = 0;   // the step's last use of them
         if (cnt <= first || cnt > kMaxBlockParticles) continue;
-        // the first particle's inputs load while the tile is gathered, and the index of
-        // the one after
-        const uint32_t last = (uint32_t)(s + cnt - 1);
-        G2PIn qa, qb;
-        g2p_load_index(pa, ld_at(d.perm, min((uint32_t)(s + first + tid), last)), qa, kCarried);
-        uint32_t pnext = ld_at(d.perm, min((uint32_t)(s + first + tid + step), last));
-        if (kKept) {
-            if (tid < 27) nbr[tid] = d.nbrs[27 * (size_t)r + tid];
-        } else {
+        if (!kKept) {
             load_neighbours(d, gt, bx, by, bz, nbr);
+            lds_barrier();
+            tile.find(nbr);
         }
-        lds_barrier();
-        if (kMode == G2P_QUAD) quad_gather_tile<kFold>(d, dt, gp, nbr, bx, by, bz, vt);
-        else gather_tile<kFold>(d, dt, gp, nbr, bx, by, bz, vt);
+        // the tile's loads go out first, then the first particle's inputs, which wait for
+        // its index, and the index of the particle after it
+        const bool keep = kept.spans(cnt);
+        const uint32_t last = (uint32_t)(cnt - 1);
+        const uint32_t j1 = min((uint32_t)(first + tid), last), j2 = min((uint32_t)(first + tid + step), last);
+        G2PIn qa, qb;
+        uint32_t p0, pnext;
+        if (keep) {
+            p0 = kept.lo + j1;
+            pnext = kept.lo + j2;
+        } else {
+            p0 = ld_at(d.perm, (uint32_t)s + j1);
+            pnext = ld_at(d.perm, (uint32_t)s + j2);
+        }
+        tile.load(d, gp);
+        g2p_load_index(pa, p0, qa, kCarried);
+        tile.store(d, dt, bx, by, bz, vt);
         lds_barrier();
         int stay = 0;   // the wave's particles that stay in the block
         for (int j0 = first; j0 < cnt; j0 += 2 * step) {   // the same trip count for every lane
-            g2p_pass<kCarry, kCarried, kMode>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0, step, E, qa, qb, pnext, stay);
+            g2p_pass<kCarry, kCarried, kMode>(d, pa, dt, vt, bx, by, bz, s, cnt, last, kept, keep, j0, step, E, qa, qb, pnext, stay);
             if (j0 + step < cnt)
-                g2p_pass<kCarry, kCarried, kMode>(d, pa, dt, vt, bx, by, bz, s, cnt, last, j0 + step, step, E, qb, qa, pnext,
-                                           stay);
+                g2p_pass<kCarry, kCarried, kMode>(d, pa, dt, vt, bx, by, bz, s, cnt, last, kept, keep, j0 + step, step, E, qb,
+                                                  qa, pnext, stay);
         }
         if (stay > 0) stamp_block(d, bx, by, bz, stay, E + 1);
         lds_barrier();
@@ -2096,14 +2113,14 @@ struct GradTransfer {
 // As the MLS form: one staged particle per thread in the step-global unit, and kept orders.
 // Bound by the LDS atomics (64 per particle) and their conversions.  500,000 particles: two
 // staged particles per thread (192 VGPRs, two waves per SIMD) in a unit formed for each
-// block, and orders from scratch 63.7 us; this form 47.0 us (128 VGPRs, four waves).
-__global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_grad(DevCtx d, PartArgs pa, float dt, int gp, int gt, int reuse) {
-    b_p2g<false, GradTransfer>(d, pa, dt, gp, gt, reuse != 0);
+// block, and orders from scratch 63.7 us; this form 45.3 us (128 VGPRs, four waves).
+__global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_grad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_p2g<false, GradTransfer>(d, pa, dt, gp, gt);
 }
 
 // As the MLS forms, with the same loop, prefetch and sharing of blocks; three waves per
 // SIMD.  500,000 particles: 56.9 us with all 16 nodes' gradients in full (211 VGPRs, two
-// waves), 39.3 us from separable sums, 41.2 us with the grid update folded in.
+// waves), 39.0 us from separable sums, 40.4 us with the grid update folded in.
 __global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_grad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
     b_g2p<false, false, true, false, G2P_GRAD>(d, pa, dt, gp, gt);
 }
@@ -2114,13 +2131,13 @@ __global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_grad_fold(DevCtx d, Part
 // ---------------------------------------------------------------- quadratic B-spline kernels
 // On the MLS forms' block loops.  Bound by the LDS atomics, 108 per particle.  500,000
 // particles: P2G with two staged particles per thread, a unit formed for each block and
-// orders from scratch 58.0 us, now 54.3 us; three waves per SIMD without spills 55.9 us.
-__global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_quad(DevCtx d, PartArgs pa, float dt, int gp, int gt, int reuse) {
-    b_p2g<false, QuadTransfer>(d, pa, dt, gp, gt, reuse != 0);
+// orders from scratch 58.0 us, now 51.5 us (three waves per SIMD without spills: 1.6 us more).
+__global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_quad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
+    b_p2g<false, QuadTransfer>(d, pa, dt, gp, gt);
 }
 
 // 500,000 particles: 55 us with 27 products and six moments per component (two waves per
-// SIMD), 39.3 us from separable sums (three waves), 39.9 us with the grid update folded in.
+// SIMD), 37.2 us from separable sums (three waves), 38.9 us with the grid update folded in.
 __global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_quad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
     b_g2p<false, false, true, false, G2P_QUAD>(d, pa, dt, gp, gt);
 }
@@ -2132,8 +2149,7 @@ __global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_quad_fold(DevCtx d, Part
 // Order of a block's particles alone (for a G2P that follows a sort without P2G).
 __global__ void __launch_bounds__(kP2GThreads) k_block_order(DevCtx d) {
     __shared__ int bcnt[kBins];
-    __shared__ int bstart[kBins + 1];
-    __shared__ int wsum[kP2GThreads / 64];
+    __shared__ int bstart[kBins];
     __shared__ uint32_t lbuf[kMaxBlockParticles];
     __shared__ uint32_t ord[kMaxBlockParticles];
     __shared__ int lay[kLayWords];
@@ -2146,7 +2162,7 @@ __global__ void __launch_bounds__(kP2GThreads) k_block_order(DevCtx d) {
         const int cnt = d.pstart[r + 1] - s;
         if (cnt > kMaxBlockParticles) continue;
         if (!bucket_full(d, r, cnt)) continue;
-        order_block<true>(d, r, s, cnt, bcnt, bstart, wsum, lbuf, ord, lay, lmask);
+        if (cnt > 0) order_block(d, r, s, cnt, bcnt, bstart, lbuf, ord, lay, lmask);
         lds_barrier();
     }
 }
@@ -2171,8 +2187,7 @@ constexpr int kFNodesM = 343, kFNodesP = 512;
 __global__ void __launch_bounds__(kP2GThreads, 2) k_g2p2g(DevCtx d, PartArgs pa, float dt, int gp_in, int gt_in,
                                                        int gp_out, int gt_out) {
     __shared__ int bcnt[kBins];
-    __shared__ int bstart[kBins + 1];
-    __shared__ int wsum[kP2GThreads / 64];
+    __shared__ int bstart[kBins];
     __shared__ int nbr_in[27], nbr_out[27];
     __shared__ uint32_t ord[kMaxBlockParticles];
     __shared__ float vt[3 * kTileNodes];
@@ -2198,7 +2213,7 @@ __global__ void __launch_bounds__(kP2GThreads, 2) k_g2p2g(DevCtx d, PartArgs pa,
         if (tid == 0) block_counts(d, E)[vb] = 0;   // the step's last use of them
         if (cnt > kMaxBlockParticles) continue;   // reported by the compaction
         if (!bucket_full(d, r, cnt)) continue;
-        order_block<true>(d, r, s, cnt, bcnt, bstart, wsum, lbuf, ord, lay, lmask);
+        if (cnt > 0) order_block(d, r, s, cnt, bcnt, bstart, lbuf, ord, lay, lmask);
         load_neighbours(d, gt_in, bx, by, bz, nbr_in);
         load_neighbours(d, gt_out, bx, by, bz, nbr_out, 64);
         lds_barrier();
@@ -2344,19 +2359,17 @@ void launch_stress(const DevCtx &d, const PartArgs &pa, hipStream_t s) {
     if (pa.n > 0) hipLaunchKernelGGL(k_stress, dim3((pa.n + kThreads - 1) / kThreads), dim3(kThreads), 0, s, d, pa);
 }
 
-void launch_p2g(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt, hipStream_t s, bool carried,
-                bool reuse) {
-    const int ru = reuse ? 1 : 0;
+void launch_p2g(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt, hipStream_t s, bool carried) {
     if (d.quadratic)
-        hipLaunchKernelGGL(k_p2g_quad, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt, ru);
+        hipLaunchKernelGGL(k_p2g_quad, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt);
     else if (d.transfer != 0)
-        hipLaunchKernelGGL(k_p2g_grad, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt, ru);
+        hipLaunchKernelGGL(k_p2g_grad, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt);
     else if (d.det)
-        hipLaunchKernelGGL(k_p2g_det, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt, ru);
+        hipLaunchKernelGGL(k_p2g_det, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt);
     else if (carried)
-        hipLaunchKernelGGL(k_p2g_carried, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt, ru);
+        hipLaunchKernelGGL(k_p2g_carried, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt);
     else
-        hipLaunchKernelGGL(k_p2g, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt, ru);
+        hipLaunchKernelGGL(k_p2g, dim3(particle_grid(d)), dim3(kP2GThreads), 0, s, d, pa, dt, gp, gt);
 }
 
 void launch_det_gather(const DevCtx &d, int gp, int gt, hipStream_t s) {
