@@ -238,7 +238,7 @@ mpm_status enqueue_p2g(mpm_ctx *ctx, const mpm_particles *p, double dt, hipStrea
     const bool carried_in = ready && ctx->carried == pa.in;
     // the G2P records the blocks it changes, so the next P2G may keep the order of the
     // others (the fused step orders the first sort's blocks again from their buckets)
-    const bool keep_orders = physics && ready && !(ctx->cfg.flags & MPM_FLAG_FUSED_G2P2G);
+    const bool keep_orders = physics && ready && !ctx->d.fused;
     if (ev) (void)hipEventRecord(ev[0], s);
     if (!ready) {
         // counts left by a G2P whose keys are not used, or by a sort without a G2P
@@ -252,8 +252,12 @@ mpm_status enqueue_p2g(mpm_ctx *ctx, const mpm_particles *p, double dt, hipStrea
     // below hands to the P2G
     if (physics && (!ready || ctx->d.det)) launch_stress(ctx->d, pa, s);
     const int t = ctx->next_table;
-    launch_compact(ctx->d, t, s);
-    launch_bucket(ctx->d, pa.n, t, t, s, keep_orders, !ready);
+    if (keep_orders && one_sort(ctx->d)) {
+        launch_sort_once(ctx->d, pa.n, t, s);
+    } else {
+        launch_compact(ctx->d, t, s);
+        launch_bucket(ctx->d, pa.n, t, t, s, keep_orders, !ready);
+    }
     ctx->next_table = t ^ 1;
     if (ev) (void)hipEventRecord(ev[1], s);
     if (!physics) {
@@ -310,6 +314,7 @@ void fill_devctx(DevCtx &d, const mpm_config &cfg, const mpm_material *mats, int
     fill_geometry(cfg, d.geo);
     d.quadratic = (cfg.flags & MPM_FLAG_QUADRATIC) ? 1 : 0;
     d.transfer = cfg.transfer;
+    d.fused = (cfg.flags & MPM_FLAG_FUSED_G2P2G) ? 1 : 0;
     for (int i = 0; i < n_mat; ++i) d.mats[i] = dev_material(mats[i]);
     d.n_mat = n_mat;
     for (int a = 0; a < 3; ++a) d.gravity[a] = (float)cfg.gravity[a];
@@ -380,7 +385,6 @@ mpm_status ctx_create(const mpm_config *cfg, const mpm_material *mats, int32_t n
         if (p) ctx->allocs.push_back(p);
         return p;
     });
-    const size_t nb = (size_t)cfg->max_blocks, nv = (size_t)d.nbv;
     if (st == MPM_OK) {
         if (hipHostMalloc((void **)&ctx->host_counters, C_COUNT * sizeof(unsigned int), hipHostMallocDefault) == hipSuccess)
             ctx->host_counters_pinned = true;
@@ -388,15 +392,9 @@ mpm_status ctx_create(const mpm_config *cfg, const mpm_material *mats, int32_t n
             st = MPM_E_OOM;
     }
     if (st == MPM_OK) {
-        bool ok = hipMemsetAsync(d.pflag, 0, 2 * stamp_stride(d.nbv) * sizeof(int), init_stream) == hipSuccess &&
-                  hipMemsetAsync(d.gflag, 0, 2 * stamp_stride(d.nbv) * sizeof(int), init_stream) == hipSuccess &&
-                  hipMemsetAsync(d.page[0], 0xff, nv * sizeof(int), init_stream) == hipSuccess &&
-                  hipMemsetAsync(d.page[1], 0xff, nv * sizeof(int), init_stream) == hipSuccess &&
-                  hipMemsetAsync(d.prank, 0xff, nv * sizeof(int), init_stream) == hipSuccess &&
-                  hipMemsetAsync(d.bchg, 0xff, nv * sizeof(int), init_stream) == hipSuccess &&
-                  hipMemsetAsync(d.pstart, 0, (nb + 1) * sizeof(int), init_stream) == hipSuccess &&
-                  hipMemsetAsync(d.counters, 0, C_COUNT * sizeof(unsigned int), init_stream) == hipSuccess &&
-                  hipMemsetAsync(d.bslots, 0, kBoundWords * sizeof(unsigned int), init_stream) == hipSuccess;
+        (void)hipGetLastError();   // an earlier call's error is not this launch's
+        launch_reset(d, init_stream);
+        bool ok = hipGetLastError() == hipSuccess;
         ok = ok && (device_sync ? hipDeviceSynchronize() : hipStreamSynchronize(init_stream)) == hipSuccess;
         if (!ok) st = MPM_E_HIP;
     }

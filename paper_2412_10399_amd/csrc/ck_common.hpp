@@ -17,6 +17,11 @@ constexpr int kTileMinus = 125;         // G- nodes [4B, 4B+4]^3 touched by the 
 constexpr int kTilePlus = 216;          // G+ nodes [4B-1, 4B+4]^3
 constexpr int kTileNodes = kTileMinus + kTilePlus;
 constexpr int kCompactChunk = 1024;     // virtual blocks per workgroup in the block compaction
+// Chunks up to which one launch sorts (b_sort_once): each workgroup reads every chunk's
+// counts and stamps (8 KiB a chunk).  A step of 1,000
+// particles takes 26.5 / 27.1 / 28.5 / 29.5 us at 1 / 4 / 8 / 12 chunks, with separate
+// launches 30.6 / 31.4 / 31.5 / 32.2 us.
+constexpr int kOneSortChunks = 12;
 constexpr int kIndexBits = 26;          // particle index bits in the packed (cell, index) sort word
 
 enum StatusBits : uint32_t {
@@ -33,7 +38,7 @@ enum Counter : int {
     C_STATUS = 2,   // status bits
     C_EPOCH = 3,    // current activation epoch
     C_MAXPB = 4,    // largest particle count of a block (formed when statistics are asked for)
-    C_SORT = 5,     // epoch of the sort in progress: set by its compaction, made current by its bucketing
+    C_SORT = 5,     // epoch of the sort in progress: set by its compaction, made current by its bucketing or P2G
     C_NGB1 = 6,
     C_BOUND_X = 7,  // P2G contribution bound, as X + dt Y (FP32 bit patterns, maxima from bslots):
     C_BOUND_Y = 8,  //   the stress pass's exact form, or headroom times the previous P2G's largest
@@ -66,6 +71,8 @@ struct DevCtx {
     Geometry geo;
     int quadratic;         // single-grid quadratic B-spline comparison kernel instead of the compact kernel
     int transfer;          // 0 MLS, 1 APIC with exact kernel gradients, 2 PIC
+    int fused;             // steps of the fused transfer, which read their sort's buckets after P2G: nothing
+                           // is kept from sort to sort
     DevMaterial mats[kMaxMaterials];
     int n_mat;
     float gravity[3];
@@ -107,6 +114,8 @@ struct DevCtx {
     unsigned int *bslots;  // [2][kBoundSlots][32]: partial maxima of the contribution bound (X, then Y),
                            // one 128-byte line per slot, reduced into the counters by the bucketing
 };
+
+__host__ __device__ inline bool one_sort(const DevCtx &d) { return d.nbv <= (long long)kOneSortChunks * kCompactChunk; }
 
 // One of the context's two pools, page tables or block lists: a selection between two
 // kernel-argument pointers by a uniform index, which the compiler keeps in scalar
@@ -237,6 +246,34 @@ __host__ __device__ constexpr long long stamp_stride(long long nbv) { return (nb
 // Particle counts of the virtual blocks in a given epoch.
 __device__ __forceinline__ int *block_counts(const DevCtx &d, int epoch) {
     return d.pflag + (epoch & 1) * stamp_stride(d.nbv);
+}
+
+// No particles in the bucket of particle block r, no kept order: the state that a sort fills.
+__device__ __forceinline__ void clear_block_record(const DevCtx &d, int r) {
+    d.bcount[r] = 0;
+    d.blo[r] = 0xffffffffu;
+    d.bhi[r] = 0u;
+}
+
+// Inclusive sums over the wave's lanes, in DPP steps (a __shfl step is an LDS round trip).
+__device__ __forceinline__ int wave_sums(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast 15, 31
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+    return v;
+}
+// Inclusive maxima over the wave's lanes, of v >= 0.
+__device__ __forceinline__ int wave_maxima(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
+    return v;
 }
 
 // For the sort of epoch E: `count` particles in block (bx,by,bz), whose 3 x 3 x 3
@@ -849,10 +886,13 @@ void launch_clear_counts(const DevCtx &d, hipStream_t s);
 void launch_reset(const DevCtx &d, hipStream_t s);
 void launch_stats(const DevCtx &d, hipStream_t s);
 void launch_compact(const DevCtx &d, int table, hipStream_t s);
+// The whole sort in one launch, for a state the context's previous G2P wrote that a P2G
+// follows, on lattices that one_sort() takes.
+void launch_sort_once(const DevCtx &d, int n, int table, hipStream_t s);
 // marked: the keys were computed by launch_flag_keys, which leaves marks in place of the
 // block counts: the blocks' ranges of sorted positions are formed after the bucketing.
-// reuse: as for launch_p2g (blocks whose order the P2G keeps get their position range
-// instead of a filled bucket)
+// reuse: the state is the one the context's previous G2P wrote (a block that G2P left
+// unchanged keeps its order: it gets its position range instead of a filled bucket)
 void launch_bucket(const DevCtx &d, int n, int zero_pool, int zero_table, hipStream_t s, bool reuse = false,
                    bool marked = false);
 void launch_block_sort(const DevCtx &d, hipStream_t s);

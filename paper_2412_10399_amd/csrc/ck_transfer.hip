@@ -655,26 +655,8 @@ constexpr int kLayMaskWords = 2 * kLayers * (kP2GThreads / 64);
 // fixed-point tile
 constexpr int kOrderWords = kMaxBlockParticles * 4 / 8;
 
-// Inclusive sums over the wave's lanes, in DPP steps (a __shfl step is an LDS round trip).
-__device__ __forceinline__ int wave_sums(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast 15, 31
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
-    return v;
-}
 // The wave's largest v >= 0.
-__device__ __forceinline__ int wave_largest(int v) {
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
-    return __builtin_amdgcn_readlane(v, 63);
-}
+__device__ __forceinline__ int wave_largest(int v) { return __builtin_amdgcn_readlane(wave_maxima(v), 63); }
 
 // Orders the particles of block r (count cnt > 0, first sorted position s) in the layered
 // order, or by (half-cell octant, cell, index) when a bin holds more than kLayers: ord[j] =
@@ -786,12 +768,26 @@ __device__ __forceinline__ void order_block(const DevCtx &d, int r, int s, int c
 // the two apart); when they span exactly cnt positions the block order is that range, and
 // P2G and G2P take the particles from it without an order or a permutation.  Otherwise
 // -- which a correct change record excludes -- the status reports a stale state.
+// Where one launch sorts, the record has to be clear before it: P2G clears it once read, and
+// leaves G2P the range's start (kSorted when the order is in the permutation) in the first
+// word of the block's bucket -- on every lattice, since a test for the others cost
+// 1,000 particles more (561 -> 569 us per 20 steps) than it gave the sand column (17.20 -> 17.19 ms).
+// Not where the fused transfer runs, which reads the buckets again: it keeps no order.
+constexpr uint32_t kSorted = 0xffffffffu;
+__device__ __forceinline__ uint32_t &kept_start(const DevCtx &d, int r) { return d.bucket[(size_t)r * kMaxBlockParticles]; }
 struct BlockOrder {
     uint32_t lo, hi;
     __device__ __forceinline__ bool recorded() const { return lo <= hi; }
     __device__ __forceinline__ bool spans(int cnt) const { return recorded() && hi - lo + 1u == (uint32_t)cnt; }
 };
 __device__ __forceinline__ BlockOrder block_order(const DevCtx &d, int r) { return {d.blo[r], d.bhi[r]}; }
+// By P2G, once every wave of the block's workgroup has read the record.
+__device__ __forceinline__ void pass_record(const DevCtx &d, int r, uint32_t start) {
+    if (threadIdx.x == 0 && !d.fused) {
+        if (one_sort(d)) clear_block_record(d, r);
+        kept_start(d, r) = start;
+    }
+}
 
 // The four channels of tile node q, converted back from the fixed-point sums.
 __device__ __forceinline__ void tile_values(const TileNode &q, const unsigned long long *tile_m,
@@ -916,6 +912,8 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
         const bool keep = kept.recorded();
         if (keep ? !kept.spans(cnt) : filled != cnt) {
             set_status(d.counters, ST_STALE);
+            lds_barrier();
+            pass_record(d, r, kSorted);
             continue;
         }
         if (!keep && cnt > 0) {
@@ -935,6 +933,7 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
             if (tid < cnt) Transfer::stage(d, pa, particle(tid), bx, by, bz, dt, st);
             for (int q = tid; q < kTileWords; q += kP2GThreads) area[q] = 0ull;
             lds_barrier();
+            pass_record(d, r, keep ? kept.lo : kSorted);
             for (int j = tid; j < cnt; j += kP2GThreads) {
                 if (j > tid) Transfer::stage(d, pa, particle(j), bx, by, bz, dt, st);
                 if (!st.on) continue;
@@ -953,6 +952,8 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
         // (in deterministic mode a block without valid particles still writes a zero tile)
         unsigned long long *tile_m = area, *tile_p = area + 4 * kTileMStride;
         const int cend = (d.det && cnt == 0) ? 1 : cnt;
+        lds_barrier();
+        pass_record(d, r, keep ? kept.lo : kSorted);
         for (int c0 = 0; c0 < cend; c0 += kChunk) {
             for (int q = tid; q < kTileWords; q += kP2GThreads) area[q] = 0ull;
             if (tid == 0) bmax = 0u;
@@ -989,6 +990,17 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
             }
             lds_barrier();
         }
+    }
+    if (blockIdx.x == 0 && tid == 0) d.counters[C_EPOCH] = d.counters[C_SORT];   // nobody reads it in this launch
+    // what blocks past a capacity leave is not left to a later sort: the counts of those that
+    // no G2P visits (prank -1), the records of those that this loop passed over
+    if (d.counters[C_STATUS] & ST_CAPACITY) {
+        const long long t0 = (long long)blockIdx.x * kP2GThreads + tid, step = (long long)gridDim.x * kP2GThreads;
+        int *pc = block_counts(d, (int)d.counters[C_SORT]);
+        for (long long v = t0; v < d.nbv; v += step)
+            if (pc[v] != 0 && d.prank[v] < 0) pc[v] = 0;
+        for (long long r = t0; r < np; r += step)
+            if (d.pstart[r + 1] - d.pstart[r] > kMaxBlockParticles) clear_block_record(d, (int)r);
     }
     // the next step's unit: kBoundHeadroom times the largest contribution bound of this
     // step (contributions change little from one step to the next; a particle beyond
@@ -1726,7 +1738,7 @@ __device__ __forceinline__ int g2p_split(int np) { return np <= 256 * 6 / 4 ? 2 
 // use of a particle's inputs wait for that particle's loads alone.
 template <bool kCarry, bool kCarried, int kMode>
 __device__ __forceinline__ void g2p_pass(const DevCtx &d, const PartArgs &pa, float dt, const float *vt, int bx,
-                                         int by, int bz, int s, int cnt, uint32_t last, BlockOrder kept, bool keep,
+                                         int by, int bz, int s, int cnt, uint32_t last, uint32_t start, bool keep,
                                          int j0, int step, int E, G2PIn &cur, G2PIn &nxt, uint32_t &pnext,
                                          int &stay) {
     const int j = j0 + (int)threadIdx.x;
@@ -1734,7 +1746,7 @@ __device__ __forceinline__ void g2p_pass(const DevCtx &d, const PartArgs &pa, fl
     if (kCarried) unpack_remainder(d.geo, cur.rp, cur.xr);
     const uint32_t pn = pnext;   // the index first, then the next particle's inputs
     const uint32_t j2 = min((uint32_t)(j + 2 * step), last);
-    pnext = keep ? kept.lo + j2 : ld_at(d.perm, (uint32_t)s + j2);
+    pnext = keep ? start + j2 : ld_at(d.perm, (uint32_t)s + j2);
     g2p_load_index(pa, pn, nxt, kCarried);
     const uint32_t out = (uint32_t)(s + j);
     CellCoord cc;
@@ -1861,7 +1873,7 @@ __device__ __forceinline__ void b_g2p(const DevCtx &d, const PartArgs &pa, float
         block_coords(d.geo, vb, bx, by, bz);
         const int s = d.pstart[r];
         const int cnt = d.pstart[r + 1] - s;
-        const BlockOrder kept = block_order(d, r);
+        const uint32_t start = kept_start(d, r);
         typename std::conditional<kMode == G2P_QUAD, QuadTileGather<kFold>, TileGather<kFold>>::type tile;
         if (kKept) tile.find(d.nbrs + 27 * (size_t)r);
         if (tid == 0 && first == 0) block_counts(d, E)[vb] = 0;   // the step's last use of them
@@ -1873,14 +1885,14 @@ __device__ __forceinline__ void b_g2p(const DevCtx &d, const PartArgs &pa, float
         }
         // the tile's loads go out first, then the first particle's inputs, which wait for
         // its index, and the index of the particle after it
-        const bool keep = kept.spans(cnt);
+        const bool keep = !d.fused && start != kSorted;
         const uint32_t last = (uint32_t)(cnt - 1);
         const uint32_t j1 = min((uint32_t)(first + tid), last), j2 = min((uint32_t)(first + tid + step), last);
         G2PIn qa, qb;
         uint32_t p0, pnext;
         if (keep) {
-            p0 = kept.lo + j1;
-            pnext = kept.lo + j2;
+            p0 = start + j1;
+            pnext = start + j2;
         } else {
             p0 = ld_at(d.perm, (uint32_t)s + j1);
             pnext = ld_at(d.perm, (uint32_t)s + j2);
@@ -1891,9 +1903,9 @@ __device__ __forceinline__ void b_g2p(const DevCtx &d, const PartArgs &pa, float
         lds_barrier();
         int stay = 0;   // the wave's particles that stay in the block
         for (int j0 = first; j0 < cnt; j0 += 2 * step) {   // the same trip count for every lane
-            g2p_pass<kCarry, kCarried, kMode>(d, pa, dt, vt, bx, by, bz, s, cnt, last, kept, keep, j0, step, E, qa, qb, pnext, stay);
+            g2p_pass<kCarry, kCarried, kMode>(d, pa, dt, vt, bx, by, bz, s, cnt, last, start, keep, j0, step, E, qa, qb, pnext, stay);
             if (j0 + step < cnt)
-                g2p_pass<kCarry, kCarried, kMode>(d, pa, dt, vt, bx, by, bz, s, cnt, last, kept, keep, j0 + step, step, E, qb,
+                g2p_pass<kCarry, kCarried, kMode>(d, pa, dt, vt, bx, by, bz, s, cnt, last, start, keep, j0 + step, step, E, qb,
                                                   qa, pnext, stay);
         }
         if (stay > 0) stamp_block(d, bx, by, bz, stay, E + 1);
