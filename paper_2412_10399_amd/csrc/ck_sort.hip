@@ -177,8 +177,9 @@ __device__ __forceinline__ void wg_sum3(int (&a)[3], int *sh) {
 }
 
 constexpr int kPerThread = kCompactChunk / kThreads;   // 4 virtual blocks per thread
-// Chunks of 1,024 blocks up to which one launch does the compaction, every workgroup
-// counting the chunks before its own itself; up to which each emitting workgroup sums the
+// For sorts of a state that no G2P of the context wrote, and grouped jobs: chunks of 1,024
+// blocks up to which one launch does the compaction, every workgroup counting the chunks
+// before its own itself; up to which each emitting workgroup sums the
 // counts of the chunks before its own; above that a scan of the counts stands between.
 // One launch takes 3.5 us at 5 chunks against 3.4 + 3.3 for two, but 10.2 us at 36 chunks
 // against 4.7 + 4.8; the lone workgroup of a scan adds 7 us where the sums are still short.

@@ -1008,8 +1008,9 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
     if (!kFixed) wave_bound(d.bslots, (int)blockIdx.x, kBoundHeadroom * seen, 0.0f);
 }
 
-// Four waves per SIMD (128 VGPRs, none spilled; 40 KiB of LDS, four workgroups per
-// CU): 0.263 ms on the sand column against 0.303 ms at three.
+// Four waves per SIMD (at most 128 VGPRs, none spilled; 27 KiB of LDS, four workgroups per
+// CU): a step's P2G took 0.87 of its time at three on the sand column, where it now takes
+// 0.151 ms on the carried state.
 __global__ void __launch_bounds__(kP2GThreads, 4) k_p2g(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
     b_p2g<false, MlsTransfer<false>>(d, pa, dt, gp, gt);
 }
