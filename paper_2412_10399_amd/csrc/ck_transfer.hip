@@ -183,6 +183,9 @@ __device__ __forceinline__ bool bucket_full(const DevCtx &d, int r, int cnt) {
     return false;
 }
 
+// Whether a block's sorted positions [s, s + cnt) lie in a state of n particles.
+__device__ __forceinline__ bool within(int s, int cnt, int n) { return s <= n - cnt; }
+
 // ---------------------------------------------------------------- block sort
 // Exact stable order of one block's particles by (cell, particle index): counting
 // sort by cell in LDS, then each particle's rank among the equal-cell particles by
@@ -767,13 +770,16 @@ __device__ __forceinline__ void order_block(const DevCtx &d, int r, int s, int c
 // the block's smallest and largest position instead of filling its bucket (blo <= bhi tells
 // the two apart); when they span exactly cnt positions the block order is that range, and
 // P2G and G2P take the particles from it without an order or a permutation.  Otherwise
-// -- which a correct change record excludes -- the status reports a stale state.
+// -- which a correct change record excludes -- the status reports a stale state and the
+// block is rejected (kRejected), as is a block whose bucket does not hold the cnt particles
+// that were counted, or whose positions run past the state's: it has no order, and nothing
+// may follow what its part of the permutation last held (or never held).
 // Where one launch sorts, the record has to be clear before it: P2G clears it once read, and
-// leaves G2P the range's start (kSorted when the order is in the permutation) in the first
-// word of the block's bucket -- on every lattice, since a test for the others cost
+// leaves G2P the range's start (kSorted when the order is in the permutation, kRejected when
+// there is none) in the first word of the block's bucket -- on every lattice, since a test for the others cost
 // 1,000 particles more (561 -> 569 us per 20 steps) than it gave the sand column (17.20 -> 17.19 ms).
 // Not where the fused transfer runs, which reads the buckets again: it keeps no order.
-constexpr uint32_t kSorted = 0xffffffffu;
+constexpr uint32_t kSorted = 0xffffffffu, kRejected = 0xfffffffeu;
 __device__ __forceinline__ uint32_t &kept_start(const DevCtx &d, int r) { return d.bucket[(size_t)r * kMaxBlockParticles]; }
 struct BlockOrder {
     uint32_t lo, hi;
@@ -910,10 +916,10 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
         load_neighbours(d, gt, bx, by, bz, nbr, 0, d.nbrs + 27 * (size_t)r);
         if (cnt > kMaxBlockParticles) continue;   // reported by the compaction
         const bool keep = kept.recorded();
-        if (keep ? !kept.spans(cnt) : filled != cnt) {
+        if ((keep ? !kept.spans(cnt) : filled != cnt) || !within(s, cnt, pa.n)) {
             set_status(d.counters, ST_STALE);
             lds_barrier();
-            pass_record(d, r, kSorted);
+            pass_record(d, r, kRejected);
             continue;
         }
         if (!keep && cnt > 0) {
@@ -1879,6 +1885,9 @@ __device__ __forceinline__ void b_g2p(const DevCtx &d, const PartArgs &pa, float
         if (kKept) tile.find(d.nbrs + 27 * (size_t)r);
         if (tid == 0 && first == 0) block_counts(d, E)[vb] = 0;   // the step's last use of them
         if (cnt <= first || cnt > kMaxBlockParticles) continue;
+        // P2G found no order for the block (the fused transfer's P2G leaves no mark, and its
+        // last G2P follows a sort of its own: the bucket tells)
+        if (d.fused ? d.bcount[r] != cnt || !within(s, cnt, pa.n) : start == kRejected) continue;
         if (!kKept) {
             load_neighbours(d, gt, bx, by, bz, nbr);
             lds_barrier();
@@ -2225,7 +2234,7 @@ __global__ void __launch_bounds__(kP2GThreads, 2) k_g2p2g(DevCtx d, PartArgs pa,
         const int cnt = d.pstart[r + 1] - s;
         if (tid == 0) block_counts(d, E)[vb] = 0;   // the step's last use of them
         if (cnt > kMaxBlockParticles) continue;   // reported by the compaction
-        if (!bucket_full(d, r, cnt)) continue;
+        if (!bucket_full(d, r, cnt) || !within(s, cnt, pa.n)) continue;
         if (cnt > 0) order_block(d, r, s, cnt, bcnt, bstart, lbuf, ord, lay, lmask);
         load_neighbours(d, gt_in, bx, by, bz, nbr_in);
         load_neighbours(d, gt_out, bx, by, bz, nbr_out, 64);
