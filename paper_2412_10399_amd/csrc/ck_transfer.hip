@@ -319,12 +319,13 @@ __global__ void __launch_bounds__(kThreads) k_stress_multi(const JobStep *__rest
 // One workgroup per block, one thread per particle, and the block's 341-node tile
 // in LDS as 64-bit fixed-point integers: LDS float atomics run about 26 times slower
 // than 64-bit integer atomics on gfx950, and integer sums are exact, so the tile is
-// independent of the order of the additions.  A block is scattered in passes of at
-// most kChunk particles, each pass into a cleared tile with its own unit: 2^-39 of
-// the pass's largest contribution bound, so every contribution is below 2^40 units
-// and a node, which takes at most one contribution per particle, sums fewer than
-// kChunk * 2^40 = 2^49 units in a pass -- below 2^51, where the magic-number
-// conversion through FP64 stays exact.  Particles are ordered in layers: layer q holds the q-th particle
+// independent of the order of the additions.  The unit of a tile is 2^-39 of a bound on
+// its largest contribution, so every contribution is below 2^40 units; a node takes at
+// most one contribution per particle, and its sums stay below 2^51, where the
+// magic-number conversion through FP64 stays exact.  Plain MLS takes the bound of the
+// whole state, formed a step ahead, and scatters a block in one pass; deterministic mode
+// and the APIC, PIC and quadratic transfers take that of each pass of at most kChunk of
+// the block's particles.  Particles are ordered in layers: layer q holds the q-th particle
 // (by index) of every nonempty (half-cell octant, cell) bin, and each layer runs in
 // (octant, cell) order.  Within an octant distinct cells have distinct nodes on both
 // grids, and spreading each bin's particles over the layers keeps most lanes of one
@@ -851,12 +852,14 @@ __device__ __forceinline__ double block_scale(float bnd, unsigned int *bmax) {
 }
 
 // What P2G's block loop takes from a transfer: the staged particle, its contribution
-// bound, its scatter into the block's fixed-point tile (kTileWords words) or straight into
-// the pool, and the tile's flush.  This one: MLS on the two staggered grids (kCarried: the
+// bound, its scatter into the block's fixed-point tile (kTileWords words), the tile's flush,
+// and whether the tile is in the step-global unit (kStepUnit; then also the scatter of a
+// particle above the bound straight into the pool).  This one: MLS on the two staggered grids (kCarried: the
 // state between the steps of a sequence).
 template <bool kCarried>
 struct MlsTransfer {
     using Particle = Staged;
+    static constexpr bool kStepUnit = true;
     static constexpr int kTileWords = 4 * (kTileMStride + kTilePStride);   // [4][G-] and [4][G+]
     static __device__ __forceinline__ void stage(const DevCtx &d, const PartArgs &pa, int p, int bx, int by, int bz,
                                                  float dt, Staged &st) {
@@ -881,9 +884,11 @@ struct MlsTransfer {
 // P2G of the particle blocks.  kFixed (deterministic mode): the fixed-point tile,
 // whose sums are exact and so independent of the order of the atomics; each pass
 // stages two particles per thread, takes the block's unit from their bounds, then
-// scatters them.  Otherwise the same tile in the step-global unit: every thread stages
+// scatters them.  Plain MLS: the same tile in the step-global unit; every thread stages
 // and scatters one particle at a time (no unit to agree on first), and the block takes a
-// single pass.
+// single pass.  The other transfers: passes in units of their own, so that a quiet block
+// keeps its bits beside a violent one (a body of 5e8 times smaller contributions: its
+// velocities to 2e-3..9e-2 of the largest in the step-global unit, to 1.4e-6 in its own).
 // The order of a block that the previous G2P left unchanged is kept (BlockOrder).  A
 // block starts with one round trip for everything that its number gives (its place, its
 // range, the record of its order) and one for what those give (the neighbourhood, and the
@@ -945,7 +950,38 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
         }
         const auto particle = [&](int j) { return keep ? (int)(kept.lo + (uint32_t)j) : (int)ord[j]; };
 
-        if (!kFixed) {
+        if constexpr (!kFixed && !Transfer::kStepUnit) {
+            // ---- fixed-point tile in a unit of each pass: every thread stages its (at most
+            // two) particles of the pass for their bounds, the last of them for good, and the
+            // others again to scatter them
+            lds_barrier();
+            pass_record(d, r, keep ? kept.lo : kSorted);
+            for (int c0 = 0; c0 < cnt; c0 += kChunk) {
+                typename Transfer::Particle st;
+                float bnd = 0.0f;
+                const int j0 = c0 + tid, end = min(cnt, c0 + kChunk);
+                st.on = false;
+                for (int j = j0 + kChunk - kP2GThreads; j >= j0; j -= kP2GThreads)
+                    if (j < end) {
+                        Transfer::stage(d, pa, particle(j), bx, by, bz, dt, st);
+                        bnd = fmaxf(bnd, Transfer::bound(st));
+                    }
+                for (int q = tid; q < kTileWords; q += kP2GThreads) area[q] = 0ull;
+                if (tid == 0) bmax = 0u;
+                lds_barrier();   // tile cleared, bmax reset
+                const double S = block_scale(bnd, &bmax);
+                for (int j = j0; j < end; j += kP2GThreads) {
+                    if (j > j0) Transfer::stage(d, pa, particle(j), bx, by, bz, dt, st);
+                    if (st.on) Transfer::scatter(st, bx, by, bz, area, S);
+                }
+                lds_barrier();
+                Transfer::flush(d, pool_of(d, gp), nbr, bx, by, bz, area, 1.0 / S);
+                lds_barrier();
+            }
+            continue;
+        }
+
+        if constexpr (!kFixed && Transfer::kStepUnit) {
             // ---- fixed-point tile with the step-global unit: the bound the preceding G2P
             // (or stress pass) formed over every particle of the state, so that every
             // thread stages and scatters one particle at a time (the first one loads while
@@ -1028,7 +1064,7 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
     // the next step's unit: kBoundHeadroom times the largest contribution bound of this
     // step (contributions change little from one step to the next; a particle beyond
     // the headroom takes the float-atomic path)
-    if (!kFixed) wave_bound(d.bslots, (int)blockIdx.x, kBoundHeadroom * seen, 0.0f);
+    if (!kFixed && Transfer::kStepUnit) wave_bound(d.bslots, (int)blockIdx.x, kBoundHeadroom * seen, 0.0f);
 }
 
 // Four waves per SIMD (at most 128 VGPRs, none spilled; 27 KiB of LDS, four workgroups per
@@ -1584,33 +1620,9 @@ __device__ __forceinline__ void quad_scatter(const QStaged &r, unsigned long lon
         }
 }
 
-// Straight into the pool, for a particle above the step's contribution bound.
-__device__ __forceinline__ void quad_pool(const DevCtx &d, float *pool, const int *nbr, int bx, int by, int bz,
-                                          const QStaged &r) {
-    float w[3][3];
-    quad_weights(r.xi, w);
-    for (int oz = 0; oz < 3; ++oz)
-        for (int oy = 0; oy < 3; ++oy)
-            for (int ox = 0; ox < 3; ++ox) {
-                const float wt = (ox == 0 ? w[0][0] : ox == 1 ? w[0][1] : w[0][2]) *
-                                 (oy == 0 ? w[1][0] : oy == 1 ? w[1][1] : w[1][2]) *
-                                 (oz == 0 ? w[2][0] : oz == 1 ? w[2][1] : w[2][2]);
-                const long long a = pool_index(d, nbr, bx, by, bz, 0, 4 * bx - 1 + r.lb[0] + ox,
-                                               4 * by - 1 + r.lb[1] + oy, 4 * bz - 1 + r.lb[2] + oz, 0);
-                if (a < 0) {
-                    set_status(d.counters, ST_CAPACITY);
-                    continue;
-                }
-                atomicAdd(&pool[a], wt * r.mass);
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    atomicAdd(&pool[a + (1 + c) * 64],
-                              wt * (r.mom0[c] + r.Qc[3 * c] * ox + r.Qc[3 * c + 1] * oy + r.Qc[3 * c + 2] * oz));
-            }
-}
-
 struct QuadTransfer {
     using Particle = QStaged;
+    static constexpr bool kStepUnit = false;
     static constexpr int kTileWords = 4 * kQStride;
     static __device__ __forceinline__ void stage(const DevCtx &d, const PartArgs &pa, int p, int bx, int by, int bz,
                                                  float dt, QStaged &st) {
@@ -1619,10 +1631,6 @@ struct QuadTransfer {
     static __device__ __forceinline__ float bound(const QStaged &st) { return quad_bound(st); }
     static __device__ __forceinline__ void scatter(const QStaged &st, int, int, int, unsigned long long *tile, double S) {
         quad_scatter(st, tile, S);
-    }
-    static __device__ __forceinline__ void direct(const DevCtx &d, float *pool, const int *nbr, int bx, int by, int bz,
-                                                  const QStaged &st) {
-        quad_pool(d, pool, nbr, bx, by, bz, st);
     }
     static __device__ __forceinline__ void flush(const DevCtx &d, float *pool, const int *nbr, int bx, int by, int bz,
                                                  const unsigned long long *tile, double inv) {
@@ -2103,37 +2111,9 @@ __device__ __forceinline__ void grad_scatter(const GStaged &r, int lx, int ly, i
     }
 }
 
-// Straight into the pool, for a particle above the step's contribution bound.
-__device__ __forceinline__ void grad_pool(const DevCtx &d, float *pool, const int *nbr, int bx, int by, int bz,
-                                          const GStaged &r) {
-    float w[2][3][2], dw[2][3][2], m0[2][3];
-    int up[3];
-    grad_axes(r, w, dw, up, m0);
-#pragma unroll
-    for (int g = 0; g < 2; ++g)
-#pragma unroll
-        for (int o = 0; o < 8; ++o) {
-            const int ox = o & 1, oy = (o >> 1) & 1, oz = o >> 2;
-            const int ix = r.c[0] + (g ? up[0] - 1 : 0) + ox, iy = r.c[1] + (g ? up[1] - 1 : 0) + oy,
-                      iz = r.c[2] + (g ? up[2] - 1 : 0) + oz;
-            const long long a = pool_index(d, nbr, bx, by, bz, g, ix, iy, iz, 0);
-            if (a < 0) {
-                set_status(d.counters, ST_CAPACITY);
-                continue;
-            }
-            const float wx = w[g][0][ox], wy = w[g][1][oy], wz = w[g][2][oz], wt = wx * wy * wz;
-            const float gx = dw[g][0][ox] * wy * wz, gy = wx * dw[g][1][oy] * wz, gz = wx * wy * dw[g][2][oz];
-            atomicAdd(&pool[a], wt * r.mass);
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-                atomicAdd(&pool[a + (1 + c) * 64],
-                          wt * (m0[g][c] + ox * r.Q[3 * c] + oy * r.Q[3 * c + 1] + oz * r.Q[3 * c + 2]) +
-                              r.T[3 * c] * gx + r.T[3 * c + 1] * gy + r.T[3 * c + 2] * gz);
-        }
-}
-
 struct GradTransfer {
     using Particle = GStaged;
+    static constexpr bool kStepUnit = false;
     static constexpr int kTileWords = MlsTransfer<false>::kTileWords;
     static __device__ __forceinline__ void stage(const DevCtx &d, const PartArgs &pa, int p, int bx, int by, int bz,
                                                  float dt, GStaged &st) {
@@ -2144,20 +2124,16 @@ struct GradTransfer {
                                                    double S) {
         grad_scatter(st, st.c[0] - 4 * bx, st.c[1] - 4 * by, st.c[2] - 4 * bz, tile, tile + 4 * kTileMStride, S);
     }
-    static __device__ __forceinline__ void direct(const DevCtx &d, float *pool, const int *nbr, int bx, int by, int bz,
-                                                  const GStaged &st) {
-        grad_pool(d, pool, nbr, bx, by, bz, st);
-    }
     static __device__ __forceinline__ void flush(const DevCtx &d, float *pool, const int *nbr, int, int, int,
                                                  const unsigned long long *tile, double inv) {
         flush_tile(d, pool, nbr, tile, tile + 4 * kTileMStride, inv);
     }
 };
 
-// As the MLS form: one staged particle per thread in the step-global unit, and kept orders.
+// One staged particle per thread and kept orders, as the MLS form, in a unit of each pass.
 // Bound by the LDS atomics (64 per particle) and their conversions.  500,000 particles: two
-// staged particles per thread (192 VGPRs, two waves per SIMD) in a unit formed for each
-// block, and orders from scratch 63.7 us; this form 45.3 us (128 VGPRs, four waves).
+// staged particles per thread (192 VGPRs, two waves per SIMD) and orders from scratch
+// 63.7 us; this form, which stages half of the particles twice, 50.4 us (128 VGPRs, four waves).
 __global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_grad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
     b_p2g<false, GradTransfer>(d, pa, dt, gp, gt);
 }
@@ -2174,8 +2150,8 @@ __global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_grad_fold(DevCtx d, Part
 
 // ---------------------------------------------------------------- quadratic B-spline kernels
 // On the MLS forms' block loops.  Bound by the LDS atomics, 108 per particle.  500,000
-// particles: P2G with two staged particles per thread, a unit formed for each block and
-// orders from scratch 58.0 us, now 51.5 us (three waves per SIMD without spills: 1.6 us more).
+// particles: P2G with two staged particles per thread and orders from scratch 58.0 us, with
+// one at a time, half of them staged twice, and kept orders 55.4 us (111 VGPRs, four waves).
 __global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_quad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
     b_p2g<false, QuadTransfer>(d, pa, dt, gp, gt);
 }
