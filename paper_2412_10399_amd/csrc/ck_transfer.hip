@@ -926,7 +926,7 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
         int bx, by, bz;
         block_coords(d.geo, vb, bx, by, bz);
         const int s = d.pstart[r];
-        const int cnt = d.pstart[r + 1] - s;
+        int cnt = d.pstart[r + 1] - s;
         const BlockOrder kept = block_order(d, r);
         const int filled = d.bcount[r];
         // the neighbourhood loads while the block is ordered or its particles load (the
@@ -934,11 +934,17 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
         // that ends its iteration), and is kept for this step's G2P, for every block G2P
         // visits
         load_neighbours(d, gt, bx, by, bz, nbr, 0, d.nbrs + 27 * (size_t)r);
-        if (cnt > kMaxBlockParticles) continue;   // reported by the compaction
         const bool keep = kept.recorded();
         // (bit operations: one test of a value per thread; with && the compiler spilled 11 VGPRs)
         const bool whole = within(s, cnt, pa.n) & (keep ? kept.spans(cnt) : filled == cnt);
-        if (!whole) {
+        if constexpr (kFixed) {
+            // the gather sums the tile of every block that holds particles: a block left out
+            // writes a zero tile as one without valid particles does
+            if (!whole && cnt <= kMaxBlockParticles) set_status(d.counters, ST_STALE);
+            cnt = whole && cnt <= kMaxBlockParticles ? cnt : 0;
+        }
+        if (cnt > kMaxBlockParticles) continue;   // reported by the compaction
+        if (!kFixed && !whole) {
             set_status(d.counters, ST_STALE);
             lds_barrier();
             pass_record(d, r, kRejected);
@@ -1010,9 +1016,9 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
         // ---- fixed-point tile, kChunk particles per pass (one pass unless the block is dense)
         // (in deterministic mode a block without valid particles still writes a zero tile)
         unsigned long long *tile_m = area, *tile_p = area + 4 * kTileMStride;
-        const int cend = (d.det && cnt == 0) ? 1 : cnt;
+        const int cend = cnt == 0 ? 1 : cnt;
         lds_barrier();
-        pass_record(d, r, keep ? kept.lo : kSorted);
+        pass_record(d, r, !whole ? kRejected : keep ? kept.lo : kSorted);
         for (int c0 = 0; c0 < cend; c0 += kChunk) {
             for (int q = tid; q < kTileWords; q += kP2GThreads) area[q] = 0ull;
             if (tid == 0) bmax = 0u;

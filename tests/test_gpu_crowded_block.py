@@ -119,3 +119,27 @@ def test_crowded_job_fails_alone(grouped):
         assert srv.info(j).state == ckmpm.MPM_JOB_DONE
         _match(srv.read(j), st, "job beside a crowded one (%s)" % ("grouped" if grouped else "per job"))
     srv.close()
+
+
+def test_deterministic_grid_beside_a_crowded_block():
+    """The crowded block contributes nothing to the grid, and not what its place in the staging area last held."""
+    n_cells = (32, 32, 32)
+    crowded, ids = _crowded(n_cells)
+    sc = _bodies(n_cells)
+    run = GpuRun(crowded, deterministic=True)
+    ck, p = run.ck, run.parts
+    fewer = crowded.copy()
+    keep = np.sort(np.concatenate([ids, np.setdiff1d(np.arange(crowded.n), ids)[:500]]))
+    p.c.n = p.n = keep.size
+    p.load(*(getattr(fewer, name)[keep] for name in ("x", "v", "B", "F")))
+    ck.check(ck.mpm_p2g(run.ctx.h, p.c, sc.dt, run.stream))
+    assert run.grids()[0].sum() > 1.2 * sc.n * sc.materials[0].rho * sc.materials[0].vol0
+    p.c.n = p.n = crowded.n
+    p.load(crowded.x, crowded.v, crowded.B, crowded.F)
+    ck.check(ck.mpm_invalidate(run.ctx.h))
+    ck.check(ck.mpm_p2g(run.ctx.h, p.c, sc.dt, run.stream))
+    m, mom = run.grids()
+    assert ck.mpm_sync(run.ctx.h, run.stream) == ck.MPM_E_CAPACITY
+    _, g = oracle_step(sc, oracle_state(dict(x=sc.x, v=sc.v, B=sc.B, F=sc.F)), sc.dt)
+    assert nerr(m, g["m"]) <= TOL and nerr(mom, g["p"]) <= TOL
+    run.close()
