@@ -879,7 +879,7 @@ struct Allocator {
 };
 
 void launch_flag_keys(const DevCtx &d, const PartArgs &pa, int epoch_offset, hipStream_t s);
-// Zeroes the block counts of both epochs: before keys are computed afresh.
+// Zeroes the block counts of both epochs and the grid stamps: before keys are computed afresh.
 void launch_clear_counts(const DevCtx &d, hipStream_t s);
 // Puts the buffers of a context into the state a new one starts from, and its statistics
 // into the counters.

@@ -112,11 +112,15 @@ __global__ void __launch_bounds__(1024) k_bucket_scan(DevCtx d) {
     if (threadIdx.x == 1023) d.pstart[np] = run;
 }
 
+// The stamps go too: the last G2P made those of the epoch that is about to be sorted, for the
+// particles it wrote.
 __global__ void k_clear_counts(DevCtx d) {
     const long long n = 2 * stamp_stride(d.nbv) / 4;
-    int4 *c = reinterpret_cast<int4 *>(d.pflag);
-    for (long long v = blockIdx.x * (long long)blockDim.x + threadIdx.x; v < n; v += (long long)gridDim.x * blockDim.x)
+    int4 *c = reinterpret_cast<int4 *>(d.pflag), *g = reinterpret_cast<int4 *>(d.gflag);
+    for (long long v = blockIdx.x * (long long)blockDim.x + threadIdx.x; v < n; v += (long long)gridDim.x * blockDim.x) {
         c[v] = make_int4(0, 0, 0, 0);
+        if (v < n / 2) g[v] = make_int4(0, 0, 0, 0);
+    }
     if (one_sort(d))
         for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < d.max_blocks; r += gridDim.x * blockDim.x) clear_block_record(d, r);
 }
