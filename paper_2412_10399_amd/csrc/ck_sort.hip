@@ -183,12 +183,16 @@ __device__ __forceinline__ void wg_sum3(int (&a)[3], int *sh) {
 constexpr int kPerThread = kCompactChunk / kThreads;   // 4 virtual blocks per thread
 // For sorts of a state that no G2P of the context wrote, and grouped jobs: chunks of 1,024
 // blocks up to which one launch does the compaction, every workgroup counting the chunks
-// before its own itself; up to which each emitting workgroup sums the
-// counts of the chunks before its own; above that a scan of the counts stands between.
+// before its own itself; for every sort on larger lattices those up to which each emitting
+// workgroup sums the counts of the chunks before its own; above that a scan of the counts
+// stands between.
 // One launch takes 3.5 us at 5 chunks against 3.4 + 3.3 for two, but 10.2 us at 36 chunks
-// against 4.7 + 4.8; the lone workgroup of a scan adds 7 us where the sums are still short.
+// against 4.7 + 4.8.  A step of 1,000 particles with sums / with the lone workgroup of a
+// scan: 34.7 / 38.5 us at 892 chunks, 45.6 / 52.0 at 4,076, 60.6 / 66.0 at 7,021, 123.6 /
+// 135.4 at 16,577, 318 / 307 at 32,301 and 927 / 573 at 62,970 (the sums' work grows with
+// the square).
 constexpr int kSingleChunks = 12;
-constexpr int kPrefixChunks = 4096;
+constexpr int kPrefixChunks = 24576;
 
 // Particle counts and grid flags (stamp == E) of the kPerThread consecutive virtual blocks
 // from `base`, each array in one 16-byte load (both arrays are 256-byte aligned and padded
