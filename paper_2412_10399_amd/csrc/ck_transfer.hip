@@ -324,8 +324,8 @@ __global__ void __launch_bounds__(kThreads) k_stress_multi(const JobStep *__rest
 // most one contribution per particle, and its sums stay below 2^51, where the
 // magic-number conversion through FP64 stays exact.  Plain MLS takes the bound of the
 // whole state, formed a step ahead, and scatters a block in one pass; deterministic mode
-// and the APIC, PIC and quadratic transfers take that of each pass of at most kChunk of
-// the block's particles.  Particles are ordered in layers: layer q holds the q-th particle
+// and the APIC, PIC and quadratic transfers take that of every kChunk of the block's
+// particles.  Particles are ordered in layers: layer q holds the q-th particle
 // (by index) of every nonempty (half-cell octant, cell) bin, and each layer runs in
 // (octant, cell) order.  Within an octant distinct cells have distinct nodes on both
 // grids, and spreading each bin's particles over the layers keeps most lanes of one
@@ -841,13 +841,18 @@ __device__ __forceinline__ void flush_tile(const DevCtx &d, float *pool, const i
 }
 
 // Reduces a per-thread contribution bound over the workgroup (bmax in LDS, reset by
-// the caller before the preceding barrier) and returns the fixed-point scale.
-__device__ __forceinline__ double block_scale(float bnd, unsigned int *bmax) {
+// the caller before the preceding barrier); clears `next` on the way, if given.
+__device__ __forceinline__ float block_bound(float bnd, unsigned int *bmax, unsigned int *next = nullptr) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) bnd = fmaxf(bnd, __shfl_xor(bnd, off));
     if ((threadIdx.x & 63) == 0) atomicMax(bmax, __float_as_uint(bnd));
+    if (next && threadIdx.x == 0) *next = 0u;
     lds_barrier();
-    const float m = __uint_as_float(*bmax);
+    return __int_as_float(__builtin_amdgcn_readfirstlane((int)*bmax));
+}
+// The same as the fixed-point scale.
+__device__ __forceinline__ double block_scale(float bnd, unsigned int *bmax) {
+    const float m = block_bound(bnd, bmax);
     return m > 0.0f ? ldexp(1.0, 39 - ilogbf(m)) : 1.0;
 }
 
@@ -886,9 +891,9 @@ struct MlsTransfer {
 // stages two particles per thread, takes the block's unit from their bounds, then
 // scatters them.  Plain MLS: the same tile in the step-global unit; every thread stages
 // and scatters one particle at a time (no unit to agree on first), and the block takes a
-// single pass.  The other transfers: passes in units of their own, so that a quiet block
-// keeps its bits beside a violent one (a body of 5e8 times smaller contributions: its
-// velocities to 2e-3..9e-2 of the largest in the step-global unit, to 1.4e-6 in its own).
+// single pass.  The other transfers: units of their own, so that a quiet block keeps its
+// bits beside a violent one (a body of 5e8 times smaller contributions: its velocities to
+// 2e-3..9e-2 of the largest in the step-global unit, to 1.4e-6 in its own).
 // The order of a block that the previous G2P left unchanged is kept (BlockOrder).  A
 // block starts with one round trip for everything that its number gives (its place, its
 // range, the record of its order) and one for what those give (the neighbourhood, and the
@@ -900,7 +905,8 @@ template <bool kFixed, class Transfer>
 __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float dt, int gp, int gt) {
     __shared__ int bcnt[kBins];                 // counts, then placement cursors
     __shared__ int bstart[kBins];
-    __shared__ unsigned int bmax;
+    __shared__ unsigned int bmax3[3];
+    unsigned int &bmax = bmax3[0];
     __shared__ int nbr[27];
     __shared__ uint32_t ord[kMaxBlockParticles];   // particle index at each position of the block order
     // ordering buffer, then the fixed-point tile
@@ -957,32 +963,41 @@ __device__ __forceinline__ void b_p2g(const DevCtx &d, const PartArgs &pa, float
         const auto particle = [&](int j) { return keep ? (int)(kept.lo + (uint32_t)j) : (int)ord[j]; };
 
         if constexpr (!kFixed && !Transfer::kStepUnit) {
-            // ---- fixed-point tile in a unit of each pass: every thread stages its (at most
-            // two) particles of the pass for their bounds, the last of them for good, and the
-            // others again to scatter them
+            // ---- fixed-point tile in a unit of its own for every kChunk particles: one
+            // particle per thread and round, the unit that of the largest bound so far (2^(e-39)
+            // for bounds in [2^e, 2^(e+1))); when a round needs a larger one, the sums are
+            // taken over into it
+            if (tid < 2) bmax3[tid] = 0u;   // (the third is cleared by the first round)
             lds_barrier();
             pass_record(d, r, keep ? kept.lo : kSorted);
-            for (int c0 = 0; c0 < cnt; c0 += kChunk) {
+            int e = 0;
+            bool fresh = true;   // nothing in the tile
+            for (int c0 = 0, round = 0; c0 < cnt; c0 += kP2GThreads, round = round == 2 ? 0 : round + 1) {
                 typename Transfer::Particle st;
-                float bnd = 0.0f;
-                const int j0 = c0 + tid, end = min(cnt, c0 + kChunk);
                 st.on = false;
-                for (int j = j0 + kChunk - kP2GThreads; j >= j0; j -= kP2GThreads)
-                    if (j < end) {
-                        Transfer::stage(d, pa, particle(j), bx, by, bz, dt, st);
-                        bnd = fmaxf(bnd, Transfer::bound(st));
-                    }
-                for (int q = tid; q < kTileWords; q += kP2GThreads) area[q] = 0ull;
-                if (tid == 0) bmax = 0u;
-                lds_barrier();   // tile cleared, bmax reset
-                const double S = block_scale(bnd, &bmax);
-                for (int j = j0; j < end; j += kP2GThreads) {
-                    if (j > j0) Transfer::stage(d, pa, particle(j), bx, by, bz, dt, st);
-                    if (st.on) Transfer::scatter(st, bx, by, bz, area, S);
+                if (c0 + tid < cnt) Transfer::stage(d, pa, particle(c0 + tid), bx, by, bz, dt, st);
+                if (c0 % kChunk == 0) {
+                    for (int q = tid; q < kTileWords; q += kP2GThreads) area[q] = 0ull;
+                    fresh = true;
                 }
-                lds_barrier();
-                Transfer::flush(d, pool_of(d, gp), nbr, bx, by, bz, area, 1.0 / S);
-                lds_barrier();
+                // the words take turns: the one of the next round was last read before the
+                // barrier of the round before
+                const float bnd = block_bound(Transfer::bound(st), &bmax3[round], &bmax3[round == 2 ? 0 : round + 1]);
+                const int en = bnd > 0.0f ? min(ilogbf(bnd), 128) : e;   // (at most 2^128, also for an infinite one)
+                if (!fresh && en > e) {
+                    const int k = min(en - e, 63);
+                    for (int q = tid; q < kTileWords; q += kP2GThreads)
+                        area[q] = (unsigned long long)(((long long)area[q] + (1ll << (k - 1))) >> k);
+                    lds_barrier();
+                }
+                if (fresh || en > e) e = en;
+                fresh = fresh && !(bnd > 0.0f);
+                if (st.on) Transfer::scatter(st, bx, by, bz, area, ldexp(1.0, 39 - e));
+                if (c0 % kChunk == kChunk - kP2GThreads || c0 + kP2GThreads >= cnt) {
+                    lds_barrier();
+                    Transfer::flush(d, pool_of(d, gp), nbr, bx, by, bz, area, ldexp(1.0, e - 39));
+                    lds_barrier();
+                }
             }
             continue;
         }
@@ -2136,10 +2151,12 @@ struct GradTransfer {
     }
 };
 
-// One staged particle per thread and kept orders, as the MLS form, in a unit of each pass.
-// Bound by the LDS atomics (64 per particle) and their conversions.  500,000 particles: two
-// staged particles per thread (192 VGPRs, two waves per SIMD) and orders from scratch
-// 63.7 us; this form, which stages half of the particles twice, 50.4 us (128 VGPRs, four waves).
+// One staged particle per thread and kept orders, as the MLS form, in units of the block's
+// own.  Bound by the LDS atomics (64 per particle) and their conversions.  500,000
+// particles: two staged particles per thread (192 VGPRs, two waves per SIMD) and orders from
+// scratch 63.7 us; one at a time, each staged a second time to scatter it once the unit of
+// 512 was known, 50.4 us (and 1.2 times slower on 4,000,000 particles in random order); with
+// a unit that grows from round to round 46.5 us (128 VGPRs, four waves).
 __global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_grad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
     b_p2g<false, GradTransfer>(d, pa, dt, gp, gt);
 }
@@ -2157,7 +2174,7 @@ __global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_grad_fold(DevCtx d, Part
 // ---------------------------------------------------------------- quadratic B-spline kernels
 // On the MLS forms' block loops.  Bound by the LDS atomics, 108 per particle.  500,000
 // particles: P2G with two staged particles per thread and orders from scratch 58.0 us, with
-// one at a time, half of them staged twice, and kept orders 55.4 us (111 VGPRs, four waves).
+// one at a time, kept orders and a unit that grows from round to round 54.1 us.
 __global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_quad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
     b_p2g<false, QuadTransfer>(d, pa, dt, gp, gt);
 }

@@ -52,3 +52,30 @@ def test_each_body_in_its_own_units(kind, steps):
         for k, e in errs.items():
             assert e <= TOL, (body, k)
     run.close()
+
+
+@pytest.mark.parametrize("kind", sorted(KINDS))
+@pytest.mark.parametrize("n", [200, 300, 513, 1500, 2048])
+def test_unit_grows_within_a_block(kind, n):
+    """One block, whose particles in the upper halves of the cells along z (the later rounds of a pass) move 1e6 times
+    faster: the sums of the first rounds are taken over into the larger unit."""
+    sc = scenes.random_blob(73, n_cells=(16, 16, 16), model=scenes.FIXED_COROTATED, dt=1e-5, E=1e4, B_scale=0.0, F_scale=1e-3)
+    rng = np.random.default_rng(n)
+    X = 4.0 + 3.7 * rng.random((n, 3))
+    sc.x = (X * sc.dx).astype(np.float32)
+    up = ((X[:, 2] + 0.25) % 1.0) >= 0.5
+    sc.v = (np.where(up, 10.0, 1e-5)[:, None] * (1.0 + rng.random((n, 3)))).astype(np.float32)
+    sc.B = np.zeros((n, 3, 3), np.float32)
+    sc.F = (np.eye(3)[None] + 1e-3 * rng.standard_normal((n, 3, 3))).astype(np.float32)
+    sc.mat = np.zeros(n, np.uint8)
+    run = GpuRun(sc, **KINDS[kind])
+    got = run.phase_step(sc.dt)
+    assert got["status"] == 0
+    st = oracle_state(dict(x=sc.x, v=sc.v, B=sc.B, F=sc.F))
+    g = _oracle_step(kind, sc, st, sc.dt)
+    q = 0 if kind == "quadratic" else slice(None)
+    errs = dict(m=nerr(got["m"][q], g["m"]), p=nerr(got["p"][q], g["p"]), v=nerr(got["v"], st.v), F=nerr(got["F"], st.F))
+    log("%s %d particles: %s" % (kind, n, " ".join("%s=%.2e" % e for e in errs.items())))
+    for k, e in errs.items():
+        assert e <= TOL, k
+    run.close()
