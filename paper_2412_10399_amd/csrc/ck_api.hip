@@ -677,10 +677,9 @@ mpm_status mpm_invalidate(mpm_ctx *ctx) {
 mpm_status mpm_get_stats(mpm_ctx *ctx, mpm_stats *out, void *stream) {
     if (!ctx || !out) return MPM_E_INVALID;
     DeviceGuard g(ctx->device);
-    launch_stats(ctx->d, (hipStream_t)stream);
     if (hipStreamSynchronize((hipStream_t)stream) != hipSuccess) return MPM_E_HIP;
-    if (hipMemcpy(ctx->host_counters, ctx->d.counters, C_COUNT * sizeof(unsigned int), hipMemcpyDeviceToHost) != hipSuccess)
-        return MPM_E_HIP;
+    launch_stats(ctx->d, ctx->host_counters, nullptr);   // after every blocking stream's work, as a copy would be
+    if (last_error() != MPM_OK || hipStreamSynchronize(nullptr) != hipSuccess) return MPM_E_HIP;
     out->n_particle_blocks = ctx->host_counters[C_NPB];
     out->n_grid_blocks = ctx->host_counters[ngb_slot(ctx->grid_table)];
     out->max_block_particles = ctx->host_counters[C_MAXPB];

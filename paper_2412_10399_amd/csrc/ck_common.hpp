@@ -881,10 +881,11 @@ struct Allocator {
 void launch_flag_keys(const DevCtx &d, const PartArgs &pa, int epoch_offset, hipStream_t s);
 // Zeroes the block counts of both epochs and the grid stamps: before keys are computed afresh.
 void launch_clear_counts(const DevCtx &d, hipStream_t s);
-// Puts the buffers of a context into the state a new one starts from, and its statistics
-// into the counters.
+// Puts the buffers of a context into the state a new one starts from.
 void launch_reset(const DevCtx &d, hipStream_t s);
-void launch_stats(const DevCtx &d, hipStream_t s);
+// The counters, with the largest particle count of a block, to C_COUNT words of pinned host
+// memory.
+void launch_stats(const DevCtx &d, unsigned int *out, hipStream_t s);
 void launch_compact(const DevCtx &d, int table, hipStream_t s);
 // The whole sort in one launch, for a state the context's previous G2P wrote that a P2G
 // follows, on lattices that one_sort() takes.

@@ -146,9 +146,10 @@ __global__ void k_reset(DevCtx d) {
     if (t0 < C_COUNT) d.counters[t0] = 0u;
 }
 
-// Largest particle count of a block (one workgroup; the counters' other entries are
-// formed by the steps).
-__global__ void __launch_bounds__(1024) k_stats(DevCtx d) {
+// The counters to `out` (pinned host memory: the caller waits for the stream alone, 38 us
+// against 23 with a copy after the wait), with the largest particle count of a block (the
+// other entries are formed by the steps).  One workgroup.
+__global__ void __launch_bounds__(1024) k_stats(DevCtx d, unsigned int *out) {
     __shared__ int m;
     if (threadIdx.x == 0) m = 0;
     __syncthreads();
@@ -157,7 +158,7 @@ __global__ void __launch_bounds__(1024) k_stats(DevCtx d) {
     for (int r = threadIdx.x; r < np; r += 1024) mx = max(mx, d.pstart[r + 1] - d.pstart[r]);
     atomicMax(&m, mx);
     __syncthreads();
-    if (threadIdx.x == 0) d.counters[C_MAXPB] = (unsigned)m;
+    if (threadIdx.x < C_COUNT) out[threadIdx.x] = threadIdx.x == C_MAXPB ? (unsigned)m : d.counters[threadIdx.x];
 }
 
 // Workgroup-wide sums of three counters (256 threads).
@@ -763,7 +764,9 @@ void launch_reset(const DevCtx &d, hipStream_t s) {
     hipLaunchKernelGGL(k_reset, dim3((unsigned)std::min<long long>(wgs, 1024)), dim3(256), 0, s, d);
 }
 
-void launch_stats(const DevCtx &d, hipStream_t s) { hipLaunchKernelGGL(k_stats, dim3(1), dim3(1024), 0, s, d); }
+void launch_stats(const DevCtx &d, unsigned int *out, hipStream_t s) {
+    hipLaunchKernelGGL(k_stats, dim3(1), dim3(1024), 0, s, d, out);
+}
 
 void launch_compact(const DevCtx &d, int table, hipStream_t s) {
     const int nchunks = (int)((d.nbv + kCompactChunk - 1) / kCompactChunk);
