@@ -504,10 +504,10 @@ __device__ __forceinline__ void b_bucket_count(const DevCtx &d, int n, int zero_
     const int tid = threadIdx.x, lane = wave_lane(), w = tid >> 6;
     const int E = (int)d.counters[C_SORT];   // the epoch of this sort
     int *pc = block_counts(d, E);
-    // the tile, each XCD taking a contiguous eighth of them
-    const int per = ((n + kCountTile - 1) / kCountTile + 7) >> 3;
-    const int tile = (int)(blockIdx.x >> 3) < per ? (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3) : -1;
-    const int base = tile >= 0 ? tile * kCountTile : n;
+    // the tile in launch order: with a contiguous eighth for each XCD, rows of a state in creation
+    // order met at their blocks' counters at once (32.2 us against 23.3 at 300,000 particles,
+    // 38.7 / 31.9 at 1,000,000, 107 / 113 at 4,200,000; a state in block order takes the same)
+    const int base = (int)blockIdx.x < (n + kCountTile - 1) / kCountTile ? (int)blockIdx.x * kCountTile : n;
     const int i0 = base + tid * kCountPer;
     uint32_t vb[kCountPer];
     // the thread's 4 keys in one 16-byte load (the library's buffers are 256-byte
