@@ -659,6 +659,37 @@ __device__ __forceinline__ int ad_tile_base(const AdTile &t, const AdStencil &st
     return pair_grid() * t.T + (sel ? t.off1 : 0) + (st.base[2] - l2) * sz + (st.base[1] - l1) * sy + (st.base[0] - l0);
 }
 
+// v of lane `from` of the four consecutive lanes.
+template <int kFrom>
+__device__ __forceinline__ int quad_lane(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, 0x55 * kFrom, 0xF, 0xF, true);   // quad_perm from, from, from, from
+}
+
+// Adds lane kFrom's c[0 .. nch) at its node id (none when negative), one channel per lane of
+// the four.
+template <int kFrom>
+__device__ __forceinline__ void ad_add_quad(float4 *x, long long id, const float (&c)[4], int nch) {
+    const int lo = quad_lane<kFrom>((int)id), hi = quad_lane<kFrom>((int)(id >> 32)), ch = (int)threadIdx.x & 3;
+    float v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = __int_as_float(quad_lane<kFrom>(__float_as_int(c[k])));
+    const float mine = ch == 0 ? v[0] : ch == 1 ? v[1] : ch == 2 ? v[2] : v[3];
+    const long long at = (long long)((unsigned long long)(unsigned int)hi << 32 | (unsigned int)lo);
+    if (hi >= 0 && ch < nch) atomicAdd(reinterpret_cast<float *>(x + at) + ch, mine);
+}
+
+// Every lane's contribution to a node straight to the node array x, for workgroups whose tile
+// is off (every lane calls it; id negative: none).  Four consecutive lanes take the four
+// channels of one of their nodes at a time, as in the flush: with a lane's four channels one
+// after the other, a wave's every atomic met 64 cache lines instead of 16 (65,536 particles
+// in random order: P2G 399 us against 110, G2P adjoint 272 against 103).
+__device__ __forceinline__ void ad_add(float4 *x, long long id, const float (&c)[4], int nch) {
+    ad_add_quad<0>(x, id, c, nch);
+    ad_add_quad<1>(x, id, c, nch);
+    ad_add_quad<2>(x, id, c, nch);
+    ad_add_quad<3>(x, id, c, nch);
+}
+
 // Called by every thread after its adds: every nonzero value of the tile to the node
 // array x.  Four consecutive lanes take a node's channels, so that a wave's atomics go to
 // consecutive addresses.
@@ -751,29 +782,36 @@ __global__ void __launch_bounds__(256) k_ad_p2g(AdArgs a, const float *state, co
     AdTile t;
     int sel;
     ad_tile_begin(valid, st, bnd, 4, tw, sh, t, sel);
-    if (valid) {
-        int sy = 0, sz = 0;
-        const int r0 = t.on ? ad_tile_base(t, st, sel, sy, sz) : 0;
+    const auto terms = [&](int o, float (&c)[4]) {
+        float w, d[3], gw[3];
+        ad_weights(a, st, o, w, d, gw);
+        c[0] = w * a.mass;
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax)
+            c[1 + ax] = w * (a.mass * v[ax] + Q[3 * ax] * d[0] + Q[3 * ax + 1] * d[1] + Q[3 * ax + 2] * d[2]);
+    };
+    if (!t.on) {   // the whole workgroup
+        for (int i = 0; i < 8; ++i) {
+            const int o = ad_turn(i);
+            float c[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            long long id = -1;
+            if (valid) {
+                terms(o, c);
+                id = ad_index<kSparse>(a, pair_grid(), st.base[0] + (o & 1), st.base[1] + ((o >> 1) & 1), st.base[2] + (o >> 2));
+            }
+            ad_add(x4, id, c, 4);
+        }
+    } else if (valid) {
+        int sy, sz;
+        const int r0 = ad_tile_base(t, st, sel, sy, sz);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int o = ad_turn(i), ox = o & 1, oy = (o >> 1) & 1, oz = o >> 2;
-            float w, d[3], gw[3];
-            ad_weights(a, st, o, w, d, gw);
             float c[4];
-            c[0] = w * a.mass;
+            terms(o, c);
+            unsigned long long *tp = t.w + r0 + ox + oy * sy + oz * sz;
 #pragma unroll
-            for (int ax = 0; ax < 3; ++ax)
-                c[1 + ax] = w * (a.mass * v[ax] + Q[3 * ax] * d[0] + Q[3 * ax + 1] * d[1] + Q[3 * ax + 2] * d[2]);
-            if (t.on) {
-                unsigned long long *tp = t.w + r0 + ox + oy * sy + oz * sz;
-#pragma unroll
-                for (int ch = 0; ch < 4; ++ch) atomicAdd(tp + ch * 2 * t.T, ad_fixed(c[ch], t.S));
-            } else {
-                float *tp = reinterpret_cast<float *>(
-                    x4 + ad_index<kSparse>(a, pair_grid(), st.base[0] + ox, st.base[1] + oy, st.base[2] + oz));
-#pragma unroll
-                for (int ch = 0; ch < 4; ++ch) atomicAdd(tp + ch, c[ch]);
-            }
+            for (int ch = 0; ch < 4; ++ch) atomicAdd(tp + ch * 2 * t.T, ad_fixed(c[ch], t.S));
         }
     }
     ad_tile_flush<kSparse>(a, t, x4, 4);
@@ -996,6 +1034,22 @@ __global__ void __launch_bounds__(256) k_ad_g2p_vjp(AdArgs a, const float *state
     AdTile t;
     int sel;
     ad_tile_begin(valid, st, bnd, 3, tw, sh, t, sel);
+    if (!t.on) {   // the whole workgroup
+        for (int i = 0; i < 8; ++i) {
+            const int o = ad_turn(i);
+            float c[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            long long at = -1;
+            if (valid) {
+                float w, d[3], gw[3];
+                ad_weights(a, st, o, w, d, gw);
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax)
+                    c[ax] = 0.5f * w * (vbt[ax] + Bbt[3 * ax] * d[0] + Bbt[3 * ax + 1] * d[1] + Bbt[3 * ax + 2] * d[2]);
+                at = ad_index<kSparse>(a, lane_g, st.base[0] + (o & 1), st.base[1] + ((o >> 1) & 1), st.base[2] + (o >> 2));
+            }
+            ad_add(vb4, at, c, 3);
+        }
+    }
     if (valid) {
         // one pass over the nodes: the forward B' (for C and (D^-1)b), and
         // v' = 1/2 sum w v~,  B' = 1/2 sum w v~ d^T:
@@ -1029,10 +1083,6 @@ __global__ void __launch_bounds__(256) k_ad_g2p_vjp(AdArgs a, const float *state
                 unsigned long long *tp = t.w + r0 + ox + oy * sy + oz * sz;
 #pragma unroll
                 for (int ax = 0; ax < 3; ++ax) atomicAdd(tp + ax * 2 * t.T, ad_fixed(0.5f * w * gv[ax], t.S));
-            } else {
-                float *tp = reinterpret_cast<float *>(vb4 + id[i]);
-#pragma unroll
-                for (int ax = 0; ax < 3; ++ax) atomicAdd(tp + ax, 0.5f * w * gv[ax]);
             }
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
