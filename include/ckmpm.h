@@ -167,7 +167,10 @@ mpm_status mpm_grid_update(mpm_ctx *ctx, double dt, void *stream);
  * F <- (I + dt B_p D_p^-1) F (applied to H = F - I), Drucker-Prager return mapping,
  * x <- x + dt v_p.  Writes the new state into the other buffer in the order of the
  * preceding mpm_p2g (ids and materials permuted alongside), computes the next cell
- * keys, and flips p->current. */
+ * keys, and flips p->current.  A particle that leaves the domain (MPM_E_DOMAIN) is stored
+ * once more and not placed by the steps after this one; nor are those of a block above its
+ * capacity (MPM_E_CAPACITY), or of one whose keys are stale.  The others go on, in the first
+ * positions: what the last ones hold is then unspecified. */
 mpm_status mpm_g2p(mpm_ctx *ctx, mpm_particles *p, double dt, void *stream);
 
 /* nsteps x (p2g, grid_update, g2p), enqueued back to back without host syncs.  Inside
@@ -198,7 +201,7 @@ mpm_status mpm_step(mpm_ctx *ctx, mpm_particles *p, double dt, int32_t nsteps, v
  *     before any GPU work.  A 32^3-cell grid with 32,768 particles and max_blocks 729
  *     needs about 14 MB.
  *   - Every call starts from a cleared state (keys, stress and page tables are
- *     recomputed from the particles) by fill kernels on `stream`; nothing carries over
+ *     recomputed from the particles) by a kernel on `stream`; nothing carries over
  *     from the previous call, whose contents stay in the array.
  *   - Calls that overlap on one GPU share the array and race: serialise them (one
  *     stream, or events).
