@@ -2181,7 +2181,8 @@ __global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_grad(DevCtx d, PartArgs 
 
 // As the MLS forms, with the same loop, prefetch and sharing of blocks; three waves per
 // SIMD.  500,000 particles: 56.9 us with all 16 nodes' gradients in full (211 VGPRs, two
-// waves), 39.0 us from separable sums, 40.4 us with the grid update folded in.
+// waves), 40.3 us from separable sums, 41.1 us with the grid update folded in (the last step's
+// kernel and an inner one's).
 __global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_grad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
     b_g2p<false, false, true, false, G2P_GRAD>(d, pa, dt, gp, gt);
 }
@@ -2198,7 +2199,8 @@ __global__ void __launch_bounds__(kP2GThreads, 4) k_p2g_quad(DevCtx d, PartArgs 
 }
 
 // 500,000 particles: 55 us with 27 products and six moments per component (two waves per
-// SIMD), 37.2 us from separable sums (three waves), 38.9 us with the grid update folded in.
+// SIMD), 39.4 us from separable sums (three waves), 37.6 us in the steps whose grid update is
+// folded in.
 __global__ void __launch_bounds__(kG2PThreads, 3) k_g2p_quad(DevCtx d, PartArgs pa, float dt, int gp, int gt) {
     b_g2p<false, false, true, false, G2P_QUAD>(d, pa, dt, gp, gt);
 }
