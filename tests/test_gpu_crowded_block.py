@@ -2,7 +2,7 @@
 steps of one call: its range of sorted positions is never ordered, and the keys at those
 positions are left over from before the sort.  The call reports MPM_E_CAPACITY, no kernel
 follows an order that was not formed, and the context (or the job beside it) goes on
-exactly.  Against the FP64 checker."""
+exactly.  Against the FP64 oracle."""
 import numpy as np
 import pytest
 
@@ -53,7 +53,7 @@ def first_by_id(parts, ids):
     return {k: v[at] for k, v in d.items()}
 
 
-def _checker(form, sc, steps):
+def _oracle(form, sc, steps):
     st = oracle_state(dict(x=sc.x, v=sc.v, B=sc.B, F=sc.F))
     for _ in range(steps):
         if form in KINDS:
@@ -81,13 +81,13 @@ def test_context_after_a_crowded_block(form, n_cells):
         ck.check(ck.mpm_step(run.ctx.h, p.c, sc.dt, steps, run.stream))
     assert ck.mpm_sync(run.ctx.h, run.stream) == ck.MPM_E_CAPACITY
     # the bodies' particles, which hold the first positions, went on as if the others were not there
-    _match(first_by_id(p, ids), _checker(form, sc, 8), "%s beside a crowded block" % form)
+    _match(first_by_id(p, ids), _oracle(form, sc, 8), "%s beside a crowded block" % form)
     p.c.n = p.n = sc.n
     p.load(sc.x, sc.v, sc.B, sc.F)
     ck.check(ck.mpm_invalidate(run.ctx.h))
     got = run.steps(sc.dt, 3)
     assert got["status"] == 0
-    _match(got, _checker(form, sc, 3), "%s after a crowded block" % form)
+    _match(got, _oracle(form, sc, 3), "%s after a crowded block" % form)
     run.close()
 
 
@@ -102,7 +102,7 @@ def test_noalloc_after_a_crowded_block():
                                            scene.dt, 4, status.data_ptr(), torch.cuda.current_stream()))
         torch.cuda.synchronize()
         assert int(status.item()) == want
-    _match(parts.read_by_id(), _checker("mls", sc, 4), "no-alloc call after a crowded block")
+    _match(parts.read_by_id(), _oracle("mls", sc, 4), "no-alloc call after a crowded block")
 
 
 @pytest.mark.parametrize("grouped", [False, True])
@@ -114,7 +114,7 @@ def test_crowded_job_fails_alone(grouped):
     srv.drain()
     info = srv.info(jids[1])
     assert info.state == ckmpm.MPM_JOB_FAILED and info.status == ckmpm.MPM_E_CAPACITY
-    st = _checker("mls", sc, 8)
+    st = _oracle("mls", sc, 8)
     for j in (jids[0], jids[2]):
         assert srv.info(j).state == ckmpm.MPM_JOB_DONE
         _match(srv.read(j), st, "job beside a crowded one (%s)" % ("grouped" if grouped else "per job"))

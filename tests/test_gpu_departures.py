@@ -1,13 +1,13 @@
 """Particles that leave the domain one after another during a sequence of steps: the call
 reports MPM_E_DOMAIN and they are not placed any more, while every other particle goes on
 exactly, in this call and in those after it.  In every form of the step, on lattices that
-sort in one launch and in several.  Against the FP64 checker on the other particles."""
+sort in one launch and in several.  Against the FP64 oracle on the other particles."""
 import numpy as np
 import pytest
 
 import scenes
 from gpu_util import GpuRun
-from test_gpu_crowded_block import FORMS, _checker, _match, first_by_id
+from test_gpu_crowded_block import FORMS, _oracle, _match, first_by_id
 
 pytestmark = pytest.mark.gpu
 
@@ -42,7 +42,7 @@ def test_the_others_go_on(form, n_cells):
         seen = [run.steps(sc.dt, k)["status"] for k in calls]
         assert run.ck.MPM_E_DOMAIN in seen and set(seen) <= {run.ck.MPM_OK, run.ck.MPM_E_DOMAIN}
         assert seen[-1] == run.ck.MPM_OK   # nobody is left to leave
-        _match(first_by_id(run.parts, ids), _checker(form, sc, 9), "%s, calls of %s" % (form, calls))
+        _match(first_by_id(run.parts, ids), _oracle(form, sc, 9), "%s, calls of %s" % (form, calls))
         s, stats = run.ck.mpm_get_stats(run.ctx.h, run.stream)
         assert s == 0 and stats.status_bits == 0
         run.close()
@@ -58,4 +58,4 @@ def test_the_others_go_on_without_allocation():
                                        status.data_ptr(), torch.cuda.current_stream()))
     torch.cuda.synchronize()
     assert int(status.item()) == ckmpm.MPM_E_DOMAIN
-    _match(first_by_id(parts, ids), _checker("mls", sc, 9), "no-alloc call")
+    _match(first_by_id(parts, ids), _oracle("mls", sc, 9), "no-alloc call")

@@ -1,6 +1,6 @@
 """Small bodies in the first and the last blocks of large lattices: compaction by sums over the
 chunks of 1,024 blocks before, and, above 24,576 chunks, after a scan of their counts; as a
-context of its own and as a job of a grouped server.  The FP64 checker steps each body on a
+context of its own and as a job of a grouped server.  The FP64 oracle steps each body on a
 small grid around it, its origin moved by whole blocks."""
 import numpy as np
 import pytest

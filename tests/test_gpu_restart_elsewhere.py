@@ -1,12 +1,12 @@
 """A context taken to a body somewhere else (mpm_invalidate): the grid blocks that the last
 step stamped for the old body are not allocated again beside the new one's, so that a pool
 that fits each body is enough.  In every form of the step, on lattices that sort in one
-launch and in several.  Against the FP64 checker."""
+launch and in several.  Against the FP64 oracle."""
 import numpy as np
 import pytest
 
 from gpu_util import GpuRun
-from test_gpu_crowded_block import FORMS, _bodies, _checker, _match
+from test_gpu_crowded_block import FORMS, _bodies, _oracle, _match
 
 pytestmark = pytest.mark.gpu
 
@@ -46,7 +46,7 @@ def test_pool_that_fits_each_body(form, n_cells):
         ck.check(ck.mpm_invalidate(run.ctx.h))
         got = run.steps(sc.dt, 3)
         assert got["status"] == 0
-        _match(got, _checker(form, sc, 3), "%s, from elsewhere" % form)
+        _match(got, _oracle(form, sc, 3), "%s, from elsewhere" % form)
         s, stats = ck.mpm_get_stats(run.ctx.h, run.stream)
         assert s == 0 and stats.n_grid_blocks <= room
     run.close()
